@@ -126,8 +126,10 @@ def time_solves(solver, b, steps, warmup):
 # operator variant index -> (prefetch, occupancy, tile) template arguments; N <= 7 asks for 4 waves
 def _variant_args(variant, N, fp64=False):
     mw = 4 if N <= 7 else 2
-    if variant == 5 and fp64:  # the FP64 factor ring (N = 7); other orders launch variant 0
-        return (0, mw, 3) if N == 7 else (1, 1, 0)
+    if variant in (3, 5) and fp64:  # one thread per pencil (ordinary, non-temporal factor loads)
+        return (N + 1 if N <= 7 else 4 if N <= 10 else 0, 4 if N <= 3 else 3 if N <= 7 else 2, 7 if variant == 3 else 3)
+    if variant == 4 and not fp64:  # one thread per pencil, BF16 factors in LDS
+        return (0, mw, 6)
     if variant == 6 and fp64:  # variant 2 with elements in launch order
         return (1, mw, 5)
     if variant == 6 and N == 7:  # matrix-core contractions (BF16 factors at N = 7)

@@ -299,7 +299,8 @@ sem_status sem_reset_counts(sem_ctx *ctx);
  * events on the solve's stream when the environment sets SEMCHEB_TIME_KRYLOV_OP=1;
  * empty otherwise; box meshes with stored factors), "ax_tuning" (all levels, `level` ignored: per level the
  * chosen FP64 operator variant, the measured time in microseconds of each of
- * the 7 variants (-1 where not timed; variant 6 is, for BF16 factors at N = 7
+ * the 7 variants (-1 where not timed; variants 3 and 5 for FP64 and 4 for BF16
+ * factors run one thread per pencil, variant 6 is, for BF16 factors at N = 7
  * only, the operator with its contractions on the matrix cores and, for FP64
  * factors, variant 2 with the elements taken in launch order), then the same
  * for single precision).

@@ -770,7 +770,7 @@ sem_status autotune_operator(sem_ctx *c, hipStream_t s) {
       return SEM_EINVAL;
     }
     for (auto &L : c->levels) {
-      // the trilinear operator has two variants (occupancy); other requests fall back to 0
+      // the trilinear operator has three variants; other requests fall back to 0
       L.ax_variant64 = v < (L.tri64 ? kAxTriVariants : kAxVariants64) ? v : 0;
       L.ax_variant32 = v < (L.tri32 ? kAxTriVariants : kAxVariants) ? v : 0;
     }
@@ -791,9 +791,13 @@ sem_status autotune_operator(sem_ctx *c, hipStream_t s) {
   // Levels whose streamed data fits the device's last-level cache many times over would be
   // timed warm by back-to-back launches, while inside a solve their data arrives from HBM
   // (the finer level's passes evict it). They are timed one launch at a time after an
-  // eviction: a 512 MB scratch buffer is overwritten before each timed launch.
+  // eviction: a 512 MB scratch buffer is overwritten before each timed launch. Where the
+  // finest level's own data fits as well, nothing evicts anything inside a solve either
+  // and the warm time decides (16^3, N = 7, FP64: 21 against 24 us for two variants that
+  // rank the other way after an eviction).
   constexpr size_t kEvictBytes = size_t(512) << 20;
   constexpr double kColdBelow = 192.0 * (1 << 20);
+  double finest_bytes[2] = {0.0, 0.0};
   void *evict = nullptr;
   sem_status st = SEM_OK;
   for (size_t j = 0; j + 1 < c->levels.size() && st == SEM_OK; ++j) {
@@ -811,7 +815,8 @@ sem_status autotune_operator(sem_ctx *c, hipStream_t s) {
       for (int v = 0; v < kAxVariants; ++v) times[v] = v < nvar ? 1e30f : -1.0f;
       const double nodes = (double)L.E * (L.N + 1) * (L.N + 1) * (L.N + 1);
       const double level_bytes = nodes * (trilinear ? (fp64 ? 16.0 : 8.0) : (fp64 ? 56.0 : 16.0));
-      bool cold = level_bytes < kColdBelow;
+      if (j == 0) finest_bytes[prec] = level_bytes;
+      bool cold = level_bytes < kColdBelow && finest_bytes[prec] >= kColdBelow;
       if (cold && !evict && hipMalloc(&evict, kEvictBytes) != hipSuccess) {
         (void)hipGetLastError();
         evict = nullptr;
@@ -1193,8 +1198,9 @@ sem_status setup_box_impl(const sem_box_mesh *mesh, const sem_options *opt, hipS
         TRY(upload(c, &L.gxw32, xw32.data(), xw32.size(), s));
       }
     }
-    TRY(upload(c, &L.D64, h.gll.D.data(), h.gll.D.size(), s));
-    std::vector<float> D32(h.gll.D.begin(), h.gll.D.end());
+    const std::vector<double> D64 = deriv_tables(h.gll);
+    TRY(upload(c, &L.D64, D64.data(), D64.size(), s));
+    std::vector<float> D32(D64.begin(), D64.end());
     TRY(upload(c, &L.D32, D32.data(), D32.size(), s));
     std::vector<double> inv(h.n);
     for (int64_t i = 0; i < h.n; ++i) inv[i] = 1.0 / h.diag[i];
@@ -1416,8 +1422,9 @@ sem_status setup_mesh_impl(const sem_mesh *mesh, const sem_options *opt, hipStre
     Level &L = c->levels[j];
     const bool coarse = j == nl - 1;
     TRY(upload(c, &L.G64, h.G.data(), h.G.size(), s));
-    TRY(upload(c, &L.D64, h.gll.D.data(), h.gll.D.size(), s));
-    std::vector<float> D32(h.gll.D.begin(), h.gll.D.end());
+    const std::vector<double> D64 = deriv_tables(h.gll);
+    TRY(upload(c, &L.D64, D64.data(), D64.size(), s));
+    std::vector<float> D32(D64.begin(), D64.end());
     TRY(upload(c, &L.D32, D32.data(), D32.size(), s));
     std::vector<double> inv(h.n), winv(h.n);
     for (int64_t i = 0; i < h.n; ++i) {

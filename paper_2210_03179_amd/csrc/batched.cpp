@@ -252,7 +252,6 @@ sem_status autotune_batched(sem_ctx *c, hipStream_t s) {
     std::vector<double> t(6, -1.0);
     int bestv = 0;
     for (int v = 0; v < 6 && st == SEM_OK; ++v) {
-      if (v == 5 && g.first != 7) continue;  // variant 5 is variant 0 at other FP64 orders
       t[v] = time_it([&] { launch_b_ax64(g.first, v, g.second, B.dev, s); });
       if (t[v] < t[bestv]) bestv = v;
     }

@@ -240,6 +240,14 @@ struct AxShape {
   static constexpr int min_waves = N <= 7 ? 4 : 2;
 };
 
+// Pencil operator in FP64: planes of factors requested with the input column, and the waves per
+// SIMD asked of the register allocator (its registers are the factors in flight: 12 per plane)
+template <int N>
+struct PencilShape {
+  static constexpr int pfk = N <= 7 ? N + 1 : (N <= 10 ? 4 : 0);
+  static constexpr int occ = N <= 3 ? 4 : (N <= 7 ? 3 : 2);
+};
+
 // PF = 1: the factors of plane k+1 are loaded while plane k computes (more registers);
 // PF = 0: each plane loads its own factors (fewer registers, latency hidden by occupancy).
 // The plane loop stays rolled (the FP64 kernel would not fit its registers
@@ -521,90 +529,6 @@ __device__ __forceinline__ void ax_body_tri(unsigned blk, const Box &b, int64_t 
     T *we = wL + e * n3;
 #pragma unroll
     for (int k = 0; k < n1; ++k) st_out(we + (k * n1 + j) * n1 + i, wreg[k]);
-  }
-}
-
-// ax_body_tri with the element's u tile in LDS (the structure of ax_body_tile): no
-// select-indexed register arrays, fewer VALU instructions per plane.
-template <int N, typename T>
-__device__ __forceinline__ void ax_body_tri_tile(unsigned blk, const Box &b, int64_t E, const T *__restrict__ u,
-                                                 const T *__restrict__ tri, const T *__restrict__ gxw,
-                                                 const T *__restrict__ Dm, T *__restrict__ wL) {
-  using S = AxShape<N>;
-  constexpr int n1 = S::n1, n3 = n1 * n1 * n1;
-  __shared__ T sD[n1 * n1];
-  __shared__ T su[S::epb][n1][n1][n1];
-  __shared__ T sr[S::epb][n1][n1];
-  __shared__ T ss[S::epb][n1][n1];
-  const int t = threadIdx.x;
-  const int le = t / S::tpe;
-  const int ij = t - le * S::tpe;
-  const int i = ij % n1, j = ij / n1;
-  const int64_t e = (int64_t)blk * S::epb + le;
-  const bool active = (le < S::epb) && (e < E);
-  const int lec = active ? le : 0;
-  for (int q = t; q < n1 * n1; q += S::block) sD[q] = Dm[q];
-
-  T ureg[n1], tt[n1];
-  int ex = 0, ey = 0, ez = 0;
-  if (active) {
-    const Exyz ec = elem_xyz(b, e);
-    ex = ec.x;
-    ey = ec.y;
-    ez = ec.z;
-  }
-  const int I = ex * N + i, J = ey * N + j;
-  const bool inIJ = active && I >= 1 && I <= b.nx && J >= 1 && J <= b.ny;
-  const int64_t gIJ = (int64_t)(I - 1) + (int64_t)b.nx * (J - 1);
-  const int64_t plane = (int64_t)b.nx * b.ny;
-#pragma unroll
-  for (int k = 0; k < n1; ++k) {
-    const int K = ez * N + k;
-    const bool ok = inIJ && K >= 1 && K <= b.nz;
-    const T v = u[ok ? gIJ + plane * (K - 1) : 0];
-    ureg[k] = ok ? v : T(0);
-    tt[k] = T(0);
-  }
-  const TriColumn<T> col = tri_column<N, T>(tri + (active ? e : 0) * 36, gxw, i, j);
-  if (active) {
-#pragma unroll
-    for (int k = 0; k < n1; ++k) su[lec][k][j][i] = ureg[k];
-  }
-  __syncthreads();
-  T Di[n1];
-#pragma unroll
-  for (int l = 0; l < n1; ++l) Di[l] = sD[i * n1 + l];
-#pragma unroll 1
-  for (int k = 0; k < n1; ++k) {
-    T g0, g1, g2, g3, g4, g5;
-    tri_factors<T>(col, gxw[k], gxw[n1 + k], g0, g1, g2, g3, g4, g5);
-    T ur = 0, us = 0, ut = 0;
-#pragma unroll
-    for (int l = 0; l < n1; ++l) {
-      ur += Di[l] * su[lec][k][j][l];
-      us += sD[j * n1 + l] * su[lec][k][l][i];
-      ut += Dm[k * n1 + l] * ureg[l];  // wave-uniform: scalar loads
-    }
-    const T wr = g0 * ur + g1 * us + g2 * ut;
-    const T ws = g1 * ur + g3 * us + g4 * ut;
-    const T wt = g2 * ur + g4 * us + g5 * ut;
-    if (active) {
-      sr[lec][j][i] = wr;
-      ss[lec][j][i] = ws;
-    }
-    __syncthreads();
-    T acc = 0;
-#pragma unroll
-    for (int l = 0; l < n1; ++l) acc += sD[l * n1 + i] * sr[lec][j][l] + sD[l * n1 + j] * ss[lec][l][i];
-    if (active) su[lec][k][j][i] = acc;  // every read of plane k happened before the barrier
-#pragma unroll
-    for (int l = 0; l < n1; ++l) tt[l] += Dm[k * n1 + l] * wt;
-    __syncthreads();
-  }
-  if (active) {
-    T *we = wL + e * n3;
-#pragma unroll
-    for (int k = 0; k < n1; ++k) st_out(we + (k * n1 + j) * n1 + i, su[lec][k][j][i] + tt[k]);
   }
 }
 
@@ -1000,107 +924,283 @@ __device__ __forceinline__ void ax_body_mfma(unsigned blk, const Box &b, int64_t
   }
 }
 
-// FP64 operator at N = 7 (one element per wave) with the factors streamed through a
-// ring of kRing planes in LDS by global-to-LDS DMA: while plane k computes, planes
-// k+1 .. k+kRing-1 are in flight, and no factor lives in registers. A plane is six
-// 512-byte component chunks, moved by three 16-byte-per-lane DMA loads (lanes 0-31 and
-// 32-63 take two components). The DMA writes are not tracked by the compiler: before
-// plane k is read, an explicit s_waitcnt leaves in flight only the loads of later planes,
-// and before a slot is refilled every LDS read of it has completed.
+// ------------------------------------------------------------------ pencil operator
+// Even-odd products with the GLL derivative matrix. The nodes are symmetric, so
+// D[N-i][N-l] = -D[i][l]: with the sums s_l = u_l + u_{N-l} and differences d_l = u_l - u_{N-l}
+// the rows i and N-i of D u are b_i + a_i and b_i - a_i with a = P s and b = Q d, where
+// P = (D[i][l] + D[i][N-l]) / 2 and Q = (D[i][l] - D[i][N-l]) / 2 are h x h, h = (N+1) / 2:
+// half the multiply-adds, and the tables fit the scalar registers of a wave. `eo` is the
+// table that follows D in the derivative arrays: P, Q, then for odd N+1 the middle column
+// and the middle row of D (h values each).
 template <int N>
-__device__ __forceinline__ void ax_body_ring64(unsigned blk, const Box &b, int64_t E, const double *__restrict__ u,
-                                               const double *__restrict__ G, const double *__restrict__ Dm,
-                                               double *__restrict__ wL, double *__restrict__ pdot = nullptr) {
-  static_assert(N == 7, "the ring variant assumes one 64-lane element per wave");
-  using T = double;
-  constexpr int n1 = N + 1, n2 = n1 * n1, n3 = n1 * n2;
-  constexpr int kRing = 4;
-  __shared__ __align__(16) T sG[kRing][6][n2];
-  __shared__ T sD[n2];
-  __shared__ T su[n1][n1][n1];
-  __shared__ T sr[n1][n1];
-  __shared__ T ss[n1][n1];
-  const int t = threadIdx.x;  // 64 threads
-  const int i = t % n1, j = t / n1;
-  const int64_t e = blk;
-  if (e >= E) {  // one element per block: the whole block leaves together
-    if (pdot && t == 0) pdot[blockIdx.x] = 0.0;
-    return;
-  }
-  sD[t] = Dm[t];
-  T ureg[n1], tt[n1];
-  const Exyz ec = elem_xyz(b, e);
-  const int I = ec.x * N + i, J = ec.y * N + j;
-  const bool inIJ = I >= 1 && I <= b.nx && J >= 1 && J <= b.ny;
-  const int64_t gIJ = (int64_t)(I - 1) + (int64_t)b.nx * (J - 1);
-  const int64_t plane = (int64_t)b.nx * b.ny;
+struct EvenOdd {
+  static constexpr int n1 = N + 1, h = n1 / 2, m = h;
+  static constexpr bool odd = (n1 & 1) != 0;
+  static constexpr int P = 0, Q = h * h, C = 2 * h * h, R = 2 * h * h + h;
+};
+
+// o = D u
+template <int N, typename T>
+__device__ __forceinline__ void eo_apply(const T *__restrict__ eo, const T (&u)[N + 1], T (&o)[N + 1]) {
+  using X = EvenOdd<N>;
+  T s[X::h], d[X::h];
 #pragma unroll
-  for (int k = 0; k < n1; ++k) {
-    const int K = ec.z * N + k;
-    const bool ok = inIJ && K >= 1 && K <= b.nz;
-    const T v = u[ok ? gIJ + plane * (K - 1) : 0];
-    ureg[k] = ok ? v : T(0);
-    tt[k] = T(0);
+  for (int l = 0; l < X::h; ++l) {
+    s[l] = u[l] + u[N - l];
+    d[l] = u[l] - u[N - l];
   }
-  // lane t moves bytes [16 (t % 32), +16) of component 2p + t / 32 of plane k
-  const char *gsrc = reinterpret_cast<const char *>(G + e * 6 * n3) + (t >> 5) * (n3 * 8) + (t & 31) * 16;
-  auto issue = [&](int k) {
-    char *dst = reinterpret_cast<char *>(&sG[k % kRing][0][0]);
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
-      __builtin_amdgcn_global_load_lds(gsrc + (int64_t)(2 * p) * (n3 * 8) + (int64_t)k * (n2 * 8),
-                                       (__attribute__((address_space(3))) void *)(dst + p * 1024), 16, 0,
-                                       kFactorCpol);
+  for (int i = 0; i < X::h; ++i) {
+    T a = 0, b = 0;
+#pragma unroll
+    for (int l = 0; l < X::h; ++l) {
+      a += eo[X::P + i * X::h + l] * s[l];
+      b += eo[X::Q + i * X::h + l] * d[l];
+    }
+    if constexpr (X::odd) a += eo[X::C + i] * u[X::m];
+    o[i] = b + a;
+    o[N - i] = b - a;
+  }
+  if constexpr (X::odd) {
+    T a = 0;
+#pragma unroll
+    for (int l = 0; l < X::h; ++l) a += eo[X::R + l] * d[l];
+    o[X::m] = a;
+  }
+}
+
+// o = D^T v
+template <int N, typename T>
+__device__ __forceinline__ void eo_apply_t(const T *__restrict__ eo, const T (&v)[N + 1], T (&o)[N + 1]) {
+  using X = EvenOdd<N>;
+  T p[X::h], q[X::h];
+#pragma unroll
+  for (int i = 0; i < X::h; ++i) {
+    p[i] = v[i] - v[N - i];
+    q[i] = v[i] + v[N - i];
+  }
+#pragma unroll
+  for (int l = 0; l < X::h; ++l) {
+    T a = 0, b = 0;
+#pragma unroll
+    for (int i = 0; i < X::h; ++i) {
+      a += eo[X::P + i * X::h + l] * p[i];
+      b += eo[X::Q + i * X::h + l] * q[i];
+    }
+    if constexpr (X::odd) b += eo[X::R + l] * v[X::m];
+    o[l] = a + b;
+    o[N - l] = a - b;
+  }
+  if constexpr (X::odd) {
+    T a = 0;
+#pragma unroll
+    for (int i = 0; i < X::h; ++i) a += eo[X::C + i] * p[i];
+    o[X::m] = a;
+  }
+}
+
+// Where the pencil operator takes the geometric factors from: stored, loaded into registers
+// (GEO_REG); stored as BF16, copied to LDS by global-to-LDS loads (GEO_DMA); formed from the
+// trilinear edge vectors (GEO_TRI).
+enum { GEO_REG = 0, GEO_DMA = 1, GEO_TRI = 2 };
+
+// The operator with one thread per pencil: a thread reads a whole line of n1 values of the
+// element once, multiplies it with D in registers (even-odd form, D from scalar registers) and
+// puts the line back, instead of reading n1 values from LDS for every output. Lines along t are
+// the thread's own (i, j) column; lines along r and s pass through two LDS tiles. Compared with
+// the plane loop of ax_body this needs 15 instead of about 50 LDS values per node, half the
+// multiply-adds, five barriers per element instead of three per plane, and every factor load
+// is independent of the contractions: PFK planes of factors are requested with the input
+// column, the rest once the first contractions have released their registers. Bound by HBM
+// for large meshes: 32^3 elements at N = 7, setup timing, FP64 159.0 (launch-order plane loop)
+// -> 153.9 us, BF16 factors 54.0 (matrix cores) -> 52.7 us, trilinear FP64 133.7 -> 93.6 us;
+// N = 9, 5.8 M nodes: FP64 77.3 -> 72.7, BF16 40.2 -> 31.0 us. With few elements (8^3, N = 7)
+// one memory latency instead of one per plane: 11.3 -> 7.9 us (FP64), 9.0 -> 7.0 us (BF16).
+// NT = false reads the factors with ordinary loads: at small odd sizes a plane of factors ends
+// inside a cache line whose rest the next plane's load finds in L1 (order 2: 98 -> 73 us, order
+// 4: 81 -> 71 us on 7 M local nodes; whole-line planes, order 7: no difference).
+template <int N, typename T, typename GT, int GEO, int PFK, bool MAP = false, bool NT = true>
+__device__ __forceinline__ void ax_body_pencil(unsigned blk, const Box &b, int64_t E, const T *__restrict__ u,
+                                               const GT *__restrict__ G, const T *__restrict__ Dm,
+                                               T *__restrict__ wL, const int32_t *__restrict__ map = nullptr,
+                                               double *__restrict__ pdot = nullptr,
+                                               const T *__restrict__ gxw = nullptr) {
+  using S = AxShape<N>;
+  constexpr int n1 = S::n1, n2 = n1 * n1, n3 = n2 * n1, epb = S::epb;
+  constexpr int rp = n1 | 1;  // odd row pitch: pencils along r start in distinct banks
+  constexpr bool full = epb == 1 && S::tpe == S::block;  // every thread has an element
+  constexpr int kElemBytes = 6 * n3 * 2;                 // BF16 factor block (GEO_DMA)
+  __shared__ __align__(16) uint16_t sG[GEO == GEO_DMA ? epb * 6 * n3 : 1];
+  __shared__ T sa[epb][n2 * rp];
+  __shared__ T sb[epb][n2 * rp];
+  const int t = threadIdx.x;
+  const int le = t / S::tpe;
+  const int ij = t - le * S::tpe;
+  const int i = ij % n1, j = ij / n1;
+  const int64_t e0 = (int64_t)blk * epb;
+  const int64_t e = e0 + le;
+  const bool active = full || ((le < epb) && (e < E));
+  const int lec = active ? le : 0;
+  const int64_t ec = active ? e : e0;
+  const T *eo = Dm + n2;
+  T col[n1];
+  if constexpr (MAP) {
+    int32_t gi[n1];
+#pragma unroll
+    for (int k = 0; k < n1; ++k) gi[k] = active ? map[ec * n3 + k * n2 + ij] : -1;
+#pragma unroll
+    for (int k = 0; k < n1; ++k) {
+      const T v = u[gi[k] >= 0 ? gi[k] : 0];
+      col[k] = gi[k] >= 0 ? v : T(0);
+    }
+  } else {
+    const Exyz x = elem_xyz(b, ec);
+    const int I = x.x * N + i, J = x.y * N + j;
+    const bool inIJ = active && I >= 1 && I <= b.nx && J >= 1 && J <= b.ny;
+    const int64_t gIJ = (int64_t)(I - 1) + (int64_t)b.nx * (J - 1);
+    const int64_t plane = (int64_t)b.nx * b.ny;
+#pragma unroll
+    for (int k = 0; k < n1; ++k) {
+      // unconditional load from a valid index, then select
+      const int K = x.z * N + k;
+      const bool ok = inIJ && K >= 1 && K <= b.nz;
+      const T v = u[ok ? gIJ + plane * (K - 1) : 0];
+      col[k] = ok ? v : T(0);
+    }
+  }
+  // inactive threads take the factors of a valid element; their products are not stored
+  const int ijc = active ? ij : 0;
+  [[maybe_unused]] T g[GEO == GEO_REG ? n1 : 1][6];
+  [[maybe_unused]] auto ld = [](const GT *p) -> T {
+    if constexpr (NT) return load_factor<GT, T>(p);
+    else return (T)*p;
   };
+  [[maybe_unused]] TriColumn<T> tri;
+  if constexpr (GEO == GEO_REG) {
 #pragma unroll
-  for (int k = 0; k < kRing; ++k) issue(k);
+    for (int k = 0; k < (PFK < n1 ? PFK : n1); ++k)
 #pragma unroll
-  for (int k = 0; k < n1; ++k) su[k][j][i] = ureg[k];
-  __syncthreads();
-  T Di[n1];
-#pragma unroll
-  for (int l = 0; l < n1; ++l) Di[l] = sD[i * n1 + l];
-  double dacc = 0.0;
-#pragma unroll 1
-  for (int k = 0; k < n1; ++k) {
-    // loads issued after plane k's: planes k+1 .. min(k+kRing-1, n1-1), three each
-    const int later = (n1 - 1 - k) < (kRing - 1) ? (n1 - 1 - k) : (kRing - 1);
-    if (later >= 3) asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
-    else if (later == 2) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-    else if (later == 1) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const T *gk = &sG[k % kRing][0][t];
-    const T g0 = gk[0 * n2], g1 = gk[1 * n2], g2 = gk[2 * n2], g3 = gk[3 * n2], g4 = gk[4 * n2], g5 = gk[5 * n2];
-    T ur = 0, us = 0, ut = 0;
-#pragma unroll
-    for (int l = 0; l < n1; ++l) {
-      ur += Di[l] * su[k][j][l];
-      us += sD[j * n1 + l] * su[k][l][i];
-      ut += Dm[k * n1 + l] * ureg[l];  // wave-uniform: scalar loads
+      for (int c = 0; c < 6; ++c) g[k][c] = ld(G + (ec * 6 + c) * n3 + k * n2 + ijc);
+  } else if constexpr (GEO == GEO_DMA) {
+    // every address lies inside the factor blocks of this block's elements; the copies are
+    // waited for below, before the factors are read
+    constexpr int kChunk = (kElemBytes % 16 == 0) ? 16 : 4;
+    constexpr int kWaves = S::block / 64;
+    const int64_t nel = (E - e0) < epb ? (E - e0) : epb;
+    const int nchunks = (int)(nel * kElemBytes / kChunk);
+    const char *src = reinterpret_cast<const char *>(G + e0 * 6 * n3);
+    const int wave = t >> 6, lane = t & 63;
+    for (int c0 = wave * 64; c0 < nchunks; c0 += kWaves * 64) {
+      if (c0 + lane < nchunks) {
+        const void *gp = src + (int64_t)(c0 + lane) * kChunk;
+        auto *lp = (__attribute__((address_space(3))) void *)(reinterpret_cast<char *>(sG) + c0 * kChunk);
+        if constexpr (kChunk == 16) __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, kFactorCpol);
+        else __builtin_amdgcn_global_load_lds(gp, lp, 4, 0, kFactorCpol);
+      }
     }
-    const T wr = g0 * ur + g1 * us + g2 * ut;
-    const T ws = g1 * ur + g3 * us + g4 * ut;
-    const T wt = g2 * ur + g4 * us + g5 * ut;
-    if (pdot) dacc += (double)(ur * wr + us * ws + ut * wt);
-    sr[j][i] = wr;
-    ss[j][i] = ws;
-    __syncthreads();
-    T acc = 0;
+  } else {
+    tri = tri_column<N, T>(reinterpret_cast<const T *>(G) + ec * 36, gxw, i, j);
+  }
+  T *A = sa[lec], *B = sb[lec];
+  // the thread's three pencils: column (i, j, :), row (:, i', j') and s-line (i', :, j')
+  const int cq = j * rp + i, rq = ij * rp, sq = j * (n1 * rp) + i;
+  if (active) {
 #pragma unroll
-    for (int l = 0; l < n1; ++l) acc += sD[l * n1 + i] * sr[j][l] + sD[l * n1 + j] * ss[l][i];
-    su[k][j][i] = acc;
+    for (int k = 0; k < n1; ++k) A[k * n1 * rp + cq] = col[k];
+  }
+  __syncthreads();
+  T ut[n1], vr[n1];
+  {
+    T ps[n1], vs[n1];
 #pragma unroll
-    for (int l = 0; l < n1; ++l) tt[l] += Dm[k * n1 + l] * wt;
-    __syncthreads();
-    if (k + kRing < n1) {
-      // every LDS read of slot k % kRing (the g values above) has completed
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      issue(k + kRing);
+    for (int l = 0; l < n1; ++l) ps[l] = A[(active ? sq : 0) + l * rp];
+    eo_apply<N, T>(eo, ps, vs);
+    if (active) {
+#pragma unroll
+      for (int l = 0; l < n1; ++l) B[sq + l * rp] = vs[l];
     }
   }
-  T *we = wL + e * n3;
+  {
+    T pr[n1];
 #pragma unroll
-  for (int k = 0; k < n1; ++k) st_out(we + (k * n1 + j) * n1 + i, su[k][j][i] + tt[k]);
+    for (int l = 0; l < n1; ++l) pr[l] = A[(active ? rq : 0) + l];
+    eo_apply<N, T>(eo, pr, vr);
+  }
+  eo_apply<N, T>(eo, col, ut);
+  __syncthreads();  // every pencil of A has been read
+  if (active) {
+#pragma unroll
+    for (int l = 0; l < n1; ++l) A[rq + l] = vr[l];
+  }
+  // (from order 8 on the last planes are requested in the plane loop, kNow planes ahead)
+  constexpr int kNow = N < 8 ? n1 : 5;
+  if constexpr (GEO == GEO_REG) {
+#pragma unroll
+    for (int k = PFK < n1 ? PFK : n1; k < kNow; ++k)
+#pragma unroll
+      for (int c = 0; c < 6; ++c) g[k][c] = ld(G + (ec * 6 + c) * n3 + k * n2 + ijc);
+  }
+  // the DMA copies are not tracked by the compiler; the barrier publishes every wave's share
+  if constexpr (GEO == GEO_DMA) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  double dacc = 0.0;
+  T wt[n1];
+#pragma unroll
+  for (int k = 0; k < n1; ++k) {
+    const int q = k * n1 * rp + (active ? cq : 0);
+    const T ur = A[q], us = B[q];
+    T g0, g1, g2, g3, g4, g5;
+    if constexpr (GEO == GEO_REG) {
+      if (k + kNow < n1)
+#pragma unroll
+        for (int c = 0; c < 6; ++c)
+          g[k + kNow][c] = ld(G + (ec * 6 + c) * n3 + (k + kNow) * n2 + ijc);
+      g0 = g[k][0]; g1 = g[k][1]; g2 = g[k][2]; g3 = g[k][3]; g4 = g[k][4]; g5 = g[k][5];
+    } else if constexpr (GEO == GEO_DMA) {
+      const uint16_t *Ge = sG + lec * 6 * n3 + k * n2 + ijc;
+      g0 = bf16_to_float(Ge[0 * n3]); g1 = bf16_to_float(Ge[1 * n3]); g2 = bf16_to_float(Ge[2 * n3]);
+      g3 = bf16_to_float(Ge[3 * n3]); g4 = bf16_to_float(Ge[4 * n3]); g5 = bf16_to_float(Ge[5 * n3]);
+    } else {
+      tri_factors<T>(tri, gxw[k], gxw[n1 + k], g0, g1, g2, g3, g4, g5);
+    }
+    const T wr = g0 * ur + g1 * us + g2 * ut[k];
+    const T ws = g1 * ur + g3 * us + g4 * ut[k];
+    wt[k] = g2 * ur + g4 * us + g5 * ut[k];
+    if (pdot && active) dacc += (double)(ur * wr + us * ws + ut[k] * wt[k]);
+    if (active) {  // the thread's own column again: no barrier in between
+      A[q] = wr;
+      B[q] = ws;
+    }
+  }
+  __syncthreads();
+  // in place: a pencil is read and written by the same thread
+  {
+    T ps[n1], vs[n1];
+#pragma unroll
+    for (int l = 0; l < n1; ++l) ps[l] = B[(active ? sq : 0) + l * rp];
+    eo_apply_t<N, T>(eo, ps, vs);
+    if (active) {
+#pragma unroll
+      for (int l = 0; l < n1; ++l) B[sq + l * rp] = vs[l];
+    }
+  }
+  {
+    T pr[n1];
+#pragma unroll
+    for (int l = 0; l < n1; ++l) pr[l] = A[(active ? rq : 0) + l];
+    eo_apply_t<N, T>(eo, pr, vr);
+    if (active) {
+#pragma unroll
+      for (int l = 0; l < n1; ++l) A[rq + l] = vr[l];
+    }
+  }
+  eo_apply_t<N, T>(eo, wt, ut);
+  __syncthreads();
+  if (active) {
+    T *we = wL + e * n3 + ij;
+#pragma unroll
+    for (int k = 0; k < n1; ++k) st_out(we + k * n2, A[k * n1 * rp + cq] + B[k * n1 * rp + cq] + ut[k]);
+  }
   if (pdot) block_sum_store(dacc, pdot + blockIdx.x);
 }
 

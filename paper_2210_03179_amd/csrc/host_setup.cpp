@@ -68,6 +68,17 @@ Gll make_gll(int N) {
   return g;
 }
 
+std::vector<double> deriv_tables(const Gll &g) {
+  const int N = g.N, n1 = N + 1, h = n1 / 2;
+  std::vector<double> t(g.D);
+  for (int sign : {1, -1})
+    for (int i = 0; i < h; ++i)
+      for (int l = 0; l < h; ++l) t.push_back(0.5 * (g.D[i * n1 + l] + sign * g.D[i * n1 + N - l]));
+  for (int i = 0; i < h; ++i) t.push_back(n1 % 2 ? g.D[i * n1 + h] : 0.0);
+  for (int l = 0; l < h; ++l) t.push_back(n1 % 2 ? g.D[h * n1 + l] : 0.0);
+  return t;
+}
+
 std::vector<double> make_interp(const Gll &f, const Gll &c) {
   const int nf = f.N + 1, nc = c.N + 1;
   std::vector<double> J(nf * nc);

@@ -18,6 +18,9 @@ struct Gll {
   std::vector<double> x, w, D;  // nodes, weights, D[i*(N+1)+l] = l_l'(x_i)
 };
 Gll make_gll(int N);
+// D followed by its even-odd tables (h = (N+1)/2): P and Q (h x h, (D[i][l] +- D[i][N-l]) / 2),
+// then the middle column and the middle row of D (h values each, zero for even N+1)
+std::vector<double> deriv_tables(const Gll &g);
 // J[i*(Nc+1)+a] = l_a^{(Nc)}(x_i^{(Nf)})
 std::vector<double> make_interp(const Gll &fine, const Gll &coarse);
 // beta_i^{(k)} of the optimised 4th-kind smoother: Table beta_coef of the supplementary
@@ -140,7 +143,7 @@ struct Level {
   // vectors, and the GLL nodes then weights of this order (both precisions as needed)
   double *tri64 = nullptr, *gxw64 = nullptr;
   float *tri32 = nullptr, *gxw32 = nullptr;
-  double *D64 = nullptr;      // (N+1)^2
+  double *D64 = nullptr;      // (N+1)^2, then the even-odd tables (deriv_tables)
   float *D32 = nullptr;
   double *J64 = nullptr;      // interpolation from the next level, (N+1) x (Nc+1)
   float *J32 = nullptr;
@@ -172,14 +175,14 @@ struct Level {
   float ax_time64_us[7] = {}, ax_time32_us[7] = {};  // kAxVariants
 };
 constexpr int kGmresScalars = 2 * 32 + 2;  // projections (<= 32), ||w||^2, y (<= 32)
-// variant 5 stages factors by DMA: the whole element block for BF16 factors, a ring of
-// planes for FP64 factors at N = 7 (other FP64 orders launch variant 0 for it); variant 6
-// runs the contractions on the matrix cores for BF16 factors at N = 7 (variant 5 at other
-// orders) and is variant 2 with elements taken in launch order for FP64 factors
+// FP64: variants 3 and 5 run one thread per pencil (ordinary and non-temporal factor loads),
+// variant 6 is variant 2 with elements taken in launch order. BF16 factors: variant 4 runs one
+// thread per pencil, variant 5 stages the factors by DMA, variant 6 runs the contractions on the
+// matrix cores (N = 7 only)
 constexpr int kAxVariants = 7;
 constexpr int kAxVariants64 = 7;
 constexpr int kAxVariantMfma = 6;
-constexpr int kAxTriVariants = 3;  // trilinear operator: (min_waves | 1 wave per SIMD) x register column, LDS tile
+constexpr int kAxTriVariants = 3;  // trilinear operator: register column (min_waves | 1 wave per SIMD), pencils
 
 struct CoarseSolver {
   bool dense = true;

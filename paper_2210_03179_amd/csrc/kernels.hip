@@ -23,8 +23,9 @@ using namespace dev;
 // Variants of the operator kernel chosen per level by the setup-time autotuner:
 // PF (factor prefetch), OCC (waves per SIMD requested from the register allocator)
 // and TILE (0: u column in registers with one LDS plane, 1: whole u tile in LDS,
-// 2: u tile and the element's BF16 factors in LDS, single precision only; 3: u tile and a
-// ring of FP64 factor planes in LDS, N = 7 only; 4: as 2 with every contraction on the
+// 2: u tile and the element's BF16 factors in LDS, single precision only; 3: one thread per
+// pencil, FP64; 6: one thread per pencil, BF16 factors in LDS; 7: as 3 with ordinary instead
+// of non-temporal factor loads; 4: as 2 with every contraction on the
 // matrix cores, BF16 factors at N = 7 only; 5: as 0 with the blocks taking elements in
 // launch order instead of keeping runs of consecutive elements on one XCD: the FP64
 // operator at 32^3, N = 7 then streams its factors as one front through memory and runs
@@ -36,7 +37,10 @@ ax_local_kernel(Box b, int64_t E, const T *__restrict__ u, const GT *__restrict_
                 const T *__restrict__ Dm, T *__restrict__ wL, double *__restrict__ pdot) {
   if constexpr (TILE == 5) ax_body<N, T, GT, PF>(blockIdx.x, b, E, u, G, Dm, wL, nullptr, pdot);
   else if constexpr (TILE == 4) ax_body_mfma<N>(xcd_block(blockIdx.x, gridDim.x), b, E, u, G, Dm, wL);
-  else if constexpr (TILE == 3) ax_body_ring64<N>(xcd_block(blockIdx.x, gridDim.x), b, E, u, G, Dm, wL, pdot);
+  else if constexpr (TILE == 3) ax_body_pencil<N, T, GT, GEO_REG, PF>(blockIdx.x, b, E, u, G, Dm, wL, nullptr, pdot);
+  else if constexpr (TILE == 7)
+    ax_body_pencil<N, T, GT, GEO_REG, PF, false, false>(blockIdx.x, b, E, u, G, Dm, wL, nullptr, pdot);
+  else if constexpr (TILE == 6) ax_body_pencil<N, T, GT, GEO_DMA, 0>(xcd_block(blockIdx.x, gridDim.x), b, E, u, G, Dm, wL);
   else if constexpr (TILE == 2) ax_body_dma<N>(xcd_block(blockIdx.x, gridDim.x), b, E, u, G, Dm, wL);
   else if constexpr (TILE == 1)
     ax_body_tile<N, T, GT, PF>(xcd_block(blockIdx.x, gridDim.x), b, E, u, G, Dm, wL, pdot);
@@ -44,13 +48,14 @@ ax_local_kernel(Box b, int64_t E, const T *__restrict__ u, const GT *__restrict_
 }
 
 // Operator of trilinear elements with factors computed in the kernel; OCC as above and
-// TILE 0 (ax_body_tri, u column in registers) or 1 (ax_body_tri_tile, u tile in LDS).
+// TILE 0 (ax_body_tri, u column in registers) or 1 (one thread per pencil).
 // Variants: 0 = (min_waves, 0), 1 = (1, 0), 2 = (min_waves, 1; FP64: 2 waves per SIMD).
 template <int N, typename T, int OCC, int TILE = 0>
 __global__ void __launch_bounds__(AxShape<N>::block, OCC)
 ax_tri_kernel(Box b, int64_t E, const T *__restrict__ u, const T *__restrict__ tri, const T *__restrict__ gxw,
               const T *__restrict__ Dm, T *__restrict__ wL) {
-  if constexpr (TILE == 1) ax_body_tri_tile<N, T>(xcd_block(blockIdx.x, gridDim.x), b, E, u, tri, gxw, Dm, wL);
+  if constexpr (TILE == 1)
+    ax_body_pencil<N, T, T, GEO_TRI, 0>(xcd_block(blockIdx.x, gridDim.x), b, E, u, tri, Dm, wL, nullptr, nullptr, gxw);
   else ax_body_tri<N, T>(xcd_block(blockIdx.x, gridDim.x), b, E, u, tri, gxw, Dm, wL);
 }
 
@@ -1305,8 +1310,9 @@ __device__ __forceinline__ Box lbox(const BatchLevelDev &L) {
 
 // Operator variants of the batched kernels, numbered as the single-system autotuner's:
 // 0 (prefetch, compiler's registers), 1 (no prefetch, min_waves), 2 (prefetch, min_waves),
-// 3 (u tile in LDS, prefetch), 4 (u tile in LDS, min_waves), 5 (single precision: factors
-// staged in LDS by DMA; FP64 at N = 7: ring of factor planes in LDS; other FP64 orders: 0).
+// 3 (single precision: u tile in LDS, prefetch; FP64: pencils, ordinary factor loads), 4
+// (single precision: pencils; FP64: u tile in LDS), 5 (single precision: factors staged in
+// LDS by DMA; FP64: pencils, non-temporal factor loads).
 // The batched setup times them on the batched launch of every order and level.
 template <int N, int V>
 struct BVar {
@@ -1329,20 +1335,21 @@ b_ax32_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int level, i
   // (the FP64 operator keeps launch order, which the single-system FP64 one prefers)
   const unsigned xb = xcd_block(blk, (unsigned)(tab.begin[slot_ + 1] - tab.begin[slot_]));
   if constexpr (TILE == 2) ax_body_dma<N>(xb, lbox(L), L.E, u, L.G, L.D, L.w);
+  else if constexpr (V == 4) ax_body_pencil<N, float, uint16_t, GEO_DMA, 0>(xb, lbox(L), L.E, u, L.G, L.D, L.w);
   else if constexpr (TILE == 1) ax_body_tile<N, float, uint16_t, PF>(xb, lbox(L), L.E, u, L.G, L.D, L.w);
   else ax_body<N, float, uint16_t, PF>(xb, lbox(L), L.E, u, L.G, L.D, L.w);
 }
 
 // FP64 operator on the finest level applied to the Krylov direction p
 template <int N, int V>
-__global__ void __launch_bounds__(AxShape<N>::block, ((V == 5 && N == 7) ? 4 : BVar<N, V>::occ))
+__global__ void __launch_bounds__(AxShape<N>::block, ((V == 3 || V == 5) ? PencilShape<N>::occ : BVar<N, V>::occ))
 b_ax64_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
   SEMCHEB_BATCH_SYS
   const BatchLevelDev &L = S.lev[0];
   constexpr int TILE = BVar<N, V>::tile, PF = BVar<N, V>::pf;
-  if constexpr (V == 5 && N == 7) ax_body_ring64<N>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64);
+  if constexpr (V == 3 || V == 5)
+    ax_body_pencil<N, double, double, GEO_REG, PencilShape<N>::pfk, false, V == 5>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64);
   else if constexpr (TILE == 1) ax_body_tile<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64);
-  else if constexpr (TILE == 2) ax_body<N, double, double, 1>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64);
   else ax_body<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64);
 }
 
@@ -1529,7 +1536,7 @@ void ax_launch(K kernel, dim3 grid, dim3 block, hipStream_t s, Args... args) {
 inline bool al16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 // variant 0: prefetch, compiler's register choice; 1: no prefetch, AxShape::min_waves;
-// 2: prefetch, AxShape::min_waves
+// 2: prefetch, AxShape::min_waves; 3 (FP64) and 5 (FP64), 4 (BF16): one thread per pencil
 template <int N, typename T, typename GT>
 void launch_ax_n(const Level &L, const T *u, const GT *G, const T *D, T *wL, int variant, hipStream_t s,
                  double *pdot = nullptr) {
@@ -1541,10 +1548,13 @@ void launch_ax_n(const Level &L, const T *u, const GT *G, const T *D, T *wL, int
       return;
     }
   }
-  if constexpr (sizeof(GT) == 8 && N == 7) {
+  if constexpr (sizeof(GT) == 8) {
+    if (variant == 3) {
+      ax_launch((ax_local_kernel<N, T, GT, PencilShape<N>::pfk, PencilShape<N>::occ, 7>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
+      return;
+    }
     if (variant == 5) {
-      ax_launch((ax_local_kernel<N, T, GT, 0, 4, 3>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u,
-                         G, D, wL, pdot);
+      ax_launch((ax_local_kernel<N, T, GT, PencilShape<N>::pfk, PencilShape<N>::occ, 3>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
       return;
     }
   }
@@ -1560,10 +1570,13 @@ void launch_ax_n(const Level &L, const T *u, const GT *G, const T *D, T *wL, int
       return;
     }
   }
-  if (variant == 3)
-    ax_launch((ax_local_kernel<N, T, GT, 1, 1, 1>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u,
-                       G, D, wL, pdot);
-  else if (variant == 4)
+  if (sizeof(GT) == 2 && variant == 3) {
+    if constexpr (sizeof(GT) == 2)
+      ax_launch((ax_local_kernel<N, T, GT, 1, 1, 1>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
+  } else if (sizeof(GT) == 2 && variant == 4) {
+    if constexpr (sizeof(GT) == 2)
+      ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves, 6>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
+  } else if (variant == 4)
     ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves, 1>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
   else if (variant == 1)
     ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves>), dim3(grid), dim3(S::block), s, mkbox(L),
@@ -1581,8 +1594,8 @@ void launch_ax_tri_n(const Level &L, const T *u, const T *tri, const T *gxw, con
                      hipStream_t s) {
   using S = AxShape<N>;
   const unsigned grid = (unsigned)((L.E + S::epb - 1) / S::epb);
-  // the LDS-tile form keeps the u column and the t-transpose sums in registers: FP64 asks
-  // for 2 waves per SIMD so they fit without spilling
+  // the pencil form holds whole lines and the column's edge sums: FP64 asks for 2 waves per
+  // SIMD so they fit without spilling
   constexpr int kTileOcc = sizeof(T) == 8 ? 2 : S::min_waves;
   if (variant == 2)
     hipLaunchKernelGGL((ax_tri_kernel<N, T, kTileOcc, 1>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u,
