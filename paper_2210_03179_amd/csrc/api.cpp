@@ -237,7 +237,7 @@ void smooth_schwarz(const sem_ctx *c, Level &L, int k, bool zero_guess, hipStrea
   const T *inv = V<T>::inv(L);
   auto applyS = [&](const T *v, int gmode, double a, double bc, double cc, int flags) {
     launch_schwarz_local<T>(L, v, V<T>::swS(L), V<T>::swD(L), V<T>::swY(L), s);
-    launch_schwarz_gather<T>(L, L.sw_kind, V<T>::swY(L), gmode, (T *)nullptr, r, d, x, a, bc, cc, flags, s);
+    launch_schwarz_gather<T>(L, V<T>::swY(L), gmode, (T *)nullptr, r, d, x, a, bc, cc, flags, s);
   };
   // out = src - DSS(w) (src = b or r), written as a plain global vector
   auto residual = [&](bool from_b, T *out) {
@@ -968,8 +968,7 @@ sem_status arnoldi_schwarz(sem_ctx *c, int j, double &out, hipStream_t s) {
     launch_ax(L, vk, L.w64, s);
     launch_dss<double>(L, L.w64, av, s);
     launch_schwarz_local<double>(L, av, L.swS64, L.swD64, L.swY64, s);
-    launch_schwarz_gather<double>(L, L.sw_kind, L.swY64, SWG_PLAIN, w, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0,
-                                  s);
+    launch_schwarz_gather<double>(L, L.swY64, SWG_PLAIN, w, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0, s);
     // classical Gram-Schmidt twice
     launch_multi_dot(n, k + 1, Vb, ld, w, c->partials, nb, s);
     launch_finalize_many(nb, k + 1, c->partials, dh, s);

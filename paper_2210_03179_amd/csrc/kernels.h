@@ -154,12 +154,13 @@ void launch_scale_inv_sqrt(int64_t n, const double *x, const double *nrm2, doubl
 // for every element (fast diagonalisation with Sm = [e][axis][nb][nb] eigenvectors and
 // Dinv = [e][nb^3], nb = N+3), then the node-wise weighted sum of the subdomain values
 // fused with the Chebyshev update selected by gmode (SWG_*) and flags (CHEB_D_INIT,
-// CHEB_X_INIT). z (optional) receives the smoothed value itself for SWG_PLAIN.
+// CHEB_X_INIT). L.sw_kind selects the layout of ye: [e][nb^3] for ASM, the element's own nodes
+// [e][(N+1)^3] for RAS. z (optional) receives the smoothed value itself for SWG_PLAIN.
 template <typename T>
 void launch_schwarz_local(const Level &L, const T *v, const T *Sm, const T *Dinv, T *ye, hipStream_t s);
 template <typename T>
-void launch_schwarz_gather(const Level &L, int kind, const T *ye, int gmode, T *z, T *r, T *d, T *x, double a,
-                           double bc, double c, int flags, hipStream_t s);
+void launch_schwarz_gather(const Level &L, const T *ye, int gmode, T *z, T *r, T *d, T *x, double a, double bc,
+                           double c, int flags, hipStream_t s);
 
 // out[0..n) = 0 with a kernel (no memset node when the caller captures a graph)
 template <typename T>

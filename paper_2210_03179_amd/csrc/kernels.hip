@@ -658,101 +658,120 @@ prolong_rows_kernel(Box fb, Box cb, const TC *__restrict__ xc, const T *__restri
 }
 
 // ------------------------------------------------------------------ Schwarz smoother
-// One block per element; thread (j, i) owns the column (i, j, :) of the extended
-// (N+3)^3 tile. The x and y contractions pass through one LDS plane, the z contraction and
-// the 1/D scaling stay in registers (fixed indices), the element's three eigenvector
-// matrices are staged in LDS.
+// Fast-diagonalisation solve of one extended element (nb = N + 3 unknowns per axis) per block,
+// one thread per line of nb values: a line is read once, multiplied with the axis' eigenvector
+// matrix in registers and put back, so a value crosses LDS once per direction instead of being
+// read nb times. The block's three matrices are wave-uniform and come through scalar registers.
+// Lines along z are the threads' own columns (registers only); x forward, the division by the
+// eigenvalue sums and x backward happen in one visit of a line. RAS keeps an element's own nodes
+// only: the last contractions skip the outer layer and the result is stored as an element-local
+// vector ([e][(N+1)^3]); ASM stores all nb^3 values. VALU bound (6 nb^4 multiply-adds per element).
+// 24^3 elements at N = 7, single precision, RAS: 178.8 -> 53.1 us per launch with one thread per
+// output and plane; order 3: 25.9 -> 13.0 us.
 template <int N>
 struct SwShape {
   static constexpr int nb = N + 3, nb2 = nb * nb, nb3 = nb2 * nb;
   static constexpr int block = (nb2 + 63) / 64 * 64;
 };
 
-template <int N, typename T>
+// o[c] = sum_k M[k * nb + c] v[k] (forward) and o[k] = sum_c M[k * nb + c] v[c] (backward), M
+// wave-uniform, one row of M at a time; the backward product only for rows lo <= k < hi
+template <int nb, typename T>
+__device__ __forceinline__ void sw_forward(const T *__restrict__ M, const T (&v)[nb], T (&o)[nb]) {
+#pragma unroll
+  for (int c = 0; c < nb; ++c) o[c] = 0;
+#pragma unroll
+  for (int k = 0; k < nb; ++k)
+#pragma unroll
+    for (int c = 0; c < nb; ++c) o[c] += M[k * nb + c] * v[k];
+}
+template <int nb, int lo, int hi, typename T>
+__device__ __forceinline__ void sw_backward(const T *__restrict__ M, const T (&v)[nb], T (&o)[nb]) {
+#pragma unroll
+  for (int k = lo; k < hi; ++k) {
+    T acc = 0;
+#pragma unroll
+    for (int c = 0; c < nb; ++c) acc += M[k * nb + c] * v[c];
+    o[k] = acc;
+  }
+}
+
+template <int N, typename T, bool RAS>
 __global__ void __launch_bounds__(SwShape<N>::block)
 schwarz_local_kernel(Box b, int64_t E, const T *__restrict__ v, const T *__restrict__ Sm,
                      const T *__restrict__ Dinv, T *__restrict__ ye) {
   using S = SwShape<N>;
-  constexpr int nb = S::nb, nb2 = S::nb2, nb3 = S::nb3;
-  __shared__ T sS[3 * nb2];
-  __shared__ T pl[nb2];
-  const int64_t e = xcd_block(blockIdx.x, gridDim.x);
-  if (e >= E) return;  // whole block
+  constexpr int nb = S::nb, nb2 = S::nb2, nb3 = S::nb3, n1 = N + 1;
+  constexpr int rp = nb | 1;                          // odd row pitch: lines along x in distinct banks
+  constexpr int lo = RAS ? 1 : 0, hi = RAS ? nb - 1 : nb;  // rows kept by the last contractions
+  __shared__ T A[nb2 * rp];
+  const int64_t e = xcd_block(blockIdx.x, gridDim.x);  // grid: one block per element
   const int t = threadIdx.x;
   const bool act = t < nb2;
-  const int i = act ? t % nb : 0, j = act ? t / nb : 0;
-  for (int q = t; q < 3 * nb2; q += S::block) sS[q] = Sm[e * 3 * nb2 + q];
+  const int tc = act ? t : 0;
+  const int i = tc % nb, j = tc / nb;
   const Exyz ec = elem_xyz(b, e);
   const int I = ec.x * N - 1 + i, J = ec.y * N - 1 + j;
   const bool inIJ = act && I >= 1 && I <= b.nx && J >= 1 && J <= b.ny;
   const int64_t gIJ = (int64_t)(I - 1) + (int64_t)b.nx * (J - 1), plane = (int64_t)b.nx * b.ny;
-  T col[nb];
+  T p[nb], q[nb], dv[nb];
 #pragma unroll
   for (int k = 0; k < nb; ++k) {
     const int K = ec.z * N - 1 + k;
     const bool ok = inIJ && K >= 1 && K <= b.nz;
     const T val = v[ok ? gIJ + plane * (K - 1) : 0];
-    col[k] = ok ? val : T(0);
+    p[k] = ok ? val : T(0);
+  }
+#pragma unroll
+  for (int a = 0; a < nb; ++a) dv[a] = Dinv[e * nb3 + (int64_t)tc * nb + a];  // line t along x
+  const T *Sx = Sm + e * 3 * nb2, *Sy = Sx + nb2, *Sz = Sy + nb2;
+  const int cz = j * rp + i, cy = j * nb * rp + i, cx = tc * rp;  // the thread's three lines
+  sw_forward<nb, T>(Sz, p, q);
+  if (act) {
+#pragma unroll
+    for (int k = 0; k < nb; ++k) A[k * nb * rp + cz] = q[k];
   }
   __syncthreads();
-  const T *Sx = sS, *Sy = sS + nb2, *Sz = sS + 2 * nb2;
-  // forward: (S_y^T S_x^T) per plane
 #pragma unroll
-  for (int k = 0; k < nb; ++k) {
-    if (act) pl[j * nb + i] = col[k];
-    __syncthreads();
-    T tx = 0;
+  for (int l = 0; l < nb; ++l) p[l] = A[cy + l * rp];
+  sw_forward<nb, T>(Sy, p, q);
+  if (act) {  // in place: a line is read and written by the same thread
 #pragma unroll
-    for (int l = 0; l < nb; ++l) tx += Sx[l * nb + i] * pl[j * nb + l];
-    __syncthreads();
-    if (act) pl[j * nb + i] = tx;
-    __syncthreads();
-    T ty = 0;
-#pragma unroll
-    for (int l = 0; l < nb; ++l) ty += Sy[l * nb + j] * pl[l * nb + i];
-    col[k] = ty;
-    __syncthreads();
+    for (int l = 0; l < nb; ++l) A[cy + l * rp] = q[l];
   }
-  // S_z^T, 1/D, S_z along the column
-  T u[nb];
+  __syncthreads();
 #pragma unroll
-  for (int c = 0; c < nb; ++c) {
-    T acc = 0;
+  for (int l = 0; l < nb; ++l) p[l] = A[cx + l];
+  sw_forward<nb, T>(Sx, p, q);
 #pragma unroll
-    for (int k = 0; k < nb; ++k) acc += Sz[k * nb + c] * col[k];
-    u[c] = act ? acc * Dinv[e * nb3 + (c * nb + j) * nb + i] : T(0);
+  for (int l = 0; l < nb; ++l) q[l] *= dv[l];
+  sw_backward<nb, lo, hi, T>(Sx, q, p);
+  if (act) {
+#pragma unroll
+    for (int l = lo; l < hi; ++l) A[cx + l] = p[l];
   }
+  __syncthreads();
 #pragma unroll
-  for (int k = 0; k < nb; ++k) {
-    T acc = 0;
+  for (int l = 0; l < nb; ++l) p[l] = A[cy + l * rp];
+  sw_backward<nb, lo, hi, T>(Sy, p, q);
+  if (act) {
 #pragma unroll
-    for (int c = 0; c < nb; ++c) acc += Sz[k * nb + c] * u[c];
-    col[k] = acc;
+    for (int l = lo; l < hi; ++l) A[cy + l * rp] = q[l];
   }
-  // backward: S_y then S_x per plane
-  T *out = ye + e * nb3;
+  __syncthreads();
+  if (!act || i < lo || i >= hi || j < lo || j >= hi) return;
 #pragma unroll
-  for (int k = 0; k < nb; ++k) {
-    if (act) pl[j * nb + i] = col[k];
-    __syncthreads();
-    T ty = 0;
+  for (int k = 0; k < nb; ++k) p[k] = A[k * nb * rp + cz];
+  sw_backward<nb, lo, hi, T>(Sz, p, q);
+  constexpr int no = RAS ? n1 : nb;  // stored values per axis
+  T *out = ye + e * (int64_t)(no * no * no) + (j - lo) * no + (i - lo);
 #pragma unroll
-    for (int l = 0; l < nb; ++l) ty += Sy[j * nb + l] * pl[l * nb + i];
-    __syncthreads();
-    if (act) pl[j * nb + i] = ty;
-    __syncthreads();
-    T tx = 0;
-#pragma unroll
-    for (int l = 0; l < nb; ++l) tx += Sx[i * nb + l] * pl[j * nb + l];
-    if (act) out[(k * nb + j) * nb + i] = tx;
-    __syncthreads();
-  }
+  for (int k = lo; k < hi; ++k) out[(k - lo) * no * no] = q[k];
 }
 
 // Subdomains containing lattice coordinate I along one axis (N >= 3): at most two, as
-// (element, subdomain-local index) pairs; ASM takes every subdomain, RAS only the
-// element's own nodes (local 1 .. N+1).
-__device__ __forceinline__ int sw_axis(int I, int N, const FastDiv &fN, int nelem, bool ras, int *el, int *loc) {
+// (element, subdomain-local index) pairs.
+__device__ __forceinline__ int sw_axis(int I, int N, const FastDiv &fN, int nelem, int *el, int *loc) {
   const int q = fdiv(fN, I), r = I - q * N;
   int cnt = 0;
   auto add = [&](int e, int l) {
@@ -764,53 +783,74 @@ __device__ __forceinline__ int sw_axis(int I, int N, const FastDiv &fN, int nele
   };
   add(q, r + 1);  // the element whose own nodes hold I (for r == 0: its local node 0)
   if (r == 0) add(q - 1, N + 1);
-  if (!ras) {
-    if (r == 1) add(q - 1, N + 2);
-    if (r == N - 1) add(q + 1, 0);
-  }
+  if (r == 1) add(q - 1, N + 2);
+  if (r == N - 1) add(q + 1, 0);
   return cnt;
 }
 
-template <typename T, int VEC>
+// The weighted node sum of the subdomain results fused with the Chebyshev update. RAS: the
+// element copies of the own nodes, averaged (the direct-stiffness gather of dss_ijk, all copies
+// requested at once); ASM: every subdomain that holds the node. The Chebyshev vectors are
+// requested before the copies. 24^3, N = 7, single precision, RAS: 35.5 -> 18.8 us (order 3: 15.8 -> 6.3).
+template <typename T, int VEC, bool RAS>
 __global__ void __launch_bounds__(256)
-schwarz_gather_kernel(Box b, int64_t n, int ras, const T *__restrict__ ye, int gmode, T *__restrict__ z,
+schwarz_gather_kernel(Box b, int64_t n, const T *__restrict__ ye, int gmode, T *__restrict__ z,
                       T *__restrict__ rv, T *__restrict__ d, T *__restrict__ x, T a, T bc, T c, int flags) {
   const int nb = b.N + 3;
   const int64_t nb3 = (int64_t)nb * nb * nb;
   const int64_t g0 = strided_first<VEC>(blockIdx.x);
   if (g0 >= n) return;
-  Ijk cc = ijk_of(b, g0);
+  T rr[VEC], dd[VEC], xx[VEC], zv[VEC];
 #pragma unroll
   for (int q = 0; q < VEC; ++q) {
     const int64_t g = g0 + 64 * q;
-    if (g < n) {
-      int ex[2], lx[2], ey[2], ly[2], ez[2], lz[2];
-      const int cx = sw_axis(cc.I, b.N, b.fN, b.nex, ras, ex, lx);
-      const int cy = sw_axis(cc.J, b.N, b.fN, b.ney, ras, ey, ly);
-      const int cz = sw_axis(cc.K, b.N, b.fN, b.nez, ras, ez, lz);
-      T acc = 0;
-      for (int w = 0; w < cz; ++w)
-        for (int v2 = 0; v2 < cy; ++v2)
-          for (int u2 = 0; u2 < cx; ++u2) {
-            const int64_t e = ex[u2] + (int64_t)b.nex * (ey[v2] + (int64_t)b.ney * ez[w]);
-            acc += ye[e * nb3 + ((int64_t)lz[w] * nb + ly[v2]) * nb + lx[u2]];
-          }
-      const T zv = acc / (T)(cx * cy * cz);
-      if (gmode == SWG_PLAIN) {
-        z[g] = zv;
-      } else if (gmode == SWG_CHEB4) {
-        const T dn = ((flags & CHEB_D_INIT) ? T(0) : a * d[g]) + bc * zv;
-        d[g] = dn;
-        x[g] = ((flags & CHEB_X_INIT) ? T(0) : x[g]) + c * dn;
+    const bool ok = g < n && gmode != SWG_PLAIN;
+    rr[q] = (ok && gmode == SWG_CHEB1 && !(flags & CHEB_D_INIT)) ? rv[g] : T(0);
+    dd[q] = (ok && !(flags & CHEB_D_INIT)) ? d[g] : T(0);
+    xx[q] = (ok && !(flags & CHEB_X_INIT)) ? x[g] : T(0);
+  }
+  Ijk cc = ijk_of(b, g0);
+#pragma unroll
+  for (int q = 0; q < VEC; ++q) {
+    if (g0 + 64 * q < n) {
+      if constexpr (RAS) {
+        int faces;
+        const T acc = dss_ijk(ye, b, cc, &faces);
+        zv[q] = acc * (T)inv_mult_faces(faces);
       } else {
-        const T rn = (flags & CHEB_D_INIT) ? zv : rv[g] - zv;
-        rv[g] = rn;
-        const T dn = ((flags & CHEB_D_INIT) ? T(0) : a * d[g]) + bc * rn;
-        d[g] = dn;
-        x[g] = ((flags & CHEB_X_INIT) ? T(0) : x[g]) + c * dn;
+        int ex[2], lx[2], ey[2], ly[2], ez[2], lz[2];
+        const int cx = sw_axis(cc.I, b.N, b.fN, b.nex, ex, lx);
+        const int cy = sw_axis(cc.J, b.N, b.fN, b.ney, ey, ly);
+        const int cz = sw_axis(cc.K, b.N, b.fN, b.nez, ez, lz);
+        T acc = 0;
+        for (int w = 0; w < cz; ++w)
+          for (int v2 = 0; v2 < cy; ++v2)
+            for (int u2 = 0; u2 < cx; ++u2) {
+              const int64_t e = ex[u2] + (int64_t)b.nex * (ey[v2] + (int64_t)b.ney * ez[w]);
+              acc += ye[e * nb3 + ((int64_t)lz[w] * nb + ly[v2]) * nb + lx[u2]];
+            }
+        zv[q] = acc / (T)(cx * cy * cz);
       }
     }
     if (q + 1 < VEC) ijk_advance(b, cc, 64);
+  }
+#pragma unroll
+  for (int q = 0; q < VEC; ++q) {
+    const int64_t g = g0 + 64 * q;
+    if (g >= n) continue;
+    if (gmode == SWG_PLAIN) {
+      z[g] = zv[q];
+    } else if (gmode == SWG_CHEB4) {
+      const T dn = a * dd[q] + bc * zv[q];
+      d[g] = dn;
+      x[g] = xx[q] + c * dn;
+    } else {
+      const T rn = (flags & CHEB_D_INIT) ? zv[q] : rr[q] - zv[q];
+      rv[g] = rn;
+      const T dn = a * dd[q] + bc * rn;
+      d[g] = dn;
+      x[g] = xx[q] + c * dn;
+    }
   }
 }
 
@@ -2004,8 +2044,12 @@ void launch_scale_inv_sqrt(int64_t n, const double *x, const double *nrm2, doubl
 
 template <int N, typename T>
 void launch_schwarz_local_n(const Level &L, const T *v, const T *Sm, const T *Dinv, T *ye, hipStream_t s) {
-  hipLaunchKernelGGL((schwarz_local_kernel<N, T>), dim3((unsigned)L.E), dim3(SwShape<N>::block), 0, s, mkbox(L),
-                     L.E, v, Sm, Dinv, ye);
+  if (L.sw_kind == SW_RAS)
+    hipLaunchKernelGGL((schwarz_local_kernel<N, T, true>), dim3((unsigned)L.E), dim3(SwShape<N>::block), 0, s,
+                       mkbox(L), L.E, v, Sm, Dinv, ye);
+  else
+    hipLaunchKernelGGL((schwarz_local_kernel<N, T, false>), dim3((unsigned)L.E), dim3(SwShape<N>::block), 0, s,
+                       mkbox(L), L.E, v, Sm, Dinv, ye);
 }
 template <typename T>
 void launch_schwarz_local(const Level &L, const T *v, const T *Sm, const T *Dinv, T *ye, hipStream_t s) {
@@ -2024,15 +2068,20 @@ template void launch_schwarz_local<float>(const Level &, const float *, const fl
                                           hipStream_t);
 
 template <typename T>
-void launch_schwarz_gather(const Level &L, int kind, const T *ye, int gmode, T *z, T *r, T *d, T *x, double a,
-                           double bc, double c, int flags, hipStream_t s) {
+void launch_schwarz_gather(const Level &L, const T *ye, int gmode, T *z, T *r, T *d, T *x, double a, double bc,
+                           double c, int flags, hipStream_t s) {
   constexpr int VEC = 16 / sizeof(T);
-  hipLaunchKernelGGL((schwarz_gather_kernel<T, VEC>), dim3(nblk((L.n + VEC - 1) / VEC)), dim3(256), 0, s, mkbox(L),
-                     L.n, kind == SW_RAS ? 1 : 0, ye, gmode, z, r, d, x, (T)a, (T)bc, (T)c, flags);
+  const unsigned grid = nblk((L.n + VEC - 1) / VEC);
+  if (L.sw_kind == SW_RAS)
+    hipLaunchKernelGGL((schwarz_gather_kernel<T, VEC, true>), dim3(grid), dim3(256), 0, s, mkbox(L), L.n, ye, gmode, z,
+                       r, d, x, (T)a, (T)bc, (T)c, flags);
+  else
+    hipLaunchKernelGGL((schwarz_gather_kernel<T, VEC, false>), dim3(grid), dim3(256), 0, s, mkbox(L), L.n, ye, gmode,
+                       z, r, d, x, (T)a, (T)bc, (T)c, flags);
 }
-template void launch_schwarz_gather<double>(const Level &, int, const double *, int, double *, double *, double *,
+template void launch_schwarz_gather<double>(const Level &, const double *, int, double *, double *, double *,
                                             double *, double, double, double, int, hipStream_t);
-template void launch_schwarz_gather<float>(const Level &, int, const float *, int, float *, float *, float *,
+template void launch_schwarz_gather<float>(const Level &, const float *, int, float *, float *, float *,
                                            float *, double, double, double, int, hipStream_t);
 
 template <typename T>

@@ -51,7 +51,7 @@ def test_pencil_operator_reduces_p_Ap(N, monkeypatch):
     hist = []
     for fused in ("1", "0"):
         monkeypatch.setenv("SEMCHEB_FUSED_KRYLOV", fused)
-        s = SemSolver(V, N=N, lambda_max=[2.0] * 3)
+        s = SemSolver(V, N=N)
         _, info = s.solve(b, rtol=1e-8)
         hist.append(info.history)
         s.close()
