@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libsemcheb.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["kernels.hip", "api.cpp", "host_setup.cpp", "batched.cpp"]
+SOURCES = ["kernels.hip", "sparse.hip", "api.cpp", "host_setup.cpp", "batched.cpp"]
 ARCH = os.environ.get("SEMCHEB_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -66,7 +66,7 @@ def build_host_sanitized(out_dir: str) -> str:
 
     def comp(src):
         obj = os.path.join(out_dir, os.path.splitext(src)[0] + ".o")
-        extra = SANITIZE if src != "kernels.hip" else []
+        extra = SANITIZE if not src.endswith(".hip") else []
         cmd = [HIPCC, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj] + COMMON + extra
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:

@@ -92,16 +92,27 @@ sem_status upload(sem_ctx *c, T **p, const T *src, size_t count, hipStream_t s) 
   return SEM_OK;
 }
 
-sem_status upload_csr(sem_ctx *c, DevCsr &d, const Csr &h, bool with32, hipStream_t s) {
+sem_status upload_ell(sem_ctx *c, EllArgs &d, const Csr &h, hipStream_t s) {
   d.nrows = h.nrows;
-  TRY(upload(c, &d.rowptr, h.rowptr.data(), h.rowptr.size(), s));
-  TRY(upload(c, &d.col, h.col.data(), h.col.size(), s));
-  TRY(upload(c, &d.val64, h.val.data(), h.val.size(), s));
-  if (with32) {
-    std::vector<float> v(h.val.begin(), h.val.end());
-    TRY(upload(c, &d.val32, v.data(), v.size(), s));
-    HIPCHK(c, hipStreamSynchronize(s));
+  d.ld = (h.nrows + 63) / 64 * 64;
+  d.width = 1;
+  for (int64_t r = 0; r < h.nrows; ++r) d.width = std::max(d.width, (int32_t)(h.rowptr[r + 1] - h.rowptr[r]));
+  std::vector<int32_t> col((size_t)d.width * d.ld, 0);
+  std::vector<double> val((size_t)d.width * d.ld, 0.0);
+  for (int64_t r = 0; r < h.nrows; ++r) {
+    const int64_t p0 = h.rowptr[r], p1 = h.rowptr[r + 1];
+    for (int64_t k = 0; k < d.width; ++k) {
+      const int64_t p = std::min(p0 + k, p1 - 1);  // padding repeats the last column with value 0
+      if (p1 > p0) col[k * d.ld + r] = h.col[p];
+      if (p0 + k < p1) val[k * d.ld + r] = h.val[p];
+    }
   }
+  int32_t *dc = nullptr;
+  double *dv = nullptr;
+  TRY(upload(c, &dc, col.data(), col.size(), s));
+  TRY(upload(c, &dv, val.data(), val.size(), s));
+  d.col = dc;
+  d.val = dv;
   return SEM_OK;
 }
 
@@ -187,7 +198,6 @@ template <> struct V<double> {
   static double *&w(Level &L) { return L.w64; }
   static const double *inv(const Level &L) { return L.invdiag64; }
   static const double *J(const Level &L) { return L.J64; }
-  static const double *val(const DevCsr &A) { return A.val64; }
   static const double *swS(const Level &L) { return L.swS64; }
   static const double *swD(const Level &L) { return L.swD64; }
   static double *swY(Level &L) { return L.swY64; }
@@ -203,7 +213,6 @@ template <> struct V<float> {
   static float *&w(Level &L) { return L.w32; }
   static const float *inv(const Level &L) { return L.invdiag32; }
   static const float *J(const Level &L) { return L.J32; }
-  static const float *val(const DevCsr &A) { return A.val32; }
   static const float *swS(const Level &L) { return L.swS32; }
   static const float *swD(const Level &L) { return L.swD32; }
   static float *swY(Level &L) { return L.swY32; }
@@ -222,8 +231,8 @@ void apply_level(Level &L, const T *u, T *w, hipStream_t s) {
   } else if (L.type == LVL_GEN) {  // unstructured mesh: element products, then their sums
     launch_ax_map(L, u, V<T>::wl(L), s);
     launch_sum_lists<T, T>(L, V<T>::wl(L), w, nullptr, false, s);
-  } else {
-    launch_csr(L.A, V<T>::val(L.A), u, (const T *)nullptr, w, 0, s);
+  } else if constexpr (sizeof(T) == 8) {  // sparse levels run in FP64 only
+    launch_ell(L.A, u, nullptr, w, 0, s);
   }
 }
 
@@ -295,6 +304,103 @@ bool krylov_op_timing_enabled() {
   return v && v[0] == '1';
 }
 
+// Centre and half width of the 1st kind's interval [lambda_min, lambda_max] for order k.
+void cheb1_interval(int kind, int k, double lmax, double &theta, double &delta) {
+  const double frac = kind == SEM_CHEB1 ? 0.1 : 1.69 / (std::pow((double)k, 1.68) + 2.11 * k + 1.98);
+  const double lmin = frac * lmax;
+  theta = 0.5 * (lmax + lmin);
+  delta = 0.5 * (lmax - lmin);
+}
+
+// Order-k Chebyshev smoothing of a sparse level (the recurrences of smooth below): one launch per
+// step, each with its own product, the first two steps from a zero guess in one launch. d moves
+// between the level's d and w vectors. A smoothing of order one has no second step to carry the
+// first one's x, so it keeps the product and the update apart.
+void smooth_ell(const sem_ctx *c, Level &L, int k, bool zero_guess, hipStream_t s) {
+  double *b = L.b64, *x = L.x64, *r = L.r64, *d = L.d64, *w = L.w64;
+  const double *inv = L.invdiag64;
+  const int kind = c->opt.smoother;
+  const int mode = kind == SEM_CHEB4 || kind == SEM_CHEB4_OPT ? 4 : 1;
+  double theta = 0.0, delta = 0.0, rho = 0.0;
+  if (mode == 1) {
+    cheb1_interval(kind, k, L.lmax, theta, delta);
+    rho = 1.0 / (theta / delta);
+  }
+  const double *beta = kind == SEM_CHEB4_OPT ? beta_row(k) : nullptr;
+  auto C = [&](int i) { return beta ? beta[i] : 1.0; };
+  auto coef = [&](int i, double &a, double &bc) {  // step i = 0 .. k-1
+    if (mode == 4) {
+      a = i ? (2.0 * i - 1.0) / (2.0 * i + 3.0) : 0.0;
+      bc = i ? ((8.0 * i + 4.0) / (2.0 * i + 3.0)) * (1.0 / L.lmax) : (4.0 / 3.0) * (1.0 / L.lmax);
+    } else if (i == 0) {
+      a = 0.0;
+      bc = 1.0 / theta;
+    } else {
+      const double rho_new = 1.0 / (2.0 * (theta / delta) - rho);
+      a = rho_new * rho;
+      bc = 2.0 * rho_new / delta;
+      rho = rho_new;
+    }
+  };
+  double a, bc;
+  coef(0, a, bc);
+  if (k == 1) {
+    if (!zero_guess) {
+      L.applies++;
+      launch_ell(L.A, x, nullptr, w, 0, s);
+    }
+    launch_cheb<double>(L, zero_guess ? nullptr : w, b, nullptr, nullptr, d, x, inv, 0.0, bc, C(0),
+                        CHEB_R_FROM_B | (mode == 1 ? CHEB_S_ON_R : 0) | CHEB_D_INIT | CHEB_LAST |
+                            (zero_guess ? CHEB_X_INIT : CHEB_SUB_AD),
+                        mode, s);
+    return;
+  }
+  const double bc0 = bc;
+  if (!zero_guess) {
+    L.applies++;
+    launch_ell_cheb(L.A, b, r, nullptr, d, x, inv, 0.0, bc0, C(0), 0.0, 0.0, ELL_FROM_X | CHEB_NO_X, mode, s);
+  }
+  for (int i = 1; i < k; ++i) {
+    coef(i, a, bc);
+    L.applies++;
+    launch_ell_cheb(L.A, b, r, d, w, x, inv, a, bc, C(i), bc0, C(0),
+                    (i == 1 ? (zero_guess ? ELL_FIRST2 : ELL_X_PLUS_D) : 0) | (i == k - 1 ? CHEB_LAST : 0), mode, s);
+    std::swap(d, w);
+  }
+}
+
+// The levels from tail_from down in one launch (see ell_tail_kernel), applications counted as
+// the separate launches would.
+void cycle_tail(sem_ctx *c, int pre, int post, hipStream_t s) {
+  TailArgs T{};
+  const int kind = c->opt.smoother;
+  T.mode = kind == SEM_CHEB4 || kind == SEM_CHEB4_OPT ? 4 : 1;
+  T.pre = pre;
+  T.post = post;
+  T.Minv = c->coarse.Minv;
+  for (int q = 0; q < 32; ++q) {
+    T.beta_pre[q] = kind == SEM_CHEB4_OPT && q < pre ? beta_row(pre)[q] : 1.0;
+    T.beta_post[q] = kind == SEM_CHEB4_OPT && q < post ? beta_row(post)[q] : 1.0;
+  }
+  for (size_t j = c->tail_from; j < c->levels.size(); ++j) {
+    Level &L = c->levels[j];
+    TailLevel &t = T.lev[T.nlev++];
+    t.n = (int)L.n;
+    t.A = L.A;
+    t.P = L.P;
+    t.R = L.R;
+    t.inv = L.invdiag64;
+    t.rlmax = L.lmax > 0.0 ? 1.0 / L.lmax : 0.0;
+    if (j + 1 < c->levels.size()) {
+      L.applies += pre + post;
+      cheb1_interval(kind, pre, L.lmax, t.theta[0], t.delta[0]);
+      cheb1_interval(kind, post, L.lmax, t.theta[1], t.delta[1]);
+    }
+  }
+  const Level &L = c->levels[c->tail_from];
+  launch_ell_tail(T, L.b64, L.x64, s);
+}
+
 // Order-k Chebyshev smoothing of A x = b on level L (Algorithms 1 and 2).
 // zero_guess: x starts at 0 (k-1 applies); otherwise from the current x (k applies).
 template <typename T>
@@ -303,6 +409,12 @@ void smooth(const sem_ctx *c, Level &L, int k, bool zero_guess, hipStream_t s) {
   if (L.sw_kind) {
     smooth_schwarz<T>(c, L, k, zero_guess, s);
     return;
+  }
+  if constexpr (sizeof(T) == 8) {
+    if (L.type == LVL_FD) {
+      smooth_ell(c, L, k, zero_guess, s);
+      return;
+    }
   }
   T *b = V<T>::b(L), *x = V<T>::x(L), *r = V<T>::r(L), *d = V<T>::d(L), *w = V<T>::w(L);
   const T *inv = V<T>::inv(L);
@@ -335,9 +447,8 @@ void smooth(const sem_ctx *c, Level &L, int k, bool zero_guess, hipStream_t s) {
                      4, s, B(1));
     }
   } else {
-    const double frac = kind == SEM_CHEB1 ? 0.1 : 1.69 / (std::pow((double)k, 1.68) + 2.11 * k + 1.98);
-    const double lmin = frac * lmax;
-    const double theta = 0.5 * (lmax + lmin), delta = 0.5 * (lmax - lmin);
+    double theta, delta;
+    cheb1_interval(kind, k, lmax, theta, delta);
     const double sigma = theta / delta;
     double rho = 1.0 / sigma;
     const int nox = zero_guess && k > 1 ? CHEB_NO_X : 0;  // x = d after the first step
@@ -461,10 +572,16 @@ void vcycle(sem_ctx *c, int j, hipStream_t s) {
   int pre = c->opt.pre_order, post = c->opt.post_order;
   // lattice levels (lattice multigrid below order 1): symmetric (m, m), m = max(pre, post)
   if (c->lattice_from >= 0 && j >= c->lattice_from) pre = post = std::max(pre, post);
+  if constexpr (sizeof(T) == 8) {
+    if (j == c->tail_from) {
+      cycle_tail(c, pre, post, s);
+      return;
+    }
+  }
   T *b = V<T>::b(L), *x = V<T>::x(L), *r = V<T>::r(L), *w = V<T>::w(L);
   if (pre > 0) {
     smooth<T>(c, L, pre, true, s);
-    apply_level<T>(L, x, w, s);
+    if (L.type != LVL_FD) apply_level<T>(L, x, w, s);
   } else {
     launch_zero<T>(L.n, x, s);
   }
@@ -498,9 +615,12 @@ void vcycle(sem_ctx *c, int j, hipStream_t s) {
     launch_gather_map<T>(L, r, V<T>::winv(L), V<T>::wl(L), s);
     launch_interp_elem<T>(L.E, C.N + 1, L.N + 1, V<T>::J(L), V<T>::wl(L), V<T>::wl(C), true, s);
     launch_sum_lists<T, T>(C, V<T>::wl(C), V<T>::b(C), nullptr, false, s);
-  } else {
-    launch_resid_weight<T>(L, ad, b, r, s);
-    launch_csr<T>(L.R, V<T>::val(L.R), r, (const T *)nullptr, V<T>::b(C), 0, s);
+  } else if constexpr (sizeof(T) == 8) {  // the residual with its product, then R = P^T
+    if (pre > 0) {
+      L.applies++;
+      launch_ell(L.A, x, b, r, 1, s);
+    }
+    launch_ell(L.R, pre > 0 ? r : b, nullptr, C.b64, 0, s);
   }
   if (to_lattice) vcycle<double>(c, j + 1, s);
   else vcycle<T>(c, j + 1, s);
@@ -521,8 +641,8 @@ void vcycle(sem_ctx *c, int j, hipStream_t s) {
     launch_gather_map<T>(C, V<T>::x(C), (const T *)nullptr, V<T>::wl(C), s);
     launch_interp_elem<T>(L.E, C.N + 1, L.N + 1, V<T>::J(L), V<T>::wl(C), V<T>::wl(L), false, s);
     launch_sum_lists<T, T>(L, V<T>::wl(L), x, V<T>::winv(L), true, s);
-  } else {
-    launch_csr<T>(L.P, V<T>::val(L.P), V<T>::x(C), (const T *)nullptr, x, 2, s);
+  } else if constexpr (sizeof(T) == 8) {
+    launch_ell(L.P, C.x64, nullptr, x, 2, s);
   }
   if (post > 0) smooth<T>(c, L, post, false, s);
 }
@@ -632,7 +752,7 @@ void fine_apply(sem_ctx *c, const double *u, double *w, const double *p, hipStre
       c->npartials = kReduceBlocks;
     }
   } else {
-    launch_csr<double>(L0.A, L0.A.val64, u, nullptr, w, 0, s);
+    launch_ell(L0.A, u, nullptr, w, 0, s);
     if (p) {
       launch_dots<double>(L0.n, 1, p, w, nullptr, nullptr, nullptr, nullptr, c->partials, kReduceBlocks, s);
       c->npartials = kReduceBlocks;
@@ -678,7 +798,7 @@ sem_status lanczos(sem_ctx *c, int j, double &out, hipStream_t s) {
       launch_ax_map(L, v, L.wl64, s);
       launch_sum_lists<double, double>(L, L.wl64, wv, nullptr, false, s);
     } else {
-      launch_csr<double>(L.A, L.A.val64, v, nullptr, wv, 0, s);
+      launch_ell(L.A, v, nullptr, wv, 0, s);
     }
     launch_mul(n, sq, wv, wv, s);
     launch_dots<double>(n, 1, q, wv, nullptr, nullptr, nullptr, nullptr, c->partials, kReduceBlocks, s);
@@ -1056,6 +1176,21 @@ sem_status init_device(sem_ctx *c, hipStream_t s) {
   return SEM_OK;
 }
 
+// First level from which on every sparse level fits one block (see ell_tail_kernel), -1 if none
+// of the smoothed levels does: at most kTailRows unknowns and kTailWidth entries per row each, a
+// dense last level of at most kTailDense unknowns (its inverse is read by one compute unit).
+int find_tail(const sem_ctx *c) {
+  const int last = (int)c->levels.size() - 1;
+  if (last < 1 || !c->coarse.dense || c->coarse.n > kTailDense || c->coarse.n != c->levels[last].n) return -1;
+  int from = -1;
+  for (int j = last - 1; j >= 0 && last - j + 1 <= kTailLevels; --j) {
+    const Level &L = c->levels[j];
+    if (L.type != LVL_FD || L.n > kTailRows || L.A.width > kTailWidth || !L.P.val) break;
+    from = j;
+  }
+  return from;
+}
+
 Csr transpose(const Csr &A);
 
 sem_status setup_box_impl(const sem_box_mesh *mesh, const sem_options *opt, hipStream_t s, sem_ctx *c) {
@@ -1257,7 +1392,7 @@ sem_status setup_box_impl(const sem_box_mesh *mesh, const sem_options *opt, hipS
     for (int q = 0; q <= nlat; ++q) {
       Level &L = c->levels[nl - 1 + q];
       const LatticeLevelHost &h = lat[q];
-      TRY(upload_csr(c, L.A, h.A, false, s));
+      TRY(upload_ell(c, L.A, h.A, s));
       std::vector<double> inv(h.A.nrows);
       for (int64_t r = 0; r < h.A.nrows; ++r)
         for (int64_t p = h.A.rowptr[r]; p < h.A.rowptr[r + 1]; ++p)
@@ -1266,9 +1401,9 @@ sem_status setup_box_impl(const sem_box_mesh *mesh, const sem_options *opt, hipS
       TRY(upload(c, &L.invdiag64, inv.data(), inv.size(), s));
       const bool last = q == nlat;
       if (!last) {
-        TRY(upload_csr(c, L.P, h.P, false, s));
+        TRY(upload_ell(c, L.P, h.P, s));
         Csr R = transpose(h.P);
-        TRY(upload_csr(c, L.R, R, false, s));
+        TRY(upload_ell(c, L.R, R, s));
       }
       TRY(dalloc(c, &L.b64, L.n));
       TRY(dalloc(c, &L.x64, L.n));
@@ -1323,6 +1458,7 @@ sem_status setup_box_impl(const sem_box_mesh *mesh, const sem_options *opt, hipS
       TRY(up32(&C.Xbot32, bt.Xbot));
     }
   }
+  if (lattice) c->tail_from = find_tail(c);
   TRY(alloc_krylov(c, c->levels[0].n));
   HIPCHK(c, hipStreamSynchronize(s));
   TRY(autotune_operator(c, s));
@@ -1537,21 +1673,22 @@ sem_status setup_fd_impl(int n, double Lx, double Ly, int factor, int coarsest_n
   for (int j = 0; j < nl; ++j) {
     Level &L = c->levels[j];
     const FdLevelHost &h = c->fd_host[j];
-    TRY(upload_csr(c, L.A, h.A, false, s));
+    TRY(upload_ell(c, L.A, h.A, s));
     std::vector<double> inv(h.m);
     for (int64_t r = 0; r < h.A.nrows; ++r)
       for (int64_t p = h.A.rowptr[r]; p < h.A.rowptr[r + 1]; ++p)
         if (h.A.col[p] == r) inv[r] = 1.0 / h.A.val[p];
     TRY(upload(c, &L.invdiag64, inv.data(), inv.size(), s));
     if (j + 1 < nl) {
-      TRY(upload_csr(c, L.P, h.P, false, s));
+      TRY(upload_ell(c, L.P, h.P, s));
       Csr R = transpose(h.P);
-      TRY(upload_csr(c, L.R, R, false, s));
+      TRY(upload_ell(c, L.R, R, s));
     }
     TRY(alloc_level_vectors(c, L, false, j == nl - 1));
     HIPCHK(c, hipStreamSynchronize(s));
   }
   TRY(upload(c, &c->coarse.Minv, Ac.data(), Ac.size(), s));
+  c->tail_from = find_tail(c);
   TRY(alloc_krylov(c, c->levels[0].n));
   HIPCHK(c, hipStreamSynchronize(s));
   TRY(estimate_lambdas(c, s));

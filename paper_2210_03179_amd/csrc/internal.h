@@ -122,12 +122,29 @@ double tridiag_max_eig(const std::vector<double> &a, const std::vector<double> &
 // its operator results and transfers are global vectors, like those of LVL_FD)
 enum LevelType { LVL_SEM = 0, LVL_FD = 1, LVL_GEN = 2 };
 
-struct DevCsr {
-  int64_t nrows = 0;
-  int64_t *rowptr = nullptr;
-  int32_t *col = nullptr;
-  double *val64 = nullptr;
-  float *val32 = nullptr;
+// Sparse matrix of a CSR level on the device, stored by entries (ELL): entry k of row r at
+// k * ld + r, shorter rows padded with zero values (and a column of the row).
+struct EllArgs {
+  int64_t nrows = 0, ld = 0;
+  int32_t width = 0;
+  const int32_t *col = nullptr;
+  const double *val = nullptr;
+};
+
+// Levels of at most kTailRows unknowns that one block runs from the first to the dense last one.
+constexpr int kTailRows = 1024, kTailLevels = 8, kTailWidth = 9, kTailDense = 256;
+struct TailLevel {
+  int n;
+  EllArgs A, P, R;  // P: from the next level, R: to it (unused on the last level)
+  const double *inv;
+  double rlmax;                // 1 / lambda_max
+  double theta[2], delta[2];   // centre and half width of the 1st kind's interval (pre, post)
+};
+struct TailArgs {
+  int nlev, mode, pre, post;  // mode 4: 4th kind, 1: 1st kind
+  TailLevel lev[kTailLevels];
+  const double *Minv;  // dense inverse of the last level
+  double beta_pre[32], beta_post[32];
 };
 
 struct Level {
@@ -150,7 +167,7 @@ struct Level {
   double *mass = nullptr;     // assembled mass (finest level)
   double *coords = nullptr;   // [n][3] (finest level)
   // FD
-  DevCsr A, P, R;             // A_j; P: level j+1 -> j (rows n); R = P^T (rows n_{j+1})
+  EllArgs A, P, R;            // A_j; P: level j+1 -> j (rows n); R = P^T (rows n_{j+1})
   // unstructured mesh: local-to-global map (E (N+1)^3, -1 Dirichlet), copy lists of every
   // unknown, 1 / (number of copies), element-local work arrays
   int32_t *map = nullptr;
@@ -257,6 +274,8 @@ struct sem_ctx {
   // continues below it on the vertex lattice, -1 otherwise. Levels from this index on are
   // CSR levels (LVL_FD kernels) and always run in FP64, also inside a mixed cycle.
   int lattice_from = -1;
+  // first of the CSR levels that run in one block (ell_tail_kernel), -1: none
+  int tail_from = -1;
   // Krylov work (FP64, finest level)
   double *kr = nullptr, *kr2 = nullptr, *kz = nullptr, *kp = nullptr, *kw = nullptr;
   double *scal = nullptr;      // device scalars

@@ -20,7 +20,12 @@ enum {
   CHEB_R_ONLY = 64,   // only form and store the residual (a non-diagonal smoother follows)
   CHEB_NO_X = 128,     // do not store x (the first step from a zero guess: x = c d is implied)
   CHEB_X_FROM_D = 256, // previous iterate is cprev * (previous direction), x is not read
-  CHEB_LAST = 512      // last step of a smoothing: r and d are not read again, store only x
+  CHEB_LAST = 512,     // last step of a smoothing: r and d are not read again, store only x
+  // sparse levels only: the product gathers x; the first two steps from a zero guess in one; the
+  // previous step has not added its cprev * d to x
+  ELL_FROM_X = 1024,
+  ELL_FIRST2 = 2048,
+  ELL_X_PLUS_D = 4096
 };
 // Schwarz smoother modes of the fused gather (Chebyshev recurrences of Algorithms 1 and 2
 // with z = S v in place of diag(A)^{-1} r)
@@ -98,8 +103,13 @@ int launch_prolong(const Level &F, const Level &C, const T *xc, const T *J, T *x
 bool prolong_rows_available(int nf, int nc);
 // summation of a single-precision element-local vector into an FP64 global one
 void launch_dss_wide(const Level &L, const float *wL, double *out, hipStream_t s);
-template <typename T>
-void launch_csr(const DevCsr &A, const T *val, const T *x, const T *b, T *y, int mode, hipStream_t s);
+// sparse levels (sparse.hip): y = A x, b - A x or y + A x (mode 0, 1, 2); one Chebyshev step with
+// its product; the small levels of a cycle in one block
+void launch_ell(const EllArgs &A, const double *x, const double *b, double *y, int mode, hipStream_t s);
+void launch_ell_cheb(const EllArgs &A, const double *b, double *r, const double *d, double *dn, double *x,
+                     const double *inv, double a, double bc, double c, double c0, double cprev, int flags, int mode,
+                     hipStream_t s);
+void launch_ell_tail(const TailArgs &T, const double *b, double *x, hipStream_t s);
 void launch_gemv(int64_t nrows, int64_t ncols, const double *M, const double *x, const double *b, double *y,
                  int sub, hipStream_t s);
 // Up to two independent products in one launch, one 256-thread block per output row:

@@ -855,20 +855,6 @@ schwarz_gather_kernel(Box b, int64_t n, const T *__restrict__ ye, int gmode, T *
 }
 
 // ------------------------------------------------------------------ sparse / dense
-// y = A x (mode 0), y = b - A x (mode 1), y += A x (mode 2); one thread per row.
-template <typename T>
-__global__ void csr_kernel(int64_t nrows, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
-                           const T *__restrict__ v, const T *__restrict__ x, const T *__restrict__ bvec,
-                           T *__restrict__ y, int mode) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nrows) return;
-  T s = 0;
-  for (int64_t p = rp[r]; p < rp[r + 1]; ++p) s += v[p] * x[ci[p]];
-  if (mode == 0) y[r] = s;
-  else if (mode == 1) y[r] = bvec[r] - s;
-  else y[r] += s;
-}
-
 // Dense row-major products of the coarse solve, one 256-thread block per row:
 //   y = M1 x1 - M2 x2 (M2 optional), then y = b - y when sub = 1.
 // Each thread issues its (up to kGemvUnroll) loads per matrix before summing, so a
@@ -1949,16 +1935,6 @@ bool prolong_rows_available(int nf, int nc) {
 void launch_dss_wide(const Level &L, const float *wL, double *out, hipStream_t s) {
   hipLaunchKernelGGL((dss_kernel<float, double>), dim3(nblk(L.n)), dim3(256), 0, s, mkbox(L), L.n, wL, out);
 }
-
-template <typename T>
-void launch_csr(const DevCsr &A, const T *val, const T *x, const T *b, T *y, int mode, hipStream_t s) {
-  hipLaunchKernelGGL((csr_kernel<T>), dim3(nblk(A.nrows)), dim3(256), 0, s, A.nrows, A.rowptr, A.col, val, x,
-                     b, y, mode);
-}
-template void launch_csr<double>(const DevCsr &, const double *, const double *, const double *, double *, int,
-                                 hipStream_t);
-template void launch_csr<float>(const DevCsr &, const float *, const float *, const float *, float *, int,
-                                hipStream_t);
 
 void launch_gemv(int64_t nrows, int64_t ncols, const double *M, const double *x, const double *b, double *y,
                  int sub, hipStream_t s) {
