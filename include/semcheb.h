@@ -99,8 +99,8 @@ enum { SEM_PCG = 0, SEM_FCG = 1, SEM_GMRES = 2, SEM_MG = 3 };
  * SEM contexts only. */
 enum { SEM_GEOM_STORED = 0, SEM_GEOM_TRILINEAR = 1 };
 /* Treatment of the order-1 level of a SEM hierarchy. SEM_COARSE_EXACT solves it exactly
- * (M_l^{-1} = A_l^{-1}, Sec. 2): one dense inverse up to 4096 unknowns, a two-ended block
- * elimination over z-planes above. SEM_COARSE_LATTICE follows the paper's own practice of
+ * (M_l^{-1} = A_l^{-1}, Sec. 2): one dense inverse up to 4096 unknowns, nested dissection
+ * above (with coarse_planes > 0 a two-ended block elimination over z-planes). SEM_COARSE_LATTICE follows the paper's own practice of
  * one multigrid V-cycle for the order-1 system (Sec. 4.1, one algebraic V-cycle in its
  * runs): the cycle continues below order 1 on the box's vertex lattice, halving the
  * element count per direction with trilinear interpolation and Galerkin operators P^T A P
@@ -129,7 +129,8 @@ typedef struct {
   double lambda_max[SEM_MAX_LEVELS];/* lambda_max(S_j A_j) per smoothed level */
   double lambda_scale;              /* factor applied to estimated values (0 -> 1) */
   int32_t device;                   /* HIP device ordinal; -1: host-only context */
-  int32_t coarse_planes;            /* planes per block of the coarse solve, 0 = auto */
+  int32_t coarse_planes;            /* planes per block of a coarse solve blocked by z-planes; 0: dense
+                                       inverse or nested dissection, by size */
   int32_t gmres_restart;            /* m of GMRES(m), 1..32; 0 = 30 */
   int32_t schwarz;                  /* smoother inside Chebyshev: SEM_JACOBI, SEM_ASM or SEM_RAS */
   int32_t geometry;                 /* SEM_GEOM_STORED or SEM_GEOM_TRILINEAR */

@@ -487,6 +487,10 @@ void coarse_solve_blocks(sem_ctx *c, const double *b, double *x, bool f32, hipSt
     launch_gemv_jobs(1, &jb, s);
     return;
   }
+  if (C.nd) {
+    for (const NdStep &st : C.nd_steps) launch_nd_step(C, st, b, x, f32, s);
+    return;
+  }
   // Block-tridiagonal substitution from both ends (blocks above `mid` top-down, below
   // it bottom-up): each launch advances both sweeps by one block.
   const int nb = (int)C.start.size() - 1, m = C.mid;
@@ -1262,8 +1266,18 @@ sem_status setup_box_impl(const sem_box_mesh *mesh, const sem_options *opt, hipS
     for (int k = 0; k < H.nz; k += gp) start.push_back((int64_t)k * plane);
     start.push_back(H.n);
   }
+  // Above 4096 unknowns, without a requested blocking: nested dissection. The z-plane chain it
+  // replaces reads three dense blocks per plane in as many dependent launches as there are planes
+  // (31^3 unknowns: 30 launches, 687 MB, 234 us inside a solve; nested dissection: 7 steps,
+  // 210 MB, 101 us; 23^3: 154 -> 51 us)
   BlockTri bt;
-  if (!block_tridiag_factor(Ac, start, bt, c->err)) return SEM_EINVAL;
+  NestedDissection nd;
+  c->coarse.nd = !lattice && opt->coarse_planes <= 0 && start.size() > 2 && ncoarse < (int64_t(1) << 30);
+  if (c->coarse.nd) {
+    if (!nested_dissection_factor(Ac, H.nx, H.ny, H.nz, nd, c->err)) return SEM_EINVAL;
+  } else if (!block_tridiag_factor(Ac, start, bt, c->err)) {
+    return SEM_EINVAL;
+  }
   if (ncoarse <= 4096) {
     c->coarse.host_dense.assign((size_t)ncoarse * ncoarse, 0.0);
     for (int64_t r = 0; r < ncoarse; ++r)
@@ -1435,6 +1449,13 @@ sem_status setup_box_impl(const sem_box_mesh *mesh, const sem_options *opt, hipS
     if (C.dense) {
       TRY(upload(c, &C.Minv, bt.Minv[0].data(), bt.Minv[0].size(), s));
       TRY(up32(&C.Minv32, bt.Minv[0]));
+    } else if (C.nd) {
+      C.nd_steps = nd.steps;
+      TRY(upload(c, &C.nd_groups, nd.groups.data(), nd.groups.size(), s));
+      TRY(upload(c, &C.nd_col, nd.col.data(), nd.col.size(), s));
+      // one copy of the values: the one the context's cycle reads
+      if (C.has32) TRY(up32(&C.nd_val32, nd.val));
+      else TRY(upload(c, &C.nd_val, nd.val.data(), nd.val.size(), s));
     } else {
       const int nb = (int)start.size() - 1;
       C.mid = bt.mid;

@@ -496,46 +496,95 @@ Csr assemble_q1(const BoxLevelHost &L) {
 }
 
 // ------------------------------------------------------------------ dense SPD inverse
+// Dot products of row a with four rows at once, sums in eight interleaved partial sums each (the
+// compiler keeps a single floating-point sum in order and cannot vectorise it).
+static inline void dot4(const double *a, const double *b0, const double *b1, const double *b2, const double *b3,
+                        int64_t n, double out[4]) {
+  double s[4][4] = {};
+  int64_t k = 0;
+  for (; k + 4 <= n; k += 4)
+    for (int u = 0; u < 4; ++u) {
+      s[0][u] += a[k + u] * b0[k + u];
+      s[1][u] += a[k + u] * b1[k + u];
+      s[2][u] += a[k + u] * b2[k + u];
+      s[3][u] += a[k + u] * b3[k + u];
+    }
+  for (int r = 0; r < 4; ++r) out[r] = (s[r][0] + s[r][1]) + (s[r][2] + s[r][3]);
+  for (; k < n; ++k) {
+    out[0] += a[k] * b0[k];
+    out[1] += a[k] * b1[k];
+    out[2] += a[k] * b2[k];
+    out[3] += a[k] * b3[k];
+  }
+}
+static inline double dot1(const double *a, const double *b, int64_t n) {
+  double o[4];
+  dot4(a, b, b, b, b, n, o);
+  return o[0];
+}
+// out[j] (op) dot(a, rows[j]) for j in [j0, j1), rows contiguous with leading dimension ld
+template <typename F>
+static inline void dot_rows(const double *a, const double *rows, int64_t ld, int64_t n, int64_t j0, int64_t j1, F f) {
+  int64_t j = j0;
+  for (; j + 4 <= j1; j += 4) {
+    double o[4];
+    const double *r = rows + j * ld;
+    dot4(a, r, r + ld, r + 2 * ld, r + 3 * ld, n, o);
+    for (int u = 0; u < 4; ++u) f(j + u, o[u]);
+  }
+  for (; j < j1; ++j) f(j, dot1(a, rows + j * ld, n));
+}
+
 bool spd_inverse(std::vector<double> &A, int64_t n) {
-  // Cholesky A = L L^T (L stored in the lower triangle of A), row-major.
-  for (int64_t j = 0; j < n; ++j) {
-    double s = A[j * n + j];
-    const double *Lj = &A[j * n];
-    for (int64_t k = 0; k < j; ++k) s -= Lj[k] * Lj[k];
-    if (!(s > 0.0)) return false;
-    const double djj = std::sqrt(s);
-    A[j * n + j] = djj;
-#pragma omp parallel for schedule(static) if (n - j > 256)
-    for (int64_t i = j + 1; i < n; ++i) {
-      const double *Li = &A[i * n];
-      double t = A[i * n + j];
-      for (int64_t k = 0; k < j; ++k) t -= Li[k] * Lj[k];
-      A[i * n + j] = t / djj;
+  // Blocked Cholesky A = L L^T, L in the lower triangle of A (row-major): columns in panels, the
+  // rows below a panel and the trailing update in parallel over rows.
+  constexpr int64_t kPanel = 64;
+  for (int64_t p0 = 0; p0 < n; p0 += kPanel) {
+    const int64_t p1 = std::min(p0 + kPanel, n);
+    for (int64_t j = p0; j < p1; ++j) {  // diagonal block
+      double *Lj = &A[j * n];
+      for (int64_t i = p0; i < j; ++i) Lj[i] = (Lj[i] - dot1(Lj + p0, &A[i * n + p0], i - p0)) / A[i * n + i];
+      const double s = Lj[j] - dot1(Lj + p0, Lj + p0, j - p0);
+      if (!(s > 0.0)) return false;
+      Lj[j] = std::sqrt(s);
+    }
+#pragma omp parallel if (n - p1 > 128)
+    {
+#pragma omp for schedule(static)
+      for (int64_t i = p1; i < n; ++i) {
+        double *Li = &A[i * n];
+        for (int64_t j = p0; j < p1; ++j) Li[j] = (Li[j] - dot1(Li + p0, &A[j * n + p0], j - p0)) / A[j * n + j];
+      }
+#pragma omp for schedule(dynamic, 16)
+      for (int64_t i = p1; i < n; ++i) {
+        double *Li = &A[i * n];
+        dot_rows(Li + p0, A.data() + p0, n, p1 - p0, p1, i + 1, [&](int64_t j, double v) { Li[j] -= v; });
+      }
     }
   }
-  // Rows of W = L^{-T}: W[j][i] = (L^{-1})[i][j], solved column by column of L^{-1}.
+  // Rows of W = L^{-T}: W[j][i] = (L^{-1})[i][j], the columns of L^{-1} one by one.
   std::vector<double> W((size_t)n * n, 0.0);
-#pragma omp parallel for schedule(dynamic, 8)
+#pragma omp parallel for schedule(dynamic, 8) if (n > 128)
   for (int64_t j = 0; j < n; ++j) {
     double *x = &W[(size_t)j * n];
     x[j] = 1.0 / A[j * n + j];
     for (int64_t i = j + 1; i < n; ++i) {
       const double *Li = &A[i * n];
-      double s = 0.0;
-      for (int64_t k = j; k < i; ++k) s -= Li[k] * x[k];
-      x[i] = s / Li[i];
+      x[i] = -dot1(Li + j, x + j, i - j) / Li[i];
     }
   }
-  // A^{-1} = L^{-T} L^{-1}: entry (i,j) = sum_{k >= max(i,j)} W[i][k] W[j][k]
-#pragma omp parallel for schedule(dynamic, 8)
+  // A^{-1} = L^{-T} L^{-1}: entry (i,j), j >= i, = sum_{k >= j} W[i][k] W[j][k]
+#pragma omp parallel for schedule(dynamic, 8) if (n > 128)
   for (int64_t i = 0; i < n; ++i) {
     const double *Wi = &W[(size_t)i * n];
-    for (int64_t j = i; j < n; ++j) {
-      const double *Wj = &W[(size_t)j * n];
-      double s = 0.0;
-      for (int64_t k = j; k < n; ++k) s += Wi[k] * Wj[k];
-      A[i * n + j] = s;
+    int64_t j = i;
+    for (; j + 4 <= n; j += 4) {  // W[j + u][k] = 0 for k < j + u
+      double o[4];
+      const double *w = &W[(size_t)j * n];
+      dot4(Wi + j, w + j, w + n + j, w + 2 * n + j, w + 3 * n + j, n - j, o);
+      for (int u = 0; u < 4; ++u) A[i * n + j + u] = o[u];
     }
+    for (; j < n; ++j) A[i * n + j] = dot1(Wi + j, &W[(size_t)j * n + j], n - j);
   }
   for (int64_t i = 0; i < n; ++i)
     for (int64_t j = 0; j < i; ++j) A[i * n + j] = A[j * n + i];
@@ -962,6 +1011,266 @@ void build_fd_hierarchy(int n, double Lx, double Ly, int factor, int coarsest_n,
     c.A = csr_matmul(PT, csr_matmul(out.back().A, out.back().P));
     out.push_back(c);
   }
+}
+
+// ------------------------------------------------------------------ nested dissection
+namespace {
+struct NdNode {
+  int lo[3], hi[3];         // box of lattice points [lo, hi) of the subtree
+  int cut[3];               // separating plane per axis, -1: not cut along it
+  int depth, height;        // from the root, from the lowest leaf
+  std::vector<int> child;   // empty: a leaf box
+};
+
+struct NdTree {
+  int dom[3];
+  std::vector<NdNode> nodes;
+  int64_t border(const NdNode &s) const {  // lattice points around the box
+    int64_t in = 1, out = 1;
+    for (int d = 0; d < 3; ++d) {
+      in *= s.hi[d] - s.lo[d];
+      out *= std::min(s.hi[d] + 1, dom[d]) - std::max(s.lo[d] - 1, 0);
+    }
+    return out - in;
+  }
+  int64_t own(const NdNode &s) const {
+    int64_t n = 1, inner = 1;
+    for (int d = 0; d < 3; ++d) {
+      n *= s.hi[d] - s.lo[d];
+      inner *= s.hi[d] - s.lo[d] - (s.cut[d] >= 0 ? 1 : 0);
+    }
+    return s.child.empty() ? n : n - inner;
+  }
+  // cuts every axis of at least three points, `levels` times; boxes of at most 64 points are leaves
+  int split(const int lo[3], const int hi[3], int depth, int levels) {
+    NdNode s{};
+    int64_t n = 1;
+    bool any = false;
+    for (int d = 0; d < 3; ++d) {
+      s.lo[d] = lo[d];
+      s.hi[d] = hi[d];
+      n *= hi[d] - lo[d];
+    }
+    for (int d = 0; d < 3; ++d) {
+      s.cut[d] = depth < levels && n > 64 && hi[d] - lo[d] >= 3 ? lo[d] + (hi[d] - lo[d]) / 2 : -1;
+      any = any || s.cut[d] >= 0;
+    }
+    s.depth = depth;
+    if (any)
+      for (int q = 0; q < 8; ++q) {
+        int l[3], h[3];
+        bool skip = false;
+        for (int d = 0; d < 3; ++d) {
+          const bool upper = (q >> d) & 1;
+          if (s.cut[d] < 0) {
+            skip = skip || upper;
+            l[d] = lo[d];
+            h[d] = hi[d];
+          } else {
+            l[d] = upper ? s.cut[d] + 1 : lo[d];
+            h[d] = upper ? hi[d] : s.cut[d];
+          }
+        }
+        if (skip) continue;
+        s.child.push_back(split(l, h, depth + 1, levels));
+        s.height = std::max(s.height, nodes[s.child.back()].height + 1);
+      }
+    nodes.push_back(s);
+    return (int)nodes.size() - 1;
+  }
+};
+}  // namespace
+
+bool nested_dissection_factor(const Csr &A, int nx, int ny, int nz, NestedDissection &out, std::string &err) {
+  // Levels of cuts: a step costs about 8 us (launch and dependent memory latencies), its factor
+  // entries 8 bytes at about 5.5 TB/s; the smallest total decides (31^3 unknowns: three levels,
+  // 7 steps, 210 MB; cutting one axis per level would take 13 to 17 steps).
+  NdTree T;
+  double best = 0.0;
+  for (int levels = 1; levels <= 5; ++levels) {
+    NdTree C;
+    C.dom[0] = nx;
+    C.dom[1] = ny;
+    C.dom[2] = nz;
+    const int zero[3] = {0, 0, 0};
+    C.split(zero, C.dom, 0, levels);
+    double entries = 0.0;
+    int H = 0, D = 0;
+    for (const NdNode &s : C.nodes) {
+      const double n = (double)C.own(s);
+      entries += n * (n + 2.0 * (double)C.border(s));
+      H = std::max(H, s.height);
+      D = std::max(D, s.depth);
+    }
+    const double cost = 8.0 * (H + 1 + D) + entries * 8.0 / 5.5e6;
+    if (T.nodes.empty() || cost < best) {
+      best = cost;
+      T = C;
+    }
+  }
+  const int nn = (int)T.nodes.size();
+  const int64_t n = A.nrows;
+  // own and border unknowns of every node, inverse Schur complement, L = A_{border,own} D^{-1}
+  // and the update of the border's matrix U
+  std::vector<std::vector<int32_t>> own(nn), bord(nn);
+  std::vector<std::vector<double>> Dinv(nn), L(nn), U(nn);
+  int H = 0, D = 0;
+  for (const NdNode &s : T.nodes) {
+    H = std::max(H, s.height);
+    D = std::max(D, s.depth);
+  }
+  bool ok = true;
+  auto eliminate = [&](int q) {
+    const NdNode &s = T.nodes[q];
+    auto &o = own[q];
+    auto &br = bord[q];
+    for (int k = std::max(s.lo[2] - 1, 0); k < std::min(s.hi[2] + 1, nz); ++k)
+      for (int j = std::max(s.lo[1] - 1, 0); j < std::min(s.hi[1] + 1, ny); ++j)
+        for (int i = std::max(s.lo[0] - 1, 0); i < std::min(s.hi[0] + 1, nx); ++i) {
+          const int p[3] = {i, j, k};
+          bool in = true, cut = s.child.empty();
+          for (int d = 0; d < 3; ++d) {
+            in = in && p[d] >= s.lo[d] && p[d] < s.hi[d];
+            cut = cut || p[d] == s.cut[d];
+          }
+          const int32_t g = (int32_t)(i + (int64_t)nx * (j + (int64_t)ny * k));
+          if (!in) br.push_back(g);
+          else if (cut) o.push_back(g);
+        }
+    const int64_t ns = (int64_t)o.size(), nb = (int64_t)br.size();
+    std::unordered_map<int32_t, int32_t> at;
+    at.reserve((size_t)(2 * (ns + nb)));
+    for (int64_t r = 0; r < ns; ++r) at[o[r]] = (int32_t)r;
+    for (int64_t r = 0; r < nb; ++r) at[br[r]] = (int32_t)(ns + r);
+    // front: own and border rows against own columns (F), border against border (U)
+    std::vector<double> F((size_t)(ns + nb) * ns, 0.0);
+    U[q].assign((size_t)nb * nb, 0.0);
+    for (int64_t r = 0; r < ns; ++r)
+      for (int64_t p = A.rowptr[o[r]]; p < A.rowptr[o[r] + 1]; ++p) {
+        const auto it = at.find(A.col[p]);
+        if (it != at.end()) F[(size_t)it->second * ns + r] += A.val[p];  // A is symmetric
+      }
+    for (int c : s.child) {  // the children's updates
+      const auto &cb = bord[c];
+      const int64_t nc = (int64_t)cb.size();
+      std::vector<int32_t> to((size_t)nc);
+      for (int64_t r = 0; r < nc; ++r) to[r] = at.at(cb[r]);
+      for (int64_t r = 0; r < nc; ++r)
+        for (int64_t t = 0; t < nc; ++t) {
+          const double v = U[c][(size_t)r * nc + t];
+          if (to[t] < ns) F[(size_t)to[r] * ns + to[t]] += v;
+          else if (to[r] >= ns) U[q][(size_t)(to[r] - ns) * nb + (to[t] - ns)] += v;
+        }
+      std::vector<double>().swap(U[c]);
+    }
+    Dinv[q].assign(F.begin(), F.begin() + (size_t)ns * ns);
+    if (!spd_inverse(Dinv[q], ns)) {
+#pragma omp atomic write
+      ok = false;
+      return;
+    }
+    L[q].resize((size_t)nb * ns);
+    const double *B = F.data() + (size_t)ns * ns;  // border x own
+#pragma omp parallel for schedule(dynamic, 8) if (nb * ns > 65536)
+    for (int64_t r = 0; r < nb; ++r)  // D^{-1} is symmetric: its rows are its columns
+      dot_rows(B + r * ns, Dinv[q].data(), ns, ns, 0, ns, [&](int64_t c, double v) { L[q][(size_t)r * ns + c] = v; });
+#pragma omp parallel for schedule(dynamic, 8) if (nb * ns > 65536)
+    for (int64_t r = 0; r < nb; ++r)
+      dot_rows(&L[q][(size_t)r * ns], B, ns, ns, 0, nb, [&](int64_t t, double v) { U[q][(size_t)r * nb + t] -= v; });
+  };
+  std::vector<std::vector<int>> by_height(H + 1), by_depth(D + 1);
+  for (int q = 0; q < nn; ++q) {
+    by_height[T.nodes[q].height].push_back(q);
+    by_depth[T.nodes[q].depth].push_back(q);
+  }
+  for (const auto &qs : by_height) {
+    // many small fronts side by side, the few large ones with the threads inside
+#pragma omp parallel for schedule(dynamic, 1) if (qs.size() >= 16)
+    for (size_t i = 0; i < qs.size(); ++i) eliminate(qs[i]);
+    if (!ok) {
+      err = "coarse Schur complement is not positive definite (nested dissection)";
+      return false;
+    }
+  }
+  // rows going up: for every unknown, the border rows of the nodes below that contain it
+  std::vector<std::vector<std::pair<int, int32_t>>> below((size_t)n);
+  for (int q = 0; q < nn; ++q)
+    for (size_t r = 0; r < bord[q].size(); ++r) below[bord[q][r]].push_back({q, (int32_t)r});
+  out = NestedDissection{};
+  int64_t nval = 0;
+  struct RowRef {
+    int node;
+    int32_t local;
+    bool up;
+    int64_t val;
+  };
+  std::vector<RowRef> rows;
+  auto append = [&](int q, const std::vector<int32_t> &ids, bool x) {
+    const uint32_t tag = (x ? kNdX : T.nodes[q].height == 0 ? kNdB : kNdY) << 30;
+    for (int32_t g : ids) out.col.push_back(tag | (uint32_t)g);
+  };
+  auto add_rows = [&](int q, const std::vector<int32_t> &locals, int64_t list, int64_t len, bool up) {
+    for (size_t i = 0; i < locals.size(); i += kNdRows) {
+      NdGroup g{};
+      g.val = nval;
+      g.col = list;
+      g.len = (int32_t)len;
+      g.nrows = (int32_t)std::min<size_t>(kNdRows, locals.size() - i);
+      for (int r = 0; r < g.nrows; ++r) {
+        g.row[r] = own[q][locals[i + r]];
+        rows.push_back({q, locals[i + r], up, nval});
+        nval += len;
+      }
+      out.groups.push_back(g);
+    }
+  };
+  auto add_step = [&](const std::vector<int> &qs, bool up) {
+    const int64_t g0 = (int64_t)out.groups.size();
+    for (int q : qs) {
+      if (!up) {
+        const int64_t list = (int64_t)out.col.size();
+        append(q, own[q], false);
+        append(q, bord[q], true);
+        std::vector<int32_t> all(own[q].size());
+        for (size_t r = 0; r < all.size(); ++r) all[r] = (int32_t)r;
+        add_rows(q, all, list, (int64_t)(own[q].size() + bord[q].size()), false);
+        continue;
+      }
+      std::map<std::vector<int>, std::vector<int32_t>> same;  // nodes read -> rows
+      for (size_t r = 0; r < own[q].size(); ++r) {
+        std::vector<int> key;
+        for (const auto &b : below[own[q][r]]) key.push_back(b.first);
+        same[key].push_back((int32_t)r);
+      }
+      for (const auto &kv : same) {
+        const int64_t list = (int64_t)out.col.size();
+        for (int d : kv.first) append(d, own[d], false);
+        add_rows(q, kv.second, list, (int64_t)out.col.size() - list, true);
+      }
+    }
+    out.steps.push_back(NdStep{g0, (int64_t)out.groups.size() - g0, up});
+  };
+  for (int h = 1; h <= H; ++h) add_step(by_height[h], true);
+  for (int d = 0; d <= D; ++d) add_step(by_depth[d], false);
+  out.val.resize((size_t)nval);
+#pragma omp parallel for schedule(dynamic, 64)
+  for (size_t i = 0; i < rows.size(); ++i) {
+    double *v = &out.val[(size_t)rows[i].val];
+    const int q = rows[i].node;
+    const int32_t r = rows[i].local;
+    const size_t ns = own[q].size();
+    if (rows[i].up) {
+      for (const auto &b : below[own[q][r]]) {
+        const size_t nd = own[b.first].size();
+        const double *Lr = &L[b.first][(size_t)b.second * nd];
+        for (size_t c = 0; c < nd; ++c) *v++ = -Lr[c];
+      }
+    } else {
+      for (size_t c = 0; c < ns; ++c) *v++ = Dinv[q][(size_t)r * ns + c];
+      for (size_t t = 0; t < bord[q].size(); ++t) *v++ = -L[q][t * ns + r];
+    }
+  }
+  return true;
 }
 
 // ------------------------------------------------------------------ tridiagonal eigenvalue

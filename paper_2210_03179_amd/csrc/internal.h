@@ -89,6 +89,35 @@ bool block_tridiag_factor(const Csr &A, const std::vector<int64_t> &start, Block
                           std::string &err);
 bool spd_inverse(std::vector<double> &A, int64_t n);  // in place, false if not SPD
 
+// Exact solve of the order-1 box operator by nested dissection of its vertex lattice: the middle
+// planes of every axis separate a box into up to eight, recursively, down to leaf boxes. The
+// solve is a list of steps, each a set of independent rows
+//   out[row] = base + sum_k val[k] * src(col[k])
+// with base = b[row], out = y going up the tree (y_s = b_s - sum over the subtree of
+// A_{s,d} D_d^{-1} y_d) and base = 0, out = x going down (x_s = D_s^{-1} y_s - sum over the
+// border of D_s^{-1} A_{s,a} x_a), D the Schur complements. A column's top two bits name its
+// vector: kNdY, kNdB (the right-hand side, which is y on the leaves) or kNdX. Up to kNdRows
+// consecutive rows that read the same columns form a group (the rows of a node going down, the
+// rows of a separator next to the same nodes going up).
+constexpr uint32_t kNdY = 0u, kNdB = 1u, kNdX = 2u;
+constexpr int kNdRows = 4;
+struct NdGroup {
+  int64_t val, col;      // start of the first row's values (rows follow each other), of the columns
+  int32_t len, nrows;
+  int32_t row[kNdRows];  // lattice indices
+};
+struct NdStep {
+  int64_t group0, ngroups;
+  bool up;
+};
+struct NestedDissection {
+  std::vector<NdGroup> groups;
+  std::vector<uint32_t> col;  // source << 30 | lattice index
+  std::vector<double> val;
+  std::vector<NdStep> steps;
+};
+bool nested_dissection_factor(const Csr &A, int nx, int ny, int nz, NestedDissection &out, std::string &err);
+
 // FD2D problem (Sec. 3) host data
 struct FdLevelHost {
   int n = 0;  // intervals
@@ -216,6 +245,13 @@ struct CoarseSolver {
   float *Minv32 = nullptr;
   std::vector<float *> Mb32, Lb32, Wb32;
   float *Xtop32 = nullptr, *Xbot32 = nullptr;
+  // nested dissection (more than 4096 unknowns, no blocking requested)
+  bool nd = false;
+  std::vector<NdStep> nd_steps;
+  NdGroup *nd_groups = nullptr;
+  uint32_t *nd_col = nullptr;
+  double *nd_val = nullptr;
+  float *nd_val32 = nullptr;
   double *b = nullptr, *y = nullptr, *x = nullptr, *t = nullptr;
   std::vector<double> host_dense;  // small problems: assembled matrix for inspection
 };

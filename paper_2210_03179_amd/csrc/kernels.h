@@ -109,6 +109,8 @@ void launch_ell(const EllArgs &A, const double *x, const double *b, double *y, i
 void launch_ell_cheb(const EllArgs &A, const double *b, double *r, const double *d, double *dn, double *x,
                      const double *inv, double a, double bc, double c, double c0, double cprev, int flags, int mode,
                      hipStream_t s);
+// one step of the nested-dissection coarse solve (b, x: coarse vectors; f32: the factors' copies)
+void launch_nd_step(const CoarseSolver &C, const NdStep &st, const double *b, double *x, bool f32, hipStream_t s);
 void launch_ell_tail(const TailArgs &T, const double *b, double *x, hipStream_t s);
 void launch_gemv(int64_t nrows, int64_t ncols, const double *M, const double *x, const double *b, double *y,
                  int sub, hipStream_t s);

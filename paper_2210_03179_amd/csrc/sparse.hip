@@ -276,6 +276,81 @@ __global__ void __launch_bounds__(kTailRows) ell_tail_kernel(TailArgs T, const d
   if (t < T.lev[0].n) x[t] = vec[T.lev[0].n + t];
 }
 
+// One step of the nested-dissection solve: out[row] = base + sum val * src(col), one group of rows
+// that share their columns per block (WPG = 4 wavefronts splitting the columns) or per wavefront
+// (WPG = 1). The gathered vector entries serve all rows of the group, and a wave keeps four times
+// the factor bytes in flight: a step is a chain of three memory latencies (group, factors and
+// columns, vector entries), not a stream. The factors are FP64 or their single-precision copies.
+// one batch of kU columns per lane from column q0 on (64 WPG apart), every load requested before
+// the first use; past the end: the last entry, not summed; a missing row repeats the first, not stored
+template <int kU, int WPG, typename V>
+__device__ __forceinline__ void nd_batch(const NdGroup &g, int q0, const V *__restrict__ v0,
+                                         const uint32_t *__restrict__ c0, const double *b, const double *y,
+                                         const double *x, double (&s)[kNdRows]) {
+  const int len = g.len;
+  uint32_t c[kU];
+  V v[kNdRows][kU];
+  double xv[kU];
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
+    const int q = q0 + 64 * WPG * u, qc = q < len ? q : len - 1;
+    c[u] = c0[qc];
+#pragma unroll
+    for (int r = 0; r < kNdRows; ++r) v[r][u] = v0[(r < g.nrows ? r : 0) * len + qc];
+  }
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
+    const uint32_t w = c[u] >> 30;
+    xv[u] = (w == kNdY ? y : w == kNdB ? b : x)[c[u] & 0x3fffffffu];
+    if (q0 + 64 * WPG * u >= len) xv[u] = 0.0;
+  }
+#pragma unroll
+  for (int r = 0; r < kNdRows; ++r)
+#pragma unroll
+    for (int u = 0; u < kU; ++u) s[r] += (double)v[r][u] * xv[u];
+}
+
+template <int WPG, typename V>
+__global__ void __launch_bounds__(256)
+nd_step_kernel(int64_t group0, int64_t ngroups, const NdGroup *__restrict__ groups, const uint32_t *__restrict__ col,
+               const V *__restrict__ val, const double *b, const double *y, const double *x, double *out, int up) {
+  __shared__ double part[4][kNdRows];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t i = WPG > 1 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wave);
+  if (WPG == 1 && i >= ngroups) return;
+  const NdGroup &g = groups[group0 + i];
+  const int len = g.len;
+  const V *v0 = val + g.val;
+  const uint32_t *c0 = col + g.col;
+  double s[kNdRows] = {0.0, 0.0, 0.0, 0.0};
+  for (int q0 = WPG > 1 ? wave * 64 : 0; q0 < len; q0 += 64 * 8 * WPG) {
+    const int left = (len - q0 + 64 * WPG - 1) / (64 * WPG);  // wave-uniform
+    if (left > 4) nd_batch<8, WPG, V>(g, q0 + lane, v0, c0, b, y, x, s);
+    else if (left > 2) nd_batch<4, WPG, V>(g, q0 + lane, v0, c0, b, y, x, s);
+    else nd_batch<2, WPG, V>(g, q0 + lane, v0, c0, b, y, x, s);
+  }
+#pragma unroll
+  for (int r = 0; r < kNdRows; ++r)
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s[r] += __shfl_down(s[r], off, 64);
+  if constexpr (WPG > 1) {
+    if (lane == 0)
+#pragma unroll
+      for (int r = 0; r < kNdRows; ++r) part[wave][r] = s[r];
+    __syncthreads();
+    const int r = threadIdx.x;
+    if (r >= g.nrows) return;
+    double t = part[0][r];
+#pragma unroll
+    for (int w = 1; w < WPG; ++w) t += part[w][r];
+    out[g.row[r]] = up ? b[g.row[r]] + t : t;
+  } else if (lane == 0) {
+#pragma unroll
+    for (int r = 0; r < kNdRows; ++r)
+      if (r < g.nrows) out[g.row[r]] = up ? b[g.row[r]] + s[r] : s[r];
+  }
+}
+
 // blocks of 64 rows while the level is too small to fill the chip with blocks of 256
 inline int ell_block(int64_t n) { return n < 256 * 256 ? 64 : 256; }
 inline unsigned blocks(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
@@ -319,6 +394,26 @@ void launch_ell_cheb(const EllArgs &A, const double *b, double *r, const double 
       hipLaunchKernelGGL((ell_cheb_kernel<0>), grid, block, 0, s, A, b, r, d, dn, x, inv, a, bc, c, c0, cprev, flags,
                          mode);
   }
+}
+
+void launch_nd_step(const CoarseSolver &C, const NdStep &st, const double *b, double *x, bool f32, hipStream_t s) {
+  double *out = st.up ? C.y : x;
+  if (st.ngroups == 0) return;
+  // four wavefronts per group while the groups alone would leave the chip short of wavefronts
+  // (eight were no faster: 31^3 unknowns, 698 groups of 2791 columns, 22.1 against 22.2 us)
+  const bool wide = st.ngroups < 4096;
+  const dim3 grid((unsigned)(wide ? st.ngroups : (st.ngroups + 3) / 4)), block(256);
+#define SEMCHEB_ND(w, V, vals)                                                                                  \
+  hipLaunchKernelGGL((nd_step_kernel<w, V>), grid, block, 0, s, st.group0, st.ngroups, C.nd_groups, C.nd_col,   \
+                     vals, b, C.y, x, out, st.up ? 1 : 0)
+  if (f32) {
+    if (wide) SEMCHEB_ND(4, float, C.nd_val32);
+    else SEMCHEB_ND(1, float, C.nd_val32);
+  } else {
+    if (wide) SEMCHEB_ND(4, double, C.nd_val);
+    else SEMCHEB_ND(1, double, C.nd_val);
+  }
+#undef SEMCHEB_ND
 }
 
 void launch_ell_tail(const TailArgs &T, const double *b, double *x, hipStream_t s) {
