@@ -752,14 +752,14 @@ void fine_apply(sem_ctx *c, const double *u, double *w, const double *p, hipStre
     launch_ax_map(L0, u, L0.wl64, s);
     launch_sum_lists<double, double>(L0, L0.wl64, w, nullptr, false, s);
     if (p) {
-      launch_dots<double>(L0.n, 1, p, w, nullptr, nullptr, nullptr, nullptr, c->partials, kReduceBlocks, s);
-      c->npartials = kReduceBlocks;
+      launch_dots<double>(L0.n, 1, p, w, nullptr, nullptr, nullptr, nullptr, c->partials, reduce_blocks(L0.n), s);
+      c->npartials = reduce_blocks(L0.n);
     }
   } else {
     launch_ell(L0.A, u, nullptr, w, 0, s);
     if (p) {
-      launch_dots<double>(L0.n, 1, p, w, nullptr, nullptr, nullptr, nullptr, c->partials, kReduceBlocks, s);
-      c->npartials = kReduceBlocks;
+      launch_dots<double>(L0.n, 1, p, w, nullptr, nullptr, nullptr, nullptr, c->partials, reduce_blocks(L0.n), s);
+      c->npartials = reduce_blocks(L0.n);
     }
   }
 }
@@ -805,14 +805,14 @@ sem_status lanczos(sem_ctx *c, int j, double &out, hipStream_t s) {
       launch_ell(L.A, v, nullptr, wv, 0, s);
     }
     launch_mul(n, sq, wv, wv, s);
-    launch_dots<double>(n, 1, q, wv, nullptr, nullptr, nullptr, nullptr, c->partials, kReduceBlocks, s);
-    launch_finalize(kReduceBlocks, 1, c->partials, c->scal, S_TMP, FIN_NONE, s);
+    launch_dots<double>(n, 1, q, wv, nullptr, nullptr, nullptr, nullptr, c->partials, reduce_blocks(n), s);
+    launch_finalize(reduce_blocks(n), 1, c->partials, c->scal, S_TMP, FIN_NONE, s);
     TRY(read_scalars(c, s));
     const double a = c->pinned[S_TMP];
     launch_axpby(n, 1.0, wv, -a, q, wv, s);
     if (it > 0) launch_axpby(n, 1.0, wv, -beta_prev, qp, wv, s);
-    launch_dots<double>(n, 1, wv, wv, nullptr, nullptr, nullptr, nullptr, c->partials, kReduceBlocks, s);
-    launch_finalize(kReduceBlocks, 1, c->partials, c->scal, S_TMP, FIN_NONE, s);
+    launch_dots<double>(n, 1, wv, wv, nullptr, nullptr, nullptr, nullptr, c->partials, reduce_blocks(n), s);
+    launch_finalize(reduce_blocks(n), 1, c->partials, c->scal, S_TMP, FIN_NONE, s);
     TRY(read_scalars(c, s));
     const double bn = std::sqrt(c->pinned[S_TMP]);
     al.push_back(a);
@@ -1067,7 +1067,7 @@ sem_status arnoldi_schwarz(sem_ctx *c, int j, double &out, hipStream_t s) {
   Level &L = c->levels[j];
   const int64_t n = L.n, ld = (n + 31) / 32 * 32;
   const int m = (int)std::min<int64_t>(30, n - 1);
-  const int nb = kReduceBlocks;
+  const int nb = reduce_blocks(n);
   double *Vb = nullptr, *dh = nullptr, *hh = nullptr;
   HIPCHK(c, hipMalloc((void **)&Vb, (size_t)(m + 1) * ld * sizeof(double)));
   HIPCHK(c, hipMalloc((void **)&dh, 2 * (kMaxRestart + 1) * sizeof(double)));
@@ -1118,7 +1118,7 @@ sem_status arnoldi_schwarz(sem_ctx *c, int j, double &out, hipStream_t s) {
       mm = k + 1;
       break;
     }
-    launch_scale_inv_sqrt(n, w, dnrm, Vb + (int64_t)(k + 1) * ld, s);
+    launch_scale_inv_sqrt(n, w, dnrm, Vb + (int64_t)(k + 1) * ld, nullptr, s);
   }
   if (st == SEM_OK) {
     std::vector<double> Hm((size_t)mm * mm);
@@ -1911,6 +1911,15 @@ sem_status sem_vcycle(sem_ctx *c, const double *r, double *z, void *stream) {
   return SEM_OK;
 }
 
+namespace {
+struct EventGuard {
+  hipEvent_t e = nullptr;
+  ~EventGuard() {
+    if (e) (void)hipEventDestroy(e);
+  }
+};
+}  // namespace
+
 // Restarted flexible GMRES(m), classical Gram-Schmidt (Sec. 6.1): per iteration one V-cycle,
 // one operator apply, the projections of w on the basis in one reduction (multi-dot), and
 // w -= V h with its norm in the second; the Hessenberg matrix, its Givens rotations and
@@ -1926,11 +1935,16 @@ sem_status gmres_solve(sem_ctx *c, const double *b, double *u, double *r, double
   }
   const int64_t n = c->levels[0].n, ld = c->gld;
   const int m = c->opt.gmres_restart > 0 ? c->opt.gmres_restart : 30;
-  const int nb = kReduceBlocks;
+  const int nb = reduce_blocks(n);
   double *Vb = c->gV, *Zb = c->gZ, *w = c->kw, *dh = c->gH, *hh = c->gpinned;
   double *dnrm = dh + kMaxRestart, *dy = dh + kMaxRestart + 1;
   std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m);
   auto Hc = [&](int i, int j) -> double & { return H[(size_t)j * (m + 1) + i]; };
+  // a mixed cycle starts from the single-precision copy that the scaling of v_j leaves
+  float *r32 = c->opt.precision == SEM_MIXED && c->kind == LVL_SEM ? c->levels[0].b32 : nullptr;
+  EventGuard ev;
+  HIPCHK(c, hipEventCreateWithFlags(&ev.e, hipEventDisableTiming));
+  double res_prev = bnorm, rate = 1.0;
   int it = 0;
   bool first = true;
   for (;;) {
@@ -1950,28 +1964,42 @@ sem_status gmres_solve(sem_ctx *c, const double *b, double *u, double *r, double
       HIPCHK(c, hipMemcpyAsync(dnrm, hh + kMaxRestart, sizeof(double), hipMemcpyHostToDevice, s));
     }
     first = false;
-    launch_scale_inv_sqrt(n, r, dnrm, Vb, s);  // v_0 = r / beta
+    launch_scale_inv_sqrt(n, r, dnrm, Vb, r32, s);  // v_0 = r / beta
     std::fill(g.begin(), g.end(), 0.0);
     g[0] = beta;
     int k = 0;
     bool done = false;
+    bool queued = false;  // z_j of this step is in flight already
+    std::vector<int64_t> counts;
     for (int j = 0; j < m; ++j) {
       double *vj = Vb + (int64_t)j * ld, *zj = Zb + (int64_t)j * ld;
-      TRY(vcycle_replay(c, vj, zj, s, false));  // z_j = M v_j
+      if (!queued) TRY(vcycle_replay(c, vj, zj, s, r32 != nullptr));  // z_j = M v_j
       fine_apply(c, zj, w, nullptr, s);           // w = A z_j
       launch_multi_dot(n, j + 1, Vb, ld, w, c->partials, nb, s);
       launch_finalize_many(nb, j + 1, c->partials, dh, s);
       launch_multi_axpy(n, j + 1, Vb, ld, dh, -1.0, w, c->partials, nb, s);
       launch_finalize_many(nb, 1, c->partials, dnrm, s);
       HIPCHK(c, hipMemcpyAsync(hh, dh, (kMaxRestart + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
-      HIPCHK(c, hipStreamSynchronize(s));
+      HIPCHK(c, hipEventRecord(ev.e, s));
+      // v_{j+1} needs no host value: it and the next cycle are queued before the host waits for the
+      // Hessenberg column, unless the last reduction rate predicts convergence within a factor
+      // of 4 (FD problem with 128 intervals: about 10 us of idle GPU per iteration)
+      queued = j + 1 < m && it + 1 < maxit && res_prev * rate > 4.0 * rtol * bnorm;
+      counts.clear();
+      if (queued) {
+        for (auto &L : c->levels) counts.push_back(L.applies);
+        double *vn = Vb + (int64_t)(j + 1) * ld;
+        launch_scale_inv_sqrt(n, w, dnrm, vn, r32, s);
+        TRY(vcycle_replay(c, vn, Zb + (int64_t)(j + 1) * ld, s, r32 != nullptr));
+      }
+      HIPCHK(c, hipEventSynchronize(ev.e));
       const double hn = std::sqrt(hh[kMaxRestart]);
       bool finite = std::isfinite(hn);
       for (int i = 0; i <= j; ++i) finite = finite && std::isfinite(hh[i]);
       if (!finite) { c->err = "non-finite value in the GMRES iteration"; return SEM_ENAN; }
       for (int i = 0; i <= j; ++i) Hc(i, j) = hh[i];
       Hc(j + 1, j) = hn;
-      if (hn > 0.0) launch_scale_inv_sqrt(n, w, dnrm, Vb + (int64_t)(j + 1) * ld, s);
+      if (hn > 0.0 && !queued && j + 1 < m) launch_scale_inv_sqrt(n, w, dnrm, Vb + (int64_t)(j + 1) * ld, r32, s);
       for (int i = 0; i < j; ++i) {  // previous rotations
         const double t = cs[i] * Hc(i, j) + sn[i] * Hc(i + 1, j);
         Hc(i + 1, j) = -sn[i] * Hc(i, j) + cs[i] * Hc(i + 1, j);
@@ -1990,8 +2018,12 @@ sem_status gmres_solve(sem_ctx *c, const double *b, double *u, double *r, double
       if (history) history[it] = res;
       if (iters) *iters = it;
       if (relres) *relres = res / bnorm;
+      rate = std::min(1.0, res / res_prev);
+      res_prev = res;
       if (res <= rtol * bnorm || hn == 0.0) {
         done = true;
+        // a cycle queued for a step that does not come is not an application of the method
+        for (size_t q = 0; q < counts.size(); ++q) c->levels[q].applies = counts[q];
         break;
       }
       if (it >= maxit) break;
@@ -2028,8 +2060,8 @@ sem_status mg_solve(sem_ctx *c, const double *b, double *u, double *r, double bn
     TRY(vcycle_replay(c, r, z, s, mixed && it > 1));
     launch_axpby(n, 1.0, u, 1.0, z, u, s);
     fine_apply(c, u, w, nullptr, s);
-    launch_resid_norm(n, b, w, r, c->partials, kReduceBlocks, r32, s);
-    launch_finalize(kReduceBlocks, 1, c->partials, c->scal, S_RR, FIN_NONE, s);
+    launch_resid_norm(n, b, w, r, c->partials, reduce_blocks(n), r32, s);
+    launch_finalize(reduce_blocks(n), 1, c->partials, c->scal, S_RR, FIN_NONE, s);
     TRY(read_scalars(c, s));
     const double rr = c->pinned[S_RR];
     if (!std::isfinite(rr)) {
@@ -2059,8 +2091,8 @@ sem_status sem_solve(sem_ctx *c, const double *b, double *u, double rtol, int32_
   if (relres) *relres = 0.0;
   c->kop_us.clear();
   // ||b||^2 and ||u0||^2
-  launch_dots<double>(n, 2, b, b, u, u, nullptr, nullptr, c->partials, kReduceBlocks, s);
-  launch_finalize(kReduceBlocks, 2, c->partials, c->scal, S_BB, FIN_NONE, s);
+  launch_dots<double>(n, 2, b, b, u, u, nullptr, nullptr, c->partials, reduce_blocks(n), s);
+  launch_finalize(reduce_blocks(n), 2, c->partials, c->scal, S_BB, FIN_NONE, s);
   TRY(read_scalars(c, s));
   const double bb = c->pinned[S_BB], uu = c->pinned[S_BB + 1];
   if (!std::isfinite(bb) || !std::isfinite(uu)) { c->err = "non-finite right-hand side or initial guess"; return SEM_ENAN; }
@@ -2071,10 +2103,14 @@ sem_status sem_solve(sem_ctx *c, const double *b, double *u, double rtol, int32_
     fine_apply(c, u, w, nullptr, s);
     launch_axpby(n, 1.0, b, -1.0, w, r, s);
   }
-  launch_dots<double>(n, 1, r, r, nullptr, nullptr, nullptr, nullptr, c->partials, kReduceBlocks, s);
-  launch_finalize(kReduceBlocks, 1, c->partials, c->scal, S_RR, FIN_NONE, s);
-  TRY(read_scalars(c, s));
-  double rn = std::sqrt(c->pinned[S_RR]);
+  double rr0 = bb;  // from a zero guess r is b and the same reduction would give the same sum
+  if (uu != 0.0) {
+    launch_dots<double>(n, 1, r, r, nullptr, nullptr, nullptr, nullptr, c->partials, reduce_blocks(n), s);
+    launch_finalize(reduce_blocks(n), 1, c->partials, c->scal, S_RR, FIN_NONE, s);
+    TRY(read_scalars(c, s));
+    rr0 = c->pinned[S_RR];
+  }
+  double rn = std::sqrt(rr0);
   if (history) history[0] = rn;
   if (bnorm == 0.0) {
     if (uu != 0.0) HIPCHK(c, hipMemsetAsync(u, 0, n * sizeof(double), s));
@@ -2092,14 +2128,14 @@ sem_status sem_solve(sem_ctx *c, const double *b, double *u, double rtol, int32_
     return st;
   }
   if (c->opt.krylov == SEM_GMRES) {
-    const sem_status st = gmres_solve(c, b, u, r, c->pinned[S_RR], bnorm, rtol, maxit, iters, relres, history, s);
+    const sem_status st = gmres_solve(c, b, u, r, rr0, bnorm, rtol, maxit, iters, relres, history, s);
     HIPCHK(c, hipStreamSynchronize(s));
     HIPCHK(c, hipGetLastError());
     return st;
   }
   TRY(vcycle_replay(c, r, z, s, false));
-  launch_dots<double>(n, 1, r, z, nullptr, nullptr, nullptr, nullptr, c->partials, kReduceBlocks, s);
-  launch_finalize(kReduceBlocks, 1, c->partials, c->scal, S_RZ, FIN_INIT_RZ, s);
+  launch_dots<double>(n, 1, r, z, nullptr, nullptr, nullptr, nullptr, c->partials, reduce_blocks(n), s);
+  launch_finalize(reduce_blocks(n), 1, c->partials, c->scal, S_RZ, FIN_INIT_RZ, s);
   HIPCHK(c, hipMemcpyAsync(p, z, n * sizeof(double), hipMemcpyDeviceToDevice, s));
   sem_status status = SEM_ENOTCONV;
   int it = 0;
@@ -2117,12 +2153,7 @@ sem_status sem_solve(sem_ctx *c, const double *b, double *u, double rtol, int32_
   // has applied x += alpha p, which was due anyway, and the new p is not used. The lookahead
   // is skipped when the last reduction rate predicts convergence within a factor of 4 (a
   // wasted cycle would cost more than the waits it saves); the results are the same either way.
-  struct EventGuard {
-    hipEvent_t e = nullptr;
-    ~EventGuard() {
-      if (e) hipEventDestroy(e);
-    }
-  } sev;
+  EventGuard sev;
   HIPCHK(c, hipEventCreateWithFlags(&sev.e, hipEventDisableTiming));
   double rn_prev = bnorm, rate = 1.0;  // last residual norm and reduction factor
   // z = M r with z . r (and z . r_old for the flexible beta), reduced inside the cycle when it
@@ -2137,9 +2168,9 @@ sem_status sem_solve(sem_ctx *c, const double *b, double *u, double rtol, int32_
         c->err = "the single-precision cycle did not reduce z . r";
         return SEM_EINVAL;
       }
-      if (flexible) launch_dots<double>(n, 2, z, r, z, r2, nullptr, nullptr, c->partials, kReduceBlocks, s);
-      else launch_dots<double>(n, 1, z, r, nullptr, nullptr, nullptr, nullptr, c->partials, kReduceBlocks, s);
-      zb = kReduceBlocks;
+      if (flexible) launch_dots<double>(n, 2, z, r, z, r2, nullptr, nullptr, c->partials, reduce_blocks(n), s);
+      else launch_dots<double>(n, 1, z, r, nullptr, nullptr, nullptr, nullptr, c->partials, reduce_blocks(n), s);
+      zb = reduce_blocks(n);
     }
     launch_finalize(zb, flexible ? 2 : 1, c->partials, c->scal, S_ZR, flexible ? FIN_BETA_FCG : FIN_BETA_PCG, s);
     if (z32) launch_update_xp32(n, c->scal, u, L0.x32, p, s);
@@ -2173,8 +2204,8 @@ sem_status sem_solve(sem_ctx *c, const double *b, double *u, double rtol, int32_
     } else {
       fine_apply(c, p, w, p, s);
       launch_finalize(c->npartials, 1, c->partials, c->scal, S_PW, FIN_NONE, s);
-      launch_update_r(n, c->scal, r, w, r2, c->partials, kReduceBlocks, mixed ? c->levels[0].b32 : nullptr, s);
-      launch_finalize(kReduceBlocks, 1, c->partials, c->scal, S_RR, FIN_NONE, s);
+      launch_update_r(n, c->scal, r, w, r2, c->partials, reduce_blocks(n), mixed ? c->levels[0].b32 : nullptr, s);
+      launch_finalize(reduce_blocks(n), 1, c->partials, c->scal, S_RR, FIN_NONE, s);
     }
     x_pending = true;
     HIPCHK(c, hipMemcpyAsync(c->pinned, c->scal, S_COUNT * sizeof(double), hipMemcpyDeviceToHost, s));

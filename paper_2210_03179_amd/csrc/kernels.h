@@ -41,7 +41,8 @@ enum { S_RZ = 0, S_PW = 1, S_RR = 2, S_ZR = 3, S_ZRO = 4, S_BB = 5, S_BETA = 6, 
 // scalar operations done by the finalize kernel after the reduction
 enum { FIN_NONE = 0, FIN_INIT_RZ = 1, FIN_BETA_PCG = 2, FIN_BETA_FCG = 3 };
 
-constexpr int kReduceBlocks = 1024;  // fixed grid of the reduction kernels (deterministic sums)
+constexpr int kReduceBlocks = 1024;  // largest grid of the reduction kernels
+int reduce_blocks(int64_t n);        // their grid, by the vector length alone (deterministic sums)
 
 bool launch_ax(const Level &L, const double *u, double *wL, hipStream_t s);
 bool launch_ax(const Level &L, const float *u, float *wL, hipStream_t s);
@@ -159,8 +160,8 @@ void launch_finalize_many(int nblocks, int nd, const double *partials, double *o
 // not null, partials[blk] = (sum over the block's range of y_new^2)
 void launch_multi_axpy(int64_t n, int k, const double *V, int64_t ldv, const double *c, double sign, double *y,
                        double *partials, int nblocks, hipStream_t s);
-// y = x / sqrt(*nrm2)
-void launch_scale_inv_sqrt(int64_t n, const double *x, const double *nrm2, double *y, hipStream_t s);
+// y = x / sqrt(*nrm2), and its single-precision copy (optional)
+void launch_scale_inv_sqrt(int64_t n, const double *x, const double *nrm2, double *y, float *y32, hipStream_t s);
 
 // Schwarz smoother (Sec. 4.1) of a SEM level with element order N >= 3: y_e = Abar_e^{-1} R_e v
 // for every element (fast diagonalisation with Sm = [e][axis][nb][nb] eigenvectors and
