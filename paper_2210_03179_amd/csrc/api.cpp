@@ -202,8 +202,6 @@ template <> struct V<double> {
   static const double *swD(const Level &L) { return L.swD64; }
   static double *swY(Level &L) { return L.swY64; }
   static double *swT(Level &L) { return L.swT64; }
-  static double *wl(Level &L) { return L.wl64; }
-  static const double *winv(const Level &L) { return L.winv64; }
 };
 template <> struct V<float> {
   static float *&b(Level &L) { return L.b32; }
@@ -217,20 +215,17 @@ template <> struct V<float> {
   static const float *swD(const Level &L) { return L.swD32; }
   static float *swY(Level &L) { return L.swY32; }
   static float *swT(Level &L) { return L.swT32; }
-  static float *wl(Level &L) { return L.wl32; }
-  static const float *winv(const Level &L) { return L.winv32; }
 };
 
-// operator on level L: SEM -> element-local result in w (length E (N+1)^3),
+// operator on level L: SEM (box or mesh) -> element-local result in w (length E (N+1)^3),
 // FD -> global result in w.
 template <typename T>
 void apply_level(Level &L, const T *u, T *w, hipStream_t s) {
   L.applies++;
   if (L.type == LVL_SEM) {
     launch_ax(L, u, w, s);
-  } else if (L.type == LVL_GEN) {  // unstructured mesh: element products, then their sums
-    launch_ax_map(L, u, V<T>::wl(L), s);
-    launch_sum_lists<T, T>(L, V<T>::wl(L), w, nullptr, false, s);
+  } else if (L.type == LVL_GEN) {  // unstructured mesh
+    launch_ax_map(L, u, w, s);
   } else if constexpr (sizeof(T) == 8) {  // sparse levels run in FP64 only
     launch_ell(L.A, u, nullptr, w, 0, s);
   }
@@ -545,6 +540,7 @@ bool coarse_wide(const sem_ctx *c) {
   const size_t m = c->levels.size();
   if (m < 2) return false;
   const Level &P = c->levels[m - 2], &L = c->levels[m - 1];
+  if (P.type == LVL_GEN && L.type == LVL_GEN) return true;
   return P.type == LVL_SEM && L.type == LVL_SEM && L.N == 1 && prolong_rows_available(P.N, 1);
 }
 
@@ -613,12 +609,16 @@ void vcycle(sem_ctx *c, int j, hipStream_t s) {
     if (wide) launch_dss_wide(C, C.w32, wide_b, s);
     else launch_dss<T>(C, V<T>::w(C), V<T>::b(C), s);
   } else if (L.type == LVL_GEN) {
-    // P^T r on a mesh: the residual weighted by 1 / copies, gathered to the element copies,
-    // interpolated back to the coarse order per element and summed over the coarse copies
+    // P^T r on a mesh: the residual weighted by 1 / copies, gathered and interpolated back to the
+    // coarse order per element, summed over the coarse copies
     launch_resid_weight<T>(L, ad, b, r, s);
-    launch_gather_map<T>(L, r, V<T>::winv(L), V<T>::wl(L), s);
-    launch_interp_elem<T>(L.E, C.N + 1, L.N + 1, V<T>::J(L), V<T>::wl(L), V<T>::wl(C), true, s);
-    launch_sum_lists<T, T>(C, V<T>::wl(C), V<T>::b(C), nullptr, false, s);
+    launch_restrict_map<T>(L, C, r, V<T>::J(L), V<T>::w(C), s);
+    if constexpr (sizeof(T) == 4) {
+      if (wide) launch_sum_lists<float, double>(C, C.w32, wide_b, s);
+      else launch_sum_lists<T, T>(C, V<T>::w(C), V<T>::b(C), s);
+    } else {
+      launch_sum_lists<T, T>(C, V<T>::w(C), V<T>::b(C), s);
+    }
   } else if constexpr (sizeof(T) == 8) {  // the residual with its product, then R = P^T
     if (pre > 0) {
       L.applies++;
@@ -641,10 +641,10 @@ void vcycle(sem_ctx *c, int j, hipStream_t s) {
                                      wide ? wide_x : nullptr);
     if (zdots) c->zdot_blocks = nb;
   } else if (L.type == LVL_GEN) {
-    // x += P x_c: coarse copies, interpolated per element, averaged over the fine copies
-    launch_gather_map<T>(C, V<T>::x(C), (const T *)nullptr, V<T>::wl(C), s);
-    launch_interp_elem<T>(L.E, C.N + 1, L.N + 1, V<T>::J(L), V<T>::wl(C), V<T>::wl(L), false, s);
-    launch_sum_lists<T, T>(L, V<T>::wl(L), x, V<T>::winv(L), true, s);
+    const int nb = launch_prolong_map<T>(L, C, V<T>::x(C), V<T>::J(L), x, zout, s, zdots ? c->zdot_r1 : nullptr,
+                                         zdots ? c->zdot_r2 : nullptr, c->partials, c->partials_cap,
+                                         wide ? wide_x : nullptr);
+    if (zdots) c->zdot_blocks = nb;
   } else if constexpr (sizeof(T) == 8) {
     launch_ell(L.P, C.x64, nullptr, x, 2, s);
   }
@@ -664,7 +664,7 @@ int vcycle_top(sem_ctx *c, const double *r, double *z, hipStream_t s, bool r32_r
   bool fused_out = false;
   if (c->opt.precision == SEM_MIXED) {
     if (!r32_ready) launch_convert(L0.n, r, L0.b32, s);
-    fused_out = c->opt.post_order == 0 && L0.type == LVL_SEM && c->levels.size() > 1;
+    fused_out = c->opt.post_order == 0 && L0.type != LVL_FD && c->levels.size() > 1;
     // z == nullptr (only when fused_out): the result stays in FP32 in L0.x32
     c->zout = fused_out ? z : nullptr;
     c->zout32 = fused_out && !z;
@@ -681,7 +681,7 @@ int vcycle_top(sem_ctx *c, const double *r, double *z, hipStream_t s, bool r32_r
     L0.x64 = sx;
   }
   // the partials count only when the prolongation that wrote them produced z itself
-  const bool z_last = c->opt.post_order == 0 && L0.type == LVL_SEM && c->levels.size() > 1 &&
+  const bool z_last = c->opt.post_order == 0 && L0.type != LVL_FD && c->levels.size() > 1 &&
                       (fused_out || c->opt.precision != SEM_MIXED);
   const int dot_blocks = (d1 && z_last) ? c->zdot_blocks : 0;
   c->zdot_r1 = c->zdot_r2 = nullptr;
@@ -749,8 +749,8 @@ void fine_apply(sem_ctx *c, const double *u, double *w, const double *p, hipStre
     if (p) c->npartials = launch_dss_dot(L0, L0.w64, w, p, c->partials, s);
     else launch_dss<double>(L0, L0.w64, w, s);
   } else if (L0.type == LVL_GEN) {
-    launch_ax_map(L0, u, L0.wl64, s);
-    launch_sum_lists<double, double>(L0, L0.wl64, w, nullptr, false, s);
+    launch_ax_map(L0, u, L0.w64, s);
+    launch_sum_lists<double, double>(L0, L0.w64, w, s);
     if (p) {
       launch_dots<double>(L0.n, 1, p, w, nullptr, nullptr, nullptr, nullptr, c->partials, reduce_blocks(L0.n), s);
       c->npartials = reduce_blocks(L0.n);
@@ -799,8 +799,8 @@ sem_status lanczos(sem_ctx *c, int j, double &out, hipStream_t s) {
       launch_ax(L, v, L.w64, s);
       launch_dss<double>(L, L.w64, wv, s);
     } else if (L.type == LVL_GEN) {
-      launch_ax_map(L, v, L.wl64, s);
-      launch_sum_lists<double, double>(L, L.wl64, wv, nullptr, false, s);
+      launch_ax_map(L, v, L.w64, s);
+      launch_sum_lists<double, double>(L, L.w64, wv, s);
     } else {
       launch_ell(L.A, v, nullptr, wv, 0, s);
     }
@@ -836,7 +836,7 @@ sem_status lanczos(sem_ctx *c, int j, double &out, hipStream_t s) {
 }
 
 sem_status alloc_level_vectors(sem_ctx *c, Level &L, bool mixed, bool coarse) {
-  const int64_t wlen = L.type == LVL_SEM ? L.L : L.n;
+  const int64_t wlen = L.type == LVL_FD ? L.n : L.L;
   if (!mixed) {
     TRY(dalloc(c, &L.b64, L.n));
     TRY(dalloc(c, &L.x64, L.n));
@@ -865,8 +865,9 @@ sem_status alloc_krylov(sem_ctx *c, int64_t n) {
   TRY(dalloc(c, &c->kw, n));
   TRY(dalloc(c, &c->scal, S_COUNT));
   c->partials_cap = (int64_t)std::max<size_t>((size_t)kReduceBlocks * kMaxRestart, (size_t)(n / 256 + 2));
-  // the fused Krylov operator writes one partial per operator block (at most one per element)
-  if (!c->levels.empty()) c->partials_cap = std::max<int64_t>(c->partials_cap, c->levels[0].E + 2);
+  // the fused Krylov operator writes one partial per operator block (at most one per element), the
+  // prolongation of a mesh two per element
+  if (!c->levels.empty()) c->partials_cap = std::max<int64_t>(c->partials_cap, 2 * c->levels[0].E + 2);
   TRY(dalloc(c, &c->partials, (size_t)c->partials_cap));
   HIPCHK(c, hipHostMalloc((void **)&c->pinned, S_COUNT * sizeof(double), hipHostMallocDefault));
   if (c->opt.krylov == SEM_GMRES) {
@@ -1593,8 +1594,21 @@ sem_status setup_mesh_impl(const sem_mesh *mesh, const sem_options *opt, hipStre
     TRY(upload(c, &L.winv64, winv.data(), winv.size(), s));
     TRY(upload(c, &L.winv32, winv32.data(), winv32.size(), s));
     TRY(upload(c, &L.map, h.l2g.data(), h.l2g.size(), s));
-    TRY(upload(c, &L.lrow, h.lrow.data(), h.lrow.size(), s));
-    TRY(upload(c, &L.lidx, h.lidx.data(), h.lidx.size(), s));
+    {  // copy lists and the map of the first copies
+      int64_t width = 2;
+      for (int64_t g = 0; g < h.n; ++g) width = std::max(width, h.lrow[g + 1] - h.lrow[g]);
+      L.copies.width = (int32_t)width;
+      L.copies.ld = (h.n + 63) / 64 * 64;
+      std::vector<int32_t> idx((size_t)(width * L.copies.ld), -1), own(h.l2g.size(), -1);
+      for (int64_t g = 0; g < h.n; ++g) {
+        for (int64_t p = h.lrow[g]; p < h.lrow[g + 1]; ++p) idx[(p - h.lrow[g]) * L.copies.ld + g] = h.lidx[p];
+        own[h.lidx[h.lrow[g]]] = (int32_t)g;
+      }
+      int32_t *dev = nullptr;
+      TRY(upload(c, &dev, idx.data(), idx.size(), s));
+      L.copies.idx = dev;
+      TRY(upload(c, &L.omap, own.data(), own.size(), s));
+    }
     if (mixed && !coarse) {
       std::vector<uint16_t> gb(h.G.size());
       for (size_t q = 0; q < gb.size(); ++q) gb[q] = to_bf16(h.G[q]);
@@ -1611,13 +1625,8 @@ sem_status setup_mesh_impl(const sem_mesh *mesh, const sem_options *opt, hipStre
       TRY(upload(c, &L.coords, h.coords.data(), h.coords.size(), s));
     }
     TRY(alloc_level_vectors(c, L, mixed, coarse));
-    // element-local work arrays: FP64 for the Krylov operator and the Lanczos estimates (and
-    // the FP64 cycle), FP32 for the mixed cycle's smoothing and transfers
-    TRY(dalloc(c, &L.wl64, (size_t)L.L));
-    if (mixed) {
-      TRY(dalloc(c, &L.wl32, (size_t)L.L));
-      if (!coarse || j == 0) TRY(dalloc(c, &L.w64, (size_t)L.n));
-    }
+    // FP64 element-local results of a mixed context: Krylov operator and Lanczos estimates
+    if (mixed && (!coarse || j == 0)) TRY(dalloc(c, &L.w64, (size_t)L.L));
     HIPCHK(c, hipStreamSynchronize(s));
   }
   CoarseSolver &C = c->coarse;
@@ -2140,13 +2149,13 @@ sem_status sem_solve(sem_ctx *c, const double *b, double *u, double rtol, int32_
   sem_status status = SEM_ENOTCONV;
   int it = 0;
   bool x_pending = false;  // x += alpha p of the last residual update not yet applied
-  // On box levels with stored factors the Krylov operator reduces p . Ap itself (u . A_L u per
+  // With stored factors the Krylov operator reduces p . Ap itself (u . A_L u per
   // element) and the residual update sums the element copies of Ap, so A p is never stored
   // as a global vector (one pass and one launch less per iteration)
   Level &L0 = c->levels[0];
   // (SEMCHEB_FUSED_KRYLOV=0 in the environment keeps the separate summation pass)
   const char *fk = std::getenv("SEMCHEB_FUSED_KRYLOV");
-  const bool fused = L0.type == LVL_SEM && !L0.tri64 && L0.G64 && !(fk && fk[0] == '0');
+  const bool fused = L0.type != LVL_FD && !L0.tri64 && L0.G64 && !(fk && fk[0] == '0');
   // One step of lookahead: the next preconditioner application and the direction update are
   // queued before the host waits for this iteration's scalars, so the GPU does not idle while
   // the host checks convergence. If the iteration turns out to be the last, the queued update
@@ -2159,7 +2168,7 @@ sem_status sem_solve(sem_ctx *c, const double *b, double *u, double rtol, int32_
   // z = M r with z . r (and z . r_old for the flexible beta), reduced inside the cycle when it
   // can; then beta, x += alpha p and p = z + beta p. A one-sided mixed cycle leaves z in FP32
   // (its values are single-precision numbers; widening them for storage would only add bytes)
-  const bool z32 = mixed && c->opt.post_order == 0 && L0.type == LVL_SEM && c->levels.size() > 1;
+  const bool z32 = mixed && c->opt.post_order == 0 && L0.type != LVL_FD && c->levels.size() > 1;
   auto next_direction = [&]() -> sem_status {
     int zb = 0;
     TRY(vcycle_replay(c, r, z32 ? nullptr : z, s, mixed, r, flexible ? r2 : nullptr, &zb));
@@ -2180,7 +2189,7 @@ sem_status sem_solve(sem_ctx *c, const double *b, double *u, double rtol, int32_
   // the Krylov operator's own duration inside the solve, on request: each launch takes an event
   // pair as its kernel's start and end timestamps (no markers of their own on the stream, no
   // synchronisation), read after the solve
-  const bool kop_time = krylov_op_timing_enabled() && fused;
+  const bool kop_time = krylov_op_timing_enabled() && fused && L0.type == LVL_SEM;
   int kop_n = 0;
   if (kop_time) {
     while ((int64_t)c->kop_events.size() < 2 * (int64_t)maxit) {
@@ -2193,13 +2202,17 @@ sem_status sem_solve(sem_ctx *c, const double *b, double *u, double rtol, int32_
     if (fused) {
       L0.applies++;
       if (kop_time) set_ax_launch_events(c->kop_events[2 * kop_n], c->kop_events[2 * kop_n + 1]);
-      const int nb = launch_ax_dot(L0, p, L0.w64, c->partials, s);
+      const int nb = L0.type == LVL_GEN ? launch_ax_map_dot(L0, p, L0.w64, c->partials, s)
+                                        : launch_ax_dot(L0, p, L0.w64, c->partials, s);
       if (kop_time) {
         set_ax_launch_events(nullptr, nullptr);  // consumed by that launch; never left pending
         ++kop_n;
       }
       launch_finalize(nb, 1, c->partials, c->scal, S_PW, FIN_NONE, s);
-      const int nr = launch_update_r_dss(L0, c->scal, r, L0.w64, r2, c->partials, mixed ? L0.b32 : nullptr, s);
+      float *r32 = mixed ? L0.b32 : nullptr;
+      const int nr = L0.type == LVL_GEN
+                         ? launch_update_r_lists(L0, c->scal, r, L0.w64, r2, c->partials, r32, s)
+                         : launch_update_r_dss(L0, c->scal, r, L0.w64, r2, c->partials, r32, s);
       launch_finalize(nr, 1, c->partials, c->scal, S_RR, FIN_NONE, s);
     } else {
       fine_apply(c, p, w, p, s);

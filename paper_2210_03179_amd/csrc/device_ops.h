@@ -197,6 +197,27 @@ __device__ __forceinline__ void block_sum_store(double v, double *out) {
   }
 }
 
+// ------------------------------------------------------------------ Chebyshev update of one unknown
+// Algorithms 1 and 2 with the loaded values of an unknown: the residual input rr, ad = (A d),
+// sv = 1 / diag(A), the previous direction dd and iterate xx:
+//   rr = S_ON_R ? sv * rr : rr;  if SUB_AD:  rr -= (mode 1 ? sv * ad : ad)
+//   dn = (D_INIT ? 0 : dd) * a + bc * (mode 4 ? sv * rr : rr)
+//   xn = (X_INIT ? 0 : X_FROM_D ? cprev * dd : xx) + c * dn
+template <typename T>
+__device__ __forceinline__ void cheb_update(T &rr, T ad, T sv, T dd, T xx, T a, T bc, T c, T cprev, int flags,
+                                            int mode, T &dn, T &xn) {
+  if (flags & CHEB_S_ON_R) rr = sv * rr;
+  if (flags & CHEB_SUB_AD) rr = (mode == 1) ? rr - sv * ad : rr - ad;
+  dn = (flags & CHEB_D_INIT) ? T(0) : a * dd;
+  dn = dn + bc * (mode == 4 ? sv * rr : rr);
+  // cprev * d rounded on its own, as the first step's x was (no contraction into the fma below)
+  T xd;
+  if constexpr (sizeof(T) == 8) xd = __dmul_rn(cprev, dd);
+  else xd = __fmul_rn(cprev, dd);
+  const T xp = (flags & CHEB_X_INIT) ? T(0) : (flags & CHEB_X_FROM_D) ? xd : xx;
+  xn = xp + c * dn;
+}
+
 // ------------------------------------------------------------------ operator (element-local)
 // pdot (optional, FP64): the block's share of u . A_L u, the p . Ap of a Krylov iteration.
 // By the tensor-product form it is sum over nodes of (D_r u, D_s u, D_t u) . G (D_r u, D_s u,

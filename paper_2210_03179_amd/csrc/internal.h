@@ -147,8 +147,8 @@ double tridiag_max_eig(const std::vector<double> &a, const std::vector<double> &
 
 // ---------------------------------------------------------------- device level data
 // LVL_SEM: box lattice (index-free); LVL_FD: CSR operator; LVL_GEN: unstructured SEM mesh
-// (element operator through a local-to-global map, summation over per-unknown copy lists;
-// its operator results and transfers are global vectors, like those of LVL_FD)
+// (element operator and transfers through a local-to-global map, summation over per-unknown
+// copy lists by the kernels that use element-local results, as on a box)
 enum LevelType { LVL_SEM = 0, LVL_FD = 1, LVL_GEN = 2 };
 
 // Sparse matrix of a CSR level on the device, stored by entries (ELL): entry k of row r at
@@ -176,6 +176,14 @@ struct TailArgs {
   double beta_pre[32], beta_post[32];
 };
 
+// The element copies of every unknown of an unstructured mesh, in increasing local index: copy k of
+// unknown g at idx[k * ld + g], -1 past its last one (width >= 2).
+struct CopyLists {
+  int64_t ld = 0;
+  int32_t width = 0;
+  const int32_t *idx = nullptr;
+};
+
 struct Level {
   LevelType type = LVL_SEM;
   int N = 0, n1 = 0;
@@ -197,13 +205,13 @@ struct Level {
   double *coords = nullptr;   // [n][3] (finest level)
   // FD
   EllArgs A, P, R;            // A_j; P: level j+1 -> j (rows n); R = P^T (rows n_{j+1})
-  // unstructured mesh: local-to-global map (E (N+1)^3, -1 Dirichlet), copy lists of every
-  // unknown, 1 / (number of copies), element-local work arrays
+  // unstructured mesh: local-to-global map (E (N+1)^3, -1 Dirichlet), the map of the first copies
+  // (-1 at the others), copy lists of every unknown, 1 / (number of copies)
   int32_t *map = nullptr;
-  int64_t *lrow = nullptr;
-  int32_t *lidx = nullptr;
-  double *winv64 = nullptr, *wl64 = nullptr;
-  float *winv32 = nullptr, *wl32 = nullptr;
+  CopyLists copies;
+  int32_t *omap = nullptr;
+  double *winv64 = nullptr;
+  float *winv32 = nullptr;
   // both
   double *invdiag64 = nullptr;
   float *invdiag32 = nullptr;

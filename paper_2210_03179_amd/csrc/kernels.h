@@ -59,17 +59,36 @@ int ax_elems_per_block(int N);
 int launch_update_r_dss(const Level &L, double *scal, const double *r, const double *wL, double *rnew,
                         double *partials, float *r32, hipStream_t s);
 int update_r_dss_blocks(int64_t n);
-// unstructured meshes (LVL_GEN): operator with the input gathered through L.map, summation
-// over the local copies (optionally scaled per unknown, optionally added to out), gather of
-// a global vector to element-local copies, element-local interpolation (J: no x ni)
+// (fine, coarse) order pairs with compiled-in sizes: the N -> N/2 -> 1 schedules for
+// N = 2..12 and the (7,5,3,1) schedule; other pairs use the run-time sized kernels.
+#define SEMCHEB_TRANSFER_PAIRS(X) \
+  X(2, 1) X(3, 1) X(4, 1) X(5, 1) X(6, 1) X(4, 2) X(5, 2) X(6, 3) X(7, 3) X(8, 4) X(9, 4) X(10, 5) \
+  X(11, 5) X(12, 6) X(7, 5) X(5, 3)
+
+
+// Unstructured meshes (LVL_GEN, mesh.hip): as on a box, operator results are element-local vectors
+// that the kernel using them sums, here through the level's copy lists; the operator and the
+// transfers gather their input through the local-to-global map.
 bool launch_ax_map(const Level &L, const double *u, double *wL, hipStream_t s);
 bool launch_ax_map(const Level &L, const float *u, float *wL, hipStream_t s);
+// with one partial of u . A_L u per block; returns the number of partials
+int launch_ax_map_dot(const Level &L, const double *u, double *wL, double *partials, hipStream_t s);
 template <typename T, typename TO>
-void launch_sum_lists(const Level &L, const T *wL, TO *out, const T *scale, bool add, hipStream_t s);
+void launch_sum_lists(const Level &L, const T *wL, TO *out, hipStream_t s);
 template <typename T>
-void launch_gather_map(const Level &L, const T *u, const T *scale, T *uL, hipStream_t s);
+void launch_cheb_lists(const Level &L, const T *wL, const T *b, const T *r_in, T *r_out, T *d, T *x, const T *invdiag,
+                       double a, double bc, double c, int flags, int mode, hipStream_t s, double cprev);
 template <typename T>
-void launch_interp_elem(int64_t E, int ni, int no, const T *J, const T *in, T *out, bool transpose, hipStream_t s);
+void launch_resid_lists(const Level &L, const T *wL, const T *b, T *rw, hipStream_t s);
+template <typename T>
+void launch_restrict_map(const Level &F, const Level &C, const T *rw, const T *J, T *rcL, hipStream_t s);
+// x += P x_c or, with zout, zout = x + P x_c; dr1, dr2 and the result as in launch_prolong
+template <typename T>
+int launch_prolong_map(const Level &F, const Level &C, const T *xc, const T *J, T *xf, double *zout, hipStream_t s,
+                       const double *dr1, const double *dr2, double *partials, int64_t partials_cap,
+                       const double *xc64);
+int launch_update_r_lists(const Level &L, double *scal, const double *r, const double *wL, double *rnew,
+                          double *partials, float *r32, hipStream_t s);
 template <typename T>
 void launch_dss(const Level &L, const T *wL, T *out, hipStream_t s);
 // out = DSS(wL) and per-block partials of p . out; returns the number of partials written
