@@ -88,11 +88,12 @@ LaunchTable make_table(const std::vector<int> &act, F blocks_of) {
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 struct Tables {
-  // per smoothed level: nodes (4 per thread), nodes (1 per thread), elements; per order: operator
-  LaunchTable node4[kBatchLevels], node1[kBatchLevels], elem[kBatchLevels];
+  // per smoothed level: nodes (4 per thread), nodes (1 per thread), element runs of the transfers;
+  // per order: operator
+  LaunchTable node4[kBatchLevels], node1[kBatchLevels], xfer[kBatchLevels];
   std::vector<std::pair<int, LaunchTable>> ax[kBatchLevels];  // (order, table)
   std::vector<std::pair<int, LaunchTable>> ax64;              // finest level, FP64
-  LaunchTable coarse_rows, coarse_nodes, fine_nodes, fine_dot2;
+  LaunchTable coarse_rows, fine_nodes, fine_dot2;
   size_t lds_restrict[kBatchLevels] = {0, 0, 0}, lds_prolong[kBatchLevels] = {0, 0, 0};
 };
 
@@ -101,7 +102,6 @@ Tables build_tables(const sem_batch &B, const std::vector<int> &act) {
   for (int j = 0; j < kBatchLevels; ++j) {
     T.node4[j] = make_table(act, [&](int s) { return cdiv(B.host[s].lev[j].n, 1024); });
     T.node1[j] = make_table(act, [&](int s) { return cdiv(B.host[s].lev[j].n, 256); });
-    T.elem[j] = make_table(act, [&](int s) { return B.host[s].lev[j].E; });
     std::map<int, std::vector<int>> byN;
     for (int s : act) byN[B.host[s].lev[j].N].push_back(s);
     for (auto &kv : byN) {
@@ -111,16 +111,16 @@ Tables build_tables(const sem_batch &B, const std::vector<int> &act) {
         T.ax64.push_back({kv.first, make_table(kv.second, [&](int s) { return cdiv(B.host[s].lev[j].E, epb); })});
     }
     if (j + 1 < kBatchLevels) {
-      for (int s : act) {
-        const int nf = B.host[s].lev[j].N + 1, nc = B.host[s].lev[j + 1].N + 1;
-        T.lds_restrict[j] = std::max(T.lds_restrict[j], sizeof(float) * (size_t)(nf * nc + nf * nf * nf + nf * nf * nc));
-        T.lds_prolong[j] =
-            std::max(T.lds_prolong[j], sizeof(float) * (size_t)(nf * nc + nc * nc * nc + nc * nc * nf + nc * nf * nf));
-      }
+      T.xfer[j] = make_table(act, [&](int s) {
+        const BatchLevelDev &L = B.host[s].lev[j];
+        const BatchTransfer x = batch_transfer(L.N, j == 0);
+        T.lds_restrict[j] = std::max(T.lds_restrict[j], x.lds_down);
+        T.lds_prolong[j] = std::max(T.lds_prolong[j], x.lds_up);
+        return cdiv(L.nex, x.ex) * L.ney * L.nez;
+      });
     }
   }
   T.coarse_rows = make_table(act, [&](int s) { return B.host[s].nc; });
-  T.coarse_nodes = make_table(act, [&](int s) { return cdiv(B.host[s].nc, 256); });
   T.fine_nodes = T.node1[0];
   T.fine_dot2 = make_table(act, [&](int s) { return cdiv(B.host[s].lev[0].n, 512); });
   return T;
@@ -173,18 +173,16 @@ void vcycle_b(const sem_ctx *c, const Tables &T, const BatchSysDev *d, hipStream
   for (int j = 0; j + 1 < kBatchLevels; ++j) {
     smooth_b(c, T, d, j, pre, true, s);
     for (auto &g : T.ax[j]) launch_b_ax32(g.first, var32(c, j, g.first), g.second, d, j, 1, s);
-    launch_b_resid(T.node4[j], d, j, 1, s);
-    launch_b_restrict(T.elem[j], d, j, T.lds_restrict[j], s);
+    if (j == 0) launch_b_resid(T.node4[j], d, s);
+    launch_b_restrict(T.xfer[j], d, j, T.lds_restrict[j], s);
     launch_b_dss(T.node1[j + 1], d, j + 1, s);
   }
-  launch_b_convert(T.coarse_nodes, d, 0, 0, s);
   launch_b_coarse(T.coarse_rows, d, s);
-  launch_b_convert(T.coarse_nodes, d, 1, 0, s);
   for (int j = kBatchLevels - 2; j >= 0; --j) {
-    launch_b_prolong(T.elem[j], d, j, (j == 0 && post == 0) ? 1 : 0, T.lds_prolong[j], s);
+    launch_b_prolong(T.xfer[j], d, j, (j == 0 && post == 0) ? 1 : 0, T.lds_prolong[j], s);
     if (post > 0) smooth_b(c, T, d, j, post, false, s);
   }
-  if (post > 0) launch_b_convert(T.fine_nodes, d, 3, 0, s);
+  if (post > 0) launch_b_widen(T.fine_nodes, d, s);
 }
 
 // Batched autotuner: every operator variant is timed on the batched launch itself (all systems

@@ -205,6 +205,13 @@ namespace semcheb {
 // ---------------------------------------------------------------- batched launchers
 // The grid of every batched launch is t.begin[t.count] blocks (finalize: t.count).
 int batch_ax_elements_per_block(int N);
+// batched transfers from a level of order N: elements along x per block and the LDS bytes of a
+// block of the restriction and of the prolongation
+struct BatchTransfer {
+  int ex;
+  size_t lds_down, lds_up;
+};
+BatchTransfer batch_transfer(int N, bool finest);
 // batched operators in variant `variant` (the numbering of the single-system autotuner);
 // false for orders without batched kernels
 int64_t batched_launch_count();
@@ -213,11 +220,11 @@ bool launch_b_ax32(int N, int variant, const LaunchTable &t, const BatchSysDev *
 bool launch_b_ax64(int N, int variant, const LaunchTable &t, const BatchSysDev *sys, hipStream_t s);
 void launch_b_cheb(const LaunchTable &t, const BatchSysDev *sys, int level, int pp, int step, int flags, int mode,
                    hipStream_t s);
-void launch_b_resid(const LaunchTable &t, const BatchSysDev *sys, int level, int has_w, hipStream_t s);
+void launch_b_resid(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s);
 void launch_b_restrict(const LaunchTable &t, const BatchSysDev *sys, int level, size_t lds, hipStream_t s);
 void launch_b_dss(const LaunchTable &t, const BatchSysDev *sys, int level, hipStream_t s);
 void launch_b_prolong(const LaunchTable &t, const BatchSysDev *sys, int level, int to_z, size_t lds, hipStream_t s);
-void launch_b_convert(const LaunchTable &t, const BatchSysDev *sys, int op, int par, hipStream_t s);
+void launch_b_widen(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s);
 void launch_b_coarse(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s);
 void launch_b_dssdot(const LaunchTable &t, const BatchSysDev *sys, double *partials, hipStream_t s);
 void launch_b_finalize(const LaunchTable &t, const BatchSysDev *sys, const double *partials, int nd, int slot, int op,

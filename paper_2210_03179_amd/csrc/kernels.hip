@@ -389,18 +389,26 @@ inline bool short_runs(const Level &F, int ex) {
   return ex > 1 && (int64_t)((F.nex + ex - 1) / ex) * F.ney * F.nez < 256;
 }
 
+// LDS values of a block: the interpolation matrix and the staged rows with their partial contractions
+template <int NF, int NC, int EX>
+struct RowsLds {
+  static constexpr int nf = NF + 1, nc = NC + 1, RW = EX * NF + 1;
+  static constexpr int down = nf * nc + nf * nf * RW + EX * nf * nf * nc + EX * nf * nc * nc;
+  static constexpr int up = nf * nc + EX * nc * nc * nc + EX * nc * nc * nf + EX * nc * nf * nf;
+};
+
 template <typename T, int NF, int NC, int EX>
-__global__ void __launch_bounds__(256)
-restrict_rows_kernel(Box fb, Box cb, const T *__restrict__ rw, const T *__restrict__ Jm, T *__restrict__ rcL,
-                     const T *__restrict__ wL, const T *__restrict__ bvec) {
+__device__ __forceinline__ void
+restrict_rows_body(unsigned blk, const Box &fb, const Box &cb, const T *__restrict__ rw, const T *__restrict__ Jm,
+                   T *__restrict__ rcL, const T *__restrict__ wL, const T *__restrict__ bvec, T *lds) {
   constexpr int nf = NF + 1, nc = NC + 1, RW = EX * NF + 1;
-  __shared__ T sJ[nf * nc];
-  __shared__ T srow[nf * nf * RW];         // fine rows [k][j][i_global]
-  __shared__ T t1[EX * nf * nf * nc];      // [el][k][j][a]
-  __shared__ T t2[EX * nf * nc * nc];      // [el][k][b][a]
+  T *sJ = lds;
+  T *srow = sJ + nf * nc;                  // fine rows [k][j][i_global]
+  T *t1 = srow + nf * nf * RW;             // [el][k][j][a]
+  T *t2 = t1 + EX * nf * nf * nc;          // [el][k][b][a]
   const int ngx = (fb.nex + EX - 1) / EX;
-  const int gx = blockIdx.x % ngx;
-  const int ey = (blockIdx.x / ngx) % fb.ney, ez = blockIdx.x / (ngx * fb.ney);
+  const int gx = blk % ngx;
+  const int ey = (blk / ngx) % fb.ney, ez = blk / (ngx * fb.ney);
   const int ex0 = gx * EX;
   const int nel = fb.nex - ex0 < EX ? fb.nex - ex0 : EX;
   const int t = threadIdx.x;
@@ -472,19 +480,27 @@ restrict_rows_kernel(Box fb, Box cb, const T *__restrict__ rw, const T *__restri
   }
 }
 
-template <typename T, int NF, int NC, int EX, typename TC = T>
+template <typename T, int NF, int NC, int EX>
 __global__ void __launch_bounds__(256)
-prolong_rows_kernel(Box fb, Box cb, const TC *__restrict__ xc, const T *__restrict__ Jm, T *__restrict__ xf,
-                    double *__restrict__ zout, const double *__restrict__ dr1, const double *__restrict__ dr2,
-                    double *__restrict__ partials) {
+restrict_rows_kernel(Box fb, Box cb, const T *__restrict__ rw, const T *__restrict__ Jm, T *__restrict__ rcL,
+                     const T *__restrict__ wL, const T *__restrict__ bvec) {
+  __shared__ T lds[RowsLds<NF, NC, EX>::down];
+  restrict_rows_body<T, NF, NC, EX>(blockIdx.x, fb, cb, rw, Jm, rcL, wL, bvec, lds);
+}
+
+template <typename T, int NF, int NC, int EX, typename TC>
+__device__ __forceinline__ void
+prolong_rows_body(unsigned blk, const Box &fb, const Box &cb, const TC *__restrict__ xc, const T *__restrict__ Jm,
+                  T *__restrict__ xf, double *__restrict__ zout, const double *__restrict__ dr1,
+                  const double *__restrict__ dr2, double *__restrict__ partials, T *lds) {
   constexpr int nf = NF + 1, nc = NC + 1;
-  __shared__ T sJ[nf * nc];
-  __shared__ T sc[EX * nc * nc * nc];      // [el][c][b][a]
-  __shared__ T t1[EX * nc * nc * nf];      // [el][c][b][i]
-  __shared__ T t2[EX * nc * nf * nf];      // [el][c][j][i]
+  T *sJ = lds;
+  T *sc = sJ + nf * nc;                    // [el][c][b][a]
+  T *t1 = sc + EX * nc * nc * nc;          // [el][c][b][i]
+  T *t2 = t1 + EX * nc * nc * nf;          // [el][c][j][i]
   const int ngx = (fb.nex + EX - 1) / EX;
-  const int gx = blockIdx.x % ngx;
-  const int ey = (blockIdx.x / ngx) % fb.ney, ez = blockIdx.x / (ngx * fb.ney);
+  const int gx = blk % ngx;
+  const int ey = (blk / ngx) % fb.ney, ez = blk / (ngx * fb.ney);
   const int ex0 = gx * EX;
   const int nel = fb.nex - ex0 < EX ? fb.nex - ex0 : EX;
   const int t = threadIdx.x;
@@ -566,12 +582,21 @@ prolong_rows_kernel(Box fb, Box cb, const TC *__restrict__ xc, const T *__restri
     __shared__ double sm[4];
     const int nd = dr2 ? 2 : 1;
     double s = block_sum(d1, sm);
-    if (threadIdx.x == 0) partials[(int64_t)blockIdx.x * nd] = s;
+    if (threadIdx.x == 0) partials[(int64_t)blk * nd] = s;
     if (dr2) {
       s = block_sum(d2, sm);
-      if (threadIdx.x == 0) partials[(int64_t)blockIdx.x * nd + 1] = s;
+      if (threadIdx.x == 0) partials[(int64_t)blk * nd + 1] = s;
     }
   }
+}
+
+template <typename T, int NF, int NC, int EX, typename TC = T>
+__global__ void __launch_bounds__(256)
+prolong_rows_kernel(Box fb, Box cb, const TC *__restrict__ xc, const T *__restrict__ Jm, T *__restrict__ xf,
+                    double *__restrict__ zout, const double *__restrict__ dr1, const double *__restrict__ dr2,
+                    double *__restrict__ partials) {
+  __shared__ T lds[RowsLds<NF, NC, EX>::up];
+  prolong_rows_body<T, NF, NC, EX, TC>(blockIdx.x, fb, cb, xc, Jm, xf, zout, dr1, dr2, partials, lds);
 }
 
 // ------------------------------------------------------------------ Schwarz smoother
@@ -1370,49 +1395,97 @@ b_cheb_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int level, i
 }
 
 __global__ void __launch_bounds__(256)
-b_resid_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int level, int has_w) {
+b_resid_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
   SEMCHEB_BATCH_SYS
-  const BatchLevelDev &L = S.lev[level];
-  resid_weight_body<float, 4>(blk, lbox(L), L.n, has_w ? L.w : nullptr, L.b, L.r);
+  const BatchLevelDev &L = S.lev[0];
+  resid_weight_body<float, 4>(blk, lbox(L), L.n, L.w, L.b, L.r);
 }
 
+// Order transfers: the row bodies of the single-system transfers, compiled for every batched order
+// (pairs N -> N/2 on the finest level, N/2 -> 1 below it) and selected per block, so one launch
+// serves systems of all orders; run lengths of about 1000 fine values per block, at most 4 elements
+// (systems are small: longer runs end ragged). With the orders read at run time (one element per
+// block, index divisions by variables) 16 systems of orders 5, 7, 9 with 6.3 K elements took 31 us
+// down and 32 us up on the finest level, 10 and 11 us below it; now 15.8 and 21.8 us, and 8.8 (with
+// the residual, 6.5 us before as a launch of its own) and 7.7 us.
+template <int N>
+constexpr int batch_ex() {
+  constexpr int e = 1000 / ((N + 1) * (N + 1) * N);
+  return e < 1 ? 1 : (e > 4 ? 4 : e);
+}
+#define SEMCHEB_BATCH_FINE(X) X(4, 2) X(5, 2) X(6, 3) X(7, 3) X(8, 4) X(9, 4) X(10, 5) X(11, 5) X(12, 6)
+#define SEMCHEB_BATCH_MID(X) X(2, 1) X(3, 1) X(4, 1) X(5, 1) X(6, 1)
+
+// from the weighted residual of the finest level; below it the residual is formed while reading
+template <bool FINE>
 __global__ void __launch_bounds__(256)
-b_restrict_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int level) {
+b_restrict_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
+  float *lds = reinterpret_cast<float *>(smem_raw);
   SEMCHEB_BATCH_SYS
-  const BatchLevelDev &F = S.lev[level], &C = S.lev[level + 1];
-  restrict_body<float>(blk, lbox(F), lbox(C), F.E, F.r, F.J, C.w, reinterpret_cast<float *>(smem_raw));
+  const BatchLevelDev &F = S.lev[FINE ? 0 : 1], &C = S.lev[FINE ? 1 : 2];
+#define SEMCHEB_CASE(A, B)                                                                                      \
+  case A:                                                                                                       \
+    restrict_rows_body<float, A, B, batch_ex<A>()>(blk, lbox(F), lbox(C), FINE ? F.r : nullptr, F.J, C.w, F.w, \
+                                                   F.b, lds);                                                   \
+    break;
+  if constexpr (FINE) {
+    switch (F.N) { SEMCHEB_BATCH_FINE(SEMCHEB_CASE) }
+  } else {
+    switch (F.N) { SEMCHEB_BATCH_MID(SEMCHEB_CASE) }
+  }
+#undef SEMCHEB_CASE
 }
 
-// coarse right-hand side: b = DSS of the restricted element-local values
+// correction added to x; the order-1 level's solution is read in FP64 (its values are rounded to
+// single precision as they are read)
+template <bool FINE>
+__global__ void __launch_bounds__(256)
+b_prolong_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int to_z) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  float *lds = reinterpret_cast<float *>(smem_raw);
+  SEMCHEB_BATCH_SYS
+  const BatchLevelDev &F = S.lev[FINE ? 0 : 1], &C = S.lev[FINE ? 1 : 2];
+  if constexpr (FINE) {
+    double *z = to_z ? S.z : nullptr;
+#define SEMCHEB_CASE(A, B)                                                                                    \
+  case A:                                                                                                     \
+    prolong_rows_body<float, A, B, batch_ex<A>(), float>(blk, lbox(F), lbox(C), C.x, F.J, F.x, z, nullptr,   \
+                                                         nullptr, nullptr, lds);                              \
+    break;
+    switch (F.N) { SEMCHEB_BATCH_FINE(SEMCHEB_CASE) }
+#undef SEMCHEB_CASE
+  } else {
+#define SEMCHEB_CASE(A, B)                                                                                    \
+  case A:                                                                                                     \
+    prolong_rows_body<float, A, B, batch_ex<A>(), double>(blk, lbox(F), lbox(C), S.cx, F.J, F.x, nullptr,    \
+                                                          nullptr, nullptr, nullptr, lds);                    \
+    break;
+    switch (F.N) { SEMCHEB_BATCH_MID(SEMCHEB_CASE) }
+#undef SEMCHEB_CASE
+  }
+}
+
+// coarse right-hand side: DSS of the restricted element-local values, kept in FP64 on the order-1
+// level, where the dense solve reads it
 __global__ void __launch_bounds__(256)
 b_dss_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int level) {
   SEMCHEB_BATCH_SYS
   const BatchLevelDev &L = S.lev[level];
   const int64_t g = (int64_t)blk * blockDim.x + threadIdx.x;
-  if (g < L.n) L.b[g] = dss_at(L.w, lbox(L), g);
+  if (g >= L.n) return;
+  const float v = dss_at(L.w, lbox(L), g);
+  if (level == kBatchLevels - 1) S.cb[g] = (double)v;
+  else L.b[g] = v;
 }
 
+// finest cycle result widened to the Krylov vector z
 __global__ void __launch_bounds__(256)
-b_prolong_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int level, int to_z) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  SEMCHEB_BATCH_SYS
-  const BatchLevelDev &F = S.lev[level], &C = S.lev[level + 1];
-  prolong_body<float>(blk, lbox(F), lbox(C), F.E, C.x, F.J, F.x, to_z ? S.z : nullptr,
-                      reinterpret_cast<float *>(smem_raw));
-}
-
-// conversions: 0 coarse b (FP32 -> FP64), 1 coarse x (FP64 -> FP32),
-// 2 Krylov r[par] -> finest cycle b, 3 finest cycle x -> z
-__global__ void __launch_bounds__(256)
-b_convert_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int op, int par) {
+b_widen_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
   SEMCHEB_BATCH_SYS
   const int64_t g = (int64_t)blk * blockDim.x + threadIdx.x;
-  const BatchLevelDev &C = S.lev[kBatchLevels - 1], &F = S.lev[0];
-  if (op == 0) { if (g < S.nc) S.cb[g] = (double)C.b[g]; }
-  else if (op == 1) { if (g < S.nc) C.x[g] = (float)S.cx[g]; }
-  else if (op == 2) { if (g < F.n) F.b[g] = (float)S.r[par][g]; }
-  else { if (g < F.n) S.z[g] = (double)F.x[g]; }
+  const BatchLevelDev &F = S.lev[0];
+  if (g < F.n) S.z[g] = (double)F.x[g];
 }
 
 // exact coarse solve, one block per row of the dense inverse
@@ -2070,6 +2143,20 @@ int batch_ax_elements_per_block(int N) {
   }
 }
 
+BatchTransfer batch_transfer(int N, bool finest) {
+#define SEMCHEB_CASE(A, B)                                                                       \
+  case A:                                                                                        \
+    return {batch_ex<A>(), sizeof(float) * RowsLds<A, B, batch_ex<A>()>::down,                   \
+            sizeof(float) * RowsLds<A, B, batch_ex<A>()>::up};
+  if (finest) {
+    switch (N) { SEMCHEB_BATCH_FINE(SEMCHEB_CASE) default: break; }
+  } else {
+    switch (N) { SEMCHEB_BATCH_MID(SEMCHEB_CASE) default: break; }
+  }
+#undef SEMCHEB_CASE
+  return {1, 0, 0};
+}
+
 // batched orders: finest levels 4..12, the level below 2..6 (the order-1 level is solved densely)
 // batched kernel launches issued so far (all contexts; a batched solve reports the difference)
 std::atomic<int64_t> g_batched_launches{0};
@@ -2109,16 +2196,17 @@ void launch_b_cheb(const LaunchTable &t, const BatchSysDev *sys, int level, int 
     hipLaunchKernelGGL(b_cheb_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, level, pp, step, flags, mode);
   }
 }
-void launch_b_resid(const LaunchTable &t, const BatchSysDev *sys, int level, int has_w, hipStream_t s) {
+void launch_b_resid(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s) {
   if (t.count) {
     ++g_batched_launches;
-    hipLaunchKernelGGL(b_resid_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, level, has_w);
+    hipLaunchKernelGGL(b_resid_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys);
   }
 }
 void launch_b_restrict(const LaunchTable &t, const BatchSysDev *sys, int level, size_t lds, hipStream_t s) {
   if (t.count) {
     ++g_batched_launches;
-    hipLaunchKernelGGL(b_restrict_kernel, dim3(tgrid(t)), dim3(128), lds, s, t, sys, level);
+    if (level == 0) hipLaunchKernelGGL((b_restrict_kernel<true>), dim3(tgrid(t)), dim3(256), lds, s, t, sys);
+    else hipLaunchKernelGGL((b_restrict_kernel<false>), dim3(tgrid(t)), dim3(256), lds, s, t, sys);
   }
 }
 void launch_b_dss(const LaunchTable &t, const BatchSysDev *sys, int level, hipStream_t s) {
@@ -2130,13 +2218,14 @@ void launch_b_dss(const LaunchTable &t, const BatchSysDev *sys, int level, hipSt
 void launch_b_prolong(const LaunchTable &t, const BatchSysDev *sys, int level, int to_z, size_t lds, hipStream_t s) {
   if (t.count) {
     ++g_batched_launches;
-    hipLaunchKernelGGL(b_prolong_kernel, dim3(tgrid(t)), dim3(128), lds, s, t, sys, level, to_z);
+    if (level == 0) hipLaunchKernelGGL((b_prolong_kernel<true>), dim3(tgrid(t)), dim3(256), lds, s, t, sys, to_z);
+    else hipLaunchKernelGGL((b_prolong_kernel<false>), dim3(tgrid(t)), dim3(256), lds, s, t, sys, 0);
   }
 }
-void launch_b_convert(const LaunchTable &t, const BatchSysDev *sys, int op, int par, hipStream_t s) {
+void launch_b_widen(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s) {
   if (t.count) {
     ++g_batched_launches;
-    hipLaunchKernelGGL(b_convert_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, op, par);
+    hipLaunchKernelGGL(b_widen_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys);
   }
 }
 void launch_b_coarse(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s) {
