@@ -960,9 +960,15 @@ struct EvenOdd {
   static constexpr int P = 0, Q = h * h, C = 2 * h * h, R = 2 * h * h + h;
 };
 
+// A table that no kernel writes, named in the constant address space: its uniform loads go through
+// scalar registers also where the pointer itself was read from memory (the batched kernels, which
+// otherwise hold the table in vector registers: order 7, FP64, 50 spilled, order 9 12).
+template <typename T>
+using ConstTable = const T __attribute__((address_space(4)));
+
 // o = D u
 template <int N, typename T>
-__device__ __forceinline__ void eo_apply(const T *__restrict__ eo, const T (&u)[N + 1], T (&o)[N + 1]) {
+__device__ __forceinline__ void eo_apply(ConstTable<T> *__restrict__ eo, const T (&u)[N + 1], T (&o)[N + 1]) {
   using X = EvenOdd<N>;
   T s[X::h], d[X::h];
 #pragma unroll
@@ -992,7 +998,7 @@ __device__ __forceinline__ void eo_apply(const T *__restrict__ eo, const T (&u)[
 
 // o = D^T v
 template <int N, typename T>
-__device__ __forceinline__ void eo_apply_t(const T *__restrict__ eo, const T (&v)[N + 1], T (&o)[N + 1]) {
+__device__ __forceinline__ void eo_apply_t(ConstTable<T> *__restrict__ eo, const T (&v)[N + 1], T (&o)[N + 1]) {
   using X = EvenOdd<N>;
   T p[X::h], q[X::h];
 #pragma unroll
@@ -1063,7 +1069,7 @@ __device__ __forceinline__ void ax_body_pencil(unsigned blk, const Box &b, int64
   const bool active = full || ((le < epb) && (e < E));
   const int lec = active ? le : 0;
   const int64_t ec = active ? e : e0;
-  const T *eo = Dm + n2;
+  ConstTable<T> *eo = (ConstTable<T> *)(Dm + n2);
   T col[n1];
   if constexpr (MAP) {
     int32_t gi[n1];
