@@ -93,6 +93,8 @@ struct Tables {
   LaunchTable node4[kBatchLevels], node1[kBatchLevels], xfer[kBatchLevels];
   std::vector<std::pair<int, LaunchTable>> ax[kBatchLevels];  // (order, table)
   std::vector<std::pair<int, LaunchTable>> ax64;              // finest level, FP64
+  LaunchTable ax_all[kBatchLevels];                           // all orders in one launch
+  size_t lds_all[kBatchLevels] = {0, 0, 0};
   LaunchTable coarse_rows, fine_nodes, fine_dot2;
   size_t lds_restrict[kBatchLevels] = {0, 0, 0}, lds_prolong[kBatchLevels] = {0, 0, 0};
 };
@@ -111,6 +113,12 @@ Tables build_tables(const sem_batch &B, const std::vector<int> &act) {
         T.ax64.push_back({kv.first, make_table(kv.second, [&](int s) { return cdiv(B.host[s].lev[j].E, epb); })});
     }
     if (j + 1 < kBatchLevels) {
+      T.ax_all[j] = make_table(act, [&](int s) {
+        size_t need = 0;
+        const int epb = batch_ax_shared(B.host[s].lev[j].N, &need);
+        T.lds_all[j] = std::max(T.lds_all[j], need);
+        return cdiv(B.host[s].lev[j].E, epb);
+      });
       T.xfer[j] = make_table(act, [&](int s) {
         const BatchLevelDev &L = B.host[s].lev[j];
         const BatchTransfer x = batch_transfer(L.N, j == 0);
@@ -136,15 +144,19 @@ int var64(const sem_ctx *c, int N) {
   return it == c->batch->var64.end() ? 0 : it->second;
 }
 
+// single-precision operator of a cycle level on d (src 0) or x (src 1)
+void apply_b(const sem_ctx *c, const Tables &T, const BatchSysDev *d, int j, int src, hipStream_t s) {
+  if (c->batch->shared32[j]) launch_b_ax32_all(T.ax_all[j], d, j, src, T.lds_all[j], s);
+  else for (auto &g : T.ax[j]) launch_b_ax32(g.first, var32(c, j, g.first), g.second, d, j, src, s);
+}
+
 void smooth_b(const sem_ctx *c, const Tables &T, const BatchSysDev *d, int j, int k, bool zero_guess,
               hipStream_t s) {
   if (k <= 0) return;
   const int kind = c->opt.smoother;
   const int mode = (kind == SEM_CHEB4 || kind == SEM_CHEB4_OPT) ? 4 : 1;
   const int pp = zero_guess ? 0 : 1;
-  auto ax = [&](int src) {
-    for (auto &g : T.ax[j]) launch_b_ax32(g.first, var32(c, j, g.first), g.second, d, j, src, s);
-  };
+  auto ax = [&](int src) { apply_b(c, T, d, j, src, s); };
   int f0;
   if (mode == 4) {
     f0 = zero_guess ? (CHEB_R_FROM_B | CHEB_D_INIT | CHEB_X_INIT)
@@ -172,7 +184,7 @@ void vcycle_b(const sem_ctx *c, const Tables &T, const BatchSysDev *d, hipStream
   const int pre = c->opt.pre_order, post = c->opt.post_order;
   for (int j = 0; j + 1 < kBatchLevels; ++j) {
     smooth_b(c, T, d, j, pre, true, s);
-    for (auto &g : T.ax[j]) launch_b_ax32(g.first, var32(c, j, g.first), g.second, d, j, 1, s);
+    apply_b(c, T, d, j, 1, s);
     if (j == 0) launch_b_resid(T.node4[j], d, s);
     launch_b_restrict(T.xfer[j], d, j, T.lds_restrict[j], s);
     launch_b_dss(T.node1[j + 1], d, j + 1, s);
@@ -188,7 +200,8 @@ void vcycle_b(const sem_ctx *c, const Tables &T, const BatchSysDev *d, hipStream
 // Batched autotuner: every operator variant is timed on the batched launch itself (all systems
 // of one order on one level, FP32 cycle operators and the FP64 Krylov operator), best of three
 // rounds of three launches after a warm-up; the fastest is kept per order and level. The
-// variants compute the same sums and differ in scheduling, so results agree to rounding.
+// variants compute the same sums and differ in scheduling, so results agree to rounding. A level
+// with several orders is timed with one launch for all of them as well (apply_b).
 // SEMCHEB_AX_VARIANT=v fixes variant v everywhere; SEMCHEB_AUTOTUNE=0 keeps the defaults
 // (DMA-staged factors in FP32, register columns in FP64).
 sem_status autotune_batched(sem_ctx *c, hipStream_t s) {
@@ -255,6 +268,14 @@ sem_status autotune_batched(sem_ctx *c, hipStream_t s) {
     }
     B.var64[g.first] = bestv;
     B.time64[g.first] = t;
+  }
+  // several orders: their launches in turn against the one that serves all of them
+  for (int j = 0; j + 1 < kBatchLevels && st == SEM_OK; ++j) {
+    if (T.ax[j].size() < 2) continue;
+    auto apply = [&] { apply_b(c, T, B.dev, j, 0, s); };
+    const double apart = time_it(apply);
+    B.shared32[j] = true;
+    B.shared32[j] = time_it(apply) < apart && st == SEM_OK;
   }
   hipEventDestroy(e0);
   hipEventDestroy(e1);

@@ -6,6 +6,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include <cstdint>
 
 #include "kernels.h"
@@ -1031,6 +1033,26 @@ __device__ __forceinline__ void eo_apply_t(ConstTable<T> *__restrict__ eo, const
 // trilinear edge vectors (GEO_TRI).
 enum { GEO_REG = 0, GEO_DMA = 1, GEO_TRI = 2 };
 
+// LDS of the pencil operator: the staged factors, then two tiles per element
+template <int N, typename T, bool DMA, class S>
+struct PencilLds {
+  static constexpr int n1 = N + 1;
+  static constexpr int rp = n1 | 1;  // odd row pitch: pencils along r start in distinct banks
+  static constexpr int tile = n1 * n1 * rp;
+  static constexpr int factors = DMA ? (S::epb * 12 * n1 * n1 * n1 + 15) / 16 * 16 : 0;
+  static constexpr int bytes = factors + 2 * S::epb * tile * (int)sizeof(T);
+};
+
+// Blocks of one size for every order, for kernels that serve several: as many elements as 256
+// threads hold, 76 to 100 % of the lanes at orders 2 to 10, 66 % at 12 and 56 % at 11.
+template <int N>
+struct BlockShape {
+  static constexpr int n1 = N + 1;
+  static constexpr int tpe = n1 * n1;
+  static constexpr int block = 256;
+  static constexpr int epb = block / tpe;
+};
+
 // The operator with one thread per pencil: a thread reads a whole line of n1 values of the
 // element once, multiplies it with D in registers (even-odd form, D from scalar registers) and
 // puts the line back, instead of reading n1 values from LDS for every output. Lines along t are
@@ -1046,20 +1068,25 @@ enum { GEO_REG = 0, GEO_DMA = 1, GEO_TRI = 2 };
 // NT = false reads the factors with ordinary loads: at small odd sizes a plane of factors ends
 // inside a cache line whose rest the next plane's load finds in L1 (order 2: 98 -> 73 us, order
 // 4: 81 -> 71 us on 7 M local nodes; whole-line planes, order 7: no difference).
-template <int N, typename T, typename GT, int GEO, int PFK, bool MAP = false, bool NT = true>
+// S, lds: elements per block and LDS of a kernel that serves several orders (BlockShape), by
+// default the order's own.
+template <int N, typename T, typename GT, int GEO, int PFK, bool MAP = false, bool NT = true, class S = AxShape<N>>
 __device__ __forceinline__ void ax_body_pencil(unsigned blk, const Box &b, int64_t E, const T *__restrict__ u,
                                                const GT *__restrict__ G, const T *__restrict__ Dm,
                                                T *__restrict__ wL, const int32_t *__restrict__ map = nullptr,
                                                double *__restrict__ pdot = nullptr,
-                                               const T *__restrict__ gxw = nullptr) {
-  using S = AxShape<N>;
+                                               const T *__restrict__ gxw = nullptr,
+                                               unsigned char *lds = nullptr) {
+  using X = PencilLds<N, T, GEO == GEO_DMA, S>;
   constexpr int n1 = S::n1, n2 = n1 * n1, n3 = n2 * n1, epb = S::epb;
-  constexpr int rp = n1 | 1;  // odd row pitch: pencils along r start in distinct banks
+  constexpr int rp = X::rp;
   constexpr bool full = epb == 1 && S::tpe == S::block;  // every thread has an element
   constexpr int kElemBytes = 6 * n3 * 2;                 // BF16 factor block (GEO_DMA)
-  __shared__ __align__(16) uint16_t sG[GEO == GEO_DMA ? epb * 6 * n3 : 1];
-  __shared__ T sa[epb][n2 * rp];
-  __shared__ T sb[epb][n2 * rp];
+  constexpr bool own = std::is_same<S, AxShape<N>>::value;
+  __shared__ __align__(16) unsigned char own_lds[own ? X::bytes : 16];
+  unsigned char *base = own ? own_lds : lds;
+  [[maybe_unused]] uint16_t *sG = reinterpret_cast<uint16_t *>(base);
+  T *sa = reinterpret_cast<T *>(base + X::factors), *sb = sa + epb * X::tile;
   const int t = threadIdx.x;
   const int le = t / S::tpe;
   const int ij = t - le * S::tpe;
@@ -1128,7 +1155,7 @@ __device__ __forceinline__ void ax_body_pencil(unsigned blk, const Box &b, int64
   } else {
     tri = tri_column<N, T>(reinterpret_cast<const T *>(G) + ec * 36, gxw, i, j);
   }
-  T *A = sa[lec], *B = sb[lec];
+  T *A = sa + lec * X::tile, *B = sb + lec * X::tile;
   // the thread's three pencils: column (i, j, :), row (:, i', j') and s-line (i', :, j')
   const int cq = j * rp + i, rq = ij * rp, sq = j * (n1 * rp) + i;
   if (active) {

@@ -376,5 +376,7 @@ struct sem_batch {
   // the six variants are kept for inspection (-1 where not timed)
   std::map<int, int> var32[semcheb::kBatchLevels], var64;
   std::map<int, std::vector<double>> time32[semcheb::kBatchLevels], time64;
+  // all orders of the level in one launch (pencil operator) where setup timed that as faster
+  bool shared32[semcheb::kBatchLevels] = {false, false, false};
   int64_t last_launches = 0;  // kernel launches issued by the last batched solve
 };

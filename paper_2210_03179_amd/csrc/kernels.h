@@ -218,6 +218,10 @@ int64_t batched_launch_count();
 bool launch_b_ax32(int N, int variant, const LaunchTable &t, const BatchSysDev *sys, int level, int src,
                    hipStream_t s);
 bool launch_b_ax64(int N, int variant, const LaunchTable &t, const BatchSysDev *sys, hipStream_t s);
+// the single-precision pencil operator of all orders of a level in one launch: elements per block of
+// an order and the block's LDS bytes, of which a launch takes the largest
+int batch_ax_shared(int N, size_t *lds);
+void launch_b_ax32_all(const LaunchTable &t, const BatchSysDev *sys, int level, int src, size_t lds, hipStream_t s);
 void launch_b_cheb(const LaunchTable &t, const BatchSysDev *sys, int level, int pp, int step, int flags, int mode,
                    hipStream_t s);
 void launch_b_resid(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s);

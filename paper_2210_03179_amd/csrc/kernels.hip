@@ -1333,6 +1333,9 @@ __device__ __forceinline__ int table_slot(const LaunchTable &t, unsigned b) {
 __device__ __forceinline__ Box lbox(const BatchLevelDev &L) {
   return Box{L.N, L.nex, L.ney, L.nez, L.nx, L.ny, L.nz, make_fastdiv(L.N)};
 }
+// order pairs of a batch: the finest level with the one below it, that level with order 1
+#define SEMCHEB_BATCH_FINE(X) X(4, 2) X(5, 2) X(6, 3) X(7, 3) X(8, 4) X(9, 4) X(10, 5) X(11, 5) X(12, 6)
+#define SEMCHEB_BATCH_MID(X) X(2, 1) X(3, 1) X(4, 1) X(5, 1) X(6, 1)
 #define SEMCHEB_BATCH_SYS                                  \
   const int slot_ = table_slot(tab, blockIdx.x);           \
   const BatchSysDev &S = sys[tab.sys[slot_]];              \
@@ -1383,6 +1386,34 @@ b_ax64_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
   else ax_body<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64);
 }
 
+// The pencil operator of every order of a level in one launch, the order selected per block. Systems
+// of one order are few waves: three launches of orders 5, 7, 9 each end in a thin last wave (and at
+// orders 2, 3, 4 do not fill the chip at all), where one launch fills those gaps with the other
+// orders' blocks. Registers are those of the largest order (115, still 4 waves per SIMD); LDS is
+// sized by the launch to the orders present. Chosen at setup where it is faster than the launches
+// per order: 16 systems of orders 5, 7, 9, finest level 33.1 -> 25.6 us, the level below 17.1 -> 6.8 us.
+// (The FP64 operator in the same form, orders up to 7 and from 8 on apart, was not: 217 registers.)
+template <bool FINE>
+__global__ void __launch_bounds__(256, 4)
+b_ax32_all_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int src) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  SEMCHEB_BATCH_SYS
+  const BatchLevelDev &L = S.lev[FINE ? 0 : 1];
+  const float *u = src == 0 ? L.d : L.x;
+  const unsigned xb = xcd_block(blk, (unsigned)(tab.begin[slot_ + 1] - tab.begin[slot_]));
+#define SEMCHEB_CASE(A, B)                                                                           \
+  case A:                                                                                            \
+    ax_body_pencil<A, float, uint16_t, GEO_DMA, 0, false, true, BlockShape<A>>(                      \
+        xb, lbox(L), L.E, u, L.G, L.D, L.w, nullptr, nullptr, nullptr, smem_raw);                    \
+    break;
+  if constexpr (FINE) {
+    switch (L.N) { SEMCHEB_BATCH_FINE(SEMCHEB_CASE) }
+  } else {
+    switch (L.N) { SEMCHEB_BATCH_MID(SEMCHEB_CASE) }
+  }
+#undef SEMCHEB_CASE
+}
+
 __global__ void __launch_bounds__(256)
 b_cheb_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int level, int pp, int step, int flags,
               int mode) {
@@ -1413,8 +1444,6 @@ constexpr int batch_ex() {
   constexpr int e = 1000 / ((N + 1) * (N + 1) * N);
   return e < 1 ? 1 : (e > 4 ? 4 : e);
 }
-#define SEMCHEB_BATCH_FINE(X) X(4, 2) X(5, 2) X(6, 3) X(7, 3) X(8, 4) X(9, 4) X(10, 5) X(11, 5) X(12, 6)
-#define SEMCHEB_BATCH_MID(X) X(2, 1) X(3, 1) X(4, 1) X(5, 1) X(6, 1)
 
 // from the weighted residual of the finest level; below it the residual is formed while reading
 template <bool FINE>
@@ -2143,6 +2172,19 @@ int batch_ax_elements_per_block(int N) {
   }
 }
 
+int batch_ax_shared(int N, size_t *lds) {
+#define SEMCHEB_CASE(A)                                            \
+  case A:                                                          \
+    *lds = PencilLds<A, float, true, BlockShape<A>>::bytes;        \
+    return BlockShape<A>::epb;
+  switch (N) {
+    SEMCHEB_CASE(2) SEMCHEB_CASE(3) SEMCHEB_CASE(4) SEMCHEB_CASE(5) SEMCHEB_CASE(6) SEMCHEB_CASE(7)
+    SEMCHEB_CASE(8) SEMCHEB_CASE(9) SEMCHEB_CASE(10) SEMCHEB_CASE(11) SEMCHEB_CASE(12)
+    default: *lds = 0; return 1;
+  }
+#undef SEMCHEB_CASE
+}
+
 BatchTransfer batch_transfer(int N, bool finest) {
 #define SEMCHEB_CASE(A, B)                                                                       \
   case A:                                                                                        \
@@ -2189,6 +2231,12 @@ bool launch_b_ax64(int N, int variant, const LaunchTable &t, const BatchSysDev *
   }
 }
 
+void launch_b_ax32_all(const LaunchTable &t, const BatchSysDev *sys, int level, int src, size_t lds, hipStream_t s) {
+  if (t.count == 0) return;
+  ++g_batched_launches;
+  if (level == 0) hipLaunchKernelGGL((b_ax32_all_kernel<true>), dim3(tgrid(t)), dim3(256), lds, s, t, sys, src);
+  else hipLaunchKernelGGL((b_ax32_all_kernel<false>), dim3(tgrid(t)), dim3(256), lds, s, t, sys, src);
+}
 void launch_b_cheb(const LaunchTable &t, const BatchSysDev *sys, int level, int pp, int step, int flags, int mode,
                    hipStream_t s) {
   if (t.count) {
