@@ -95,7 +95,8 @@ struct Tables {
   std::vector<std::pair<int, LaunchTable>> ax64;              // finest level, FP64
   LaunchTable ax_all[kBatchLevels];                           // all orders in one launch
   size_t lds_all[kBatchLevels] = {0, 0, 0};
-  LaunchTable coarse_rows, fine_nodes, fine_dot2;
+  LaunchTable coarse_rows, fine2;  // rows of the coarse inverse; finest nodes (2 per thread)
+  LaunchTable ax64_parts;           // blocks of the FP64 operator launches in their order
   size_t lds_restrict[kBatchLevels] = {0, 0, 0}, lds_prolong[kBatchLevels] = {0, 0, 0};
 };
 
@@ -129,8 +130,17 @@ Tables build_tables(const sem_batch &B, const std::vector<int> &act) {
     }
   }
   T.coarse_rows = make_table(act, [&](int s) { return B.host[s].nc; });
-  T.fine_nodes = T.node1[0];
-  T.fine_dot2 = make_table(act, [&](int s) { return cdiv(B.host[s].lev[0].n, 512); });
+  T.fine2 = make_table(act, [&](int s) { return cdiv(B.host[s].lev[0].n, 512); });
+  T.ax64_parts.count = 0;
+  T.ax64_parts.begin[0] = 0;
+  for (const auto &g : T.ax64) {
+    LaunchTable &P = T.ax64_parts;
+    const int base = P.begin[P.count];
+    for (int k = 0; k < g.second.count; ++k, ++P.count) {
+      P.sys[P.count] = g.second.sys[k];
+      P.begin[P.count + 1] = base + g.second.begin[k + 1];
+    }
+  }
   return T;
 }
 
@@ -179,7 +189,7 @@ void smooth_b(const sem_ctx *c, const Tables &T, const BatchSysDev *d, int j, in
   }
 }
 
-// z = V(r) for all systems of the tables; the FP32 cycle input must be in place.
+// z = V(r) for all systems of the tables, from the FP32 cycle input into the finest level's x.
 void vcycle_b(const sem_ctx *c, const Tables &T, const BatchSysDev *d, hipStream_t s) {
   const int pre = c->opt.pre_order, post = c->opt.post_order;
   for (int j = 0; j + 1 < kBatchLevels; ++j) {
@@ -191,10 +201,9 @@ void vcycle_b(const sem_ctx *c, const Tables &T, const BatchSysDev *d, hipStream
   }
   launch_b_coarse(T.coarse_rows, d, s);
   for (int j = kBatchLevels - 2; j >= 0; --j) {
-    launch_b_prolong(T.xfer[j], d, j, (j == 0 && post == 0) ? 1 : 0, T.lds_prolong[j], s);
+    launch_b_prolong(T.xfer[j], d, j, T.lds_prolong[j], s);
     if (post > 0) smooth_b(c, T, d, j, post, false, s);
   }
-  if (post > 0) launch_b_widen(T.fine_nodes, d, s);
 }
 
 // Batched autotuner: every operator variant is timed on the batched launch itself (all systems
@@ -263,7 +272,7 @@ sem_status autotune_batched(sem_ctx *c, hipStream_t s) {
     std::vector<double> t(6, -1.0);
     int bestv = 0;
     for (int v = 0; v < 6 && st == SEM_OK; ++v) {
-      t[v] = time_it([&] { launch_b_ax64(g.first, v, g.second, B.dev, s); });
+      t[v] = time_it([&] { launch_b_ax64(g.first, v, g.second, B.dev, B.partials, s); });
       if (t[v] < t[bestv]) bestv = v;
     }
     B.var64[g.first] = bestv;
@@ -352,9 +361,11 @@ sem_status setup_batched_impl(int nsys, const sem_box_mesh *meshes, const int32_
         cheb_coefs(opt->smoother, opt->post_order, L.lmax, V.coef[1]);
       }
     }
-    D.r[0] = sub->kr; D.r[1] = sub->kr2; D.z = sub->kz; D.p = sub->kp; D.w = sub->kw;
+    D.r[0] = sub->kr; D.r[1] = sub->kr2; D.p = sub->kp;
     D.cb = sub->coarse.b; D.cx = sub->coarse.x; D.Minv = sub->coarse.Minv; D.nc = sub->coarse.n;
-    cap += 2 * (cdiv(sub->levels[0].n, 256) + 2);
+    // partials of a system: an operator block covers at least one element, the vector kernels write
+    // at most two values per 1024 unknowns or one per 512
+    cap += std::max<int64_t>(cdiv(sub->levels[0].n, 512) + 2, sub->levels[0].E);
   }
   void *p = nullptr;
   BHIP(c, hipMalloc(&p, sizeof(BatchSysDev) * nsys));
@@ -395,9 +406,8 @@ sem_status solve_batched_impl(sem_ctx *c, const double *b, double *u, double rto
     return SEM_OK;
   };
   // r0 = b, u = 0, FP32 cycle input = b; ||b||^2
-  launch_b_vec(T.fine_nodes, d, 2, s);
-  launch_b_dots(T.fine_nodes, d, 0, 1, B.partials, s);
-  launch_b_finalize(T.fine_nodes, d, B.partials, 1, S_BB, FIN_NONE, s);
+  launch_b_start(T.fine2, d, B.partials, s);
+  launch_b_finalize(T.fine2, d, B.partials, 1, S_BB, FIN_NONE, s);
   sem_status st = read_scal();
   if (st != SEM_OK) return st;
   std::vector<double> bnorm(nsys);
@@ -416,16 +426,20 @@ sem_status solve_batched_impl(sem_ctx *c, const double *b, double *u, double rto
   if (act.empty()) return SEM_OK;
   T = build_tables(B, act);
   vcycle_b(c, T, d, s);
-  launch_b_dots(T.fine_nodes, d, 0, 2, B.partials, s);
-  launch_b_finalize(T.fine_nodes, d, B.partials, 1, S_RZ, FIN_INIT_RZ, s);
-  launch_b_vec(T.fine_nodes, d, 1, s);
+  launch_b_dots(T.node4[0], d, 0, 0, B.partials, s);
+  launch_b_finalize(T.node4[0], d, B.partials, 1, S_RZ, FIN_INIT_RZ, s);
+  launch_b_update_xp(T.fine2, d, 1, s);
+  const bool flexible = c->opt.krylov == SEM_FCG;
   int par = 0;
   for (int it = 1; it <= maxit && !act.empty(); ++it) {
-    for (auto &g : T.ax64) launch_b_ax64(g.first, var64(c, g.first), g.second, d, s);
-    launch_b_dssdot(T.fine_dot2, d, B.partials, s);
-    launch_b_finalize(T.fine_dot2, d, B.partials, 1, S_PW, FIN_NONE, s);
-    launch_b_update_xr(T.fine_nodes, d, par, B.partials, s);
-    launch_b_finalize(T.fine_nodes, d, B.partials, 1, S_RR, FIN_NONE, s);
+    double *parts = B.partials;
+    for (auto &g : T.ax64) {
+      launch_b_ax64(g.first, var64(c, g.first), g.second, d, parts, s);
+      parts += g.second.begin[g.second.count];
+    }
+    launch_b_finalize(T.ax64_parts, d, B.partials, 1, S_PW, FIN_NONE, s);
+    launch_b_update_r(T.fine2, d, par, B.partials, s);
+    launch_b_finalize(T.fine2, d, B.partials, 1, S_RR, FIN_NONE, s);
     st = read_scal();
     if (st != SEM_OK) return st;
     par ^= 1;
@@ -447,6 +461,12 @@ sem_status solve_batched_impl(sem_ctx *c, const double *b, double *u, double rto
       }
       if (rn > rtol * bnorm[q]) next.push_back(q);
     }
+    // systems that stop here take their last u += alpha p now, the others with the next direction
+    std::vector<int> stop;
+    for (int q : act)
+      if (it == maxit || std::find(next.begin(), next.end(), q) == next.end()) stop.push_back(q);
+    if (!stop.empty())
+      launch_b_update_xp(make_table(stop, [&](int q) { return cdiv(B.host[q].lev[0].n, 512); }), d, 2, s);
     if (next.empty()) break;
     if (next.size() != act.size()) {
       act = next;
@@ -458,10 +478,9 @@ sem_status solve_batched_impl(sem_ctx *c, const double *b, double *u, double rto
       break;
     }
     vcycle_b(c, T, d, s);
-    launch_b_dots(T.fine_nodes, d, par, 0, B.partials, s);
-    launch_b_finalize(T.fine_nodes, d, B.partials, 2, S_ZR,
-                      c->opt.krylov == SEM_FCG ? FIN_BETA_FCG : FIN_BETA_PCG, s);
-    launch_b_vec(T.fine_nodes, d, 0, s);
+    launch_b_dots(T.node4[0], d, par, flexible, B.partials, s);
+    launch_b_finalize(T.node4[0], d, B.partials, flexible ? 2 : 1, S_ZR, flexible ? FIN_BETA_FCG : FIN_BETA_PCG, s);
+    launch_b_update_xp(T.fine2, d, 0, s);
   }
   BHIP(c, hipStreamSynchronize(s));
   BHIP(c, hipGetLastError());

@@ -285,7 +285,7 @@ struct BatchLevelDev {
 struct BatchSysDev {
   BatchLevelDev lev[kBatchLevels];
   double *u, *b;                   // caller's solution and right-hand side
-  double *r[2], *z, *p, *w;        // Krylov vectors (r[0], r[1] alternate)
+  double *r[2], *p;                // Krylov vectors (r[0], r[1] alternate)
   double *scal;                    // this system's Krylov scalars
   double *cb, *cx;                 // coarse right-hand side and solution (FP64)
   const double *Minv;              // dense inverse of the coarse operator

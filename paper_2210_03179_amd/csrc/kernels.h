@@ -217,7 +217,7 @@ BatchTransfer batch_transfer(int N, bool finest);
 int64_t batched_launch_count();
 bool launch_b_ax32(int N, int variant, const LaunchTable &t, const BatchSysDev *sys, int level, int src,
                    hipStream_t s);
-bool launch_b_ax64(int N, int variant, const LaunchTable &t, const BatchSysDev *sys, hipStream_t s);
+bool launch_b_ax64(int N, int variant, const LaunchTable &t, const BatchSysDev *sys, double *pdot, hipStream_t s);
 // the single-precision pencil operator of all orders of a level in one launch: elements per block of
 // an order and the block's LDS bytes, of which a launch takes the largest
 int batch_ax_shared(int N, size_t *lds);
@@ -227,13 +227,12 @@ void launch_b_cheb(const LaunchTable &t, const BatchSysDev *sys, int level, int 
 void launch_b_resid(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s);
 void launch_b_restrict(const LaunchTable &t, const BatchSysDev *sys, int level, size_t lds, hipStream_t s);
 void launch_b_dss(const LaunchTable &t, const BatchSysDev *sys, int level, hipStream_t s);
-void launch_b_prolong(const LaunchTable &t, const BatchSysDev *sys, int level, int to_z, size_t lds, hipStream_t s);
-void launch_b_widen(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s);
+void launch_b_prolong(const LaunchTable &t, const BatchSysDev *sys, int level, size_t lds, hipStream_t s);
 void launch_b_coarse(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s);
-void launch_b_dssdot(const LaunchTable &t, const BatchSysDev *sys, double *partials, hipStream_t s);
 void launch_b_finalize(const LaunchTable &t, const BatchSysDev *sys, const double *partials, int nd, int slot, int op,
                        hipStream_t s);
-void launch_b_update_xr(const LaunchTable &t, const BatchSysDev *sys, int par, double *partials, hipStream_t s);
-void launch_b_dots(const LaunchTable &t, const BatchSysDev *sys, int par, int what, double *partials, hipStream_t s);
-void launch_b_vec(const LaunchTable &t, const BatchSysDev *sys, int op, hipStream_t s);
+void launch_b_start(const LaunchTable &t, const BatchSysDev *sys, double *partials, hipStream_t s);
+void launch_b_update_r(const LaunchTable &t, const BatchSysDev *sys, int par, double *partials, hipStream_t s);
+void launch_b_dots(const LaunchTable &t, const BatchSysDev *sys, int par, int two, double *partials, hipStream_t s);
+void launch_b_update_xp(const LaunchTable &t, const BatchSysDev *sys, int op, hipStream_t s);
 }  // namespace semcheb

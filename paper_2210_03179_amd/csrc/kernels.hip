@@ -1165,14 +1165,14 @@ update_r_kernel(int64_t n, double *__restrict__ scal, const double *__restrict__
 // itself): r_new = r - alpha * sum of the copies, with the partial ||r_new||^2 per block and the
 // optional single-precision copy. Lanes take VEC unknowns 64 apart (see strided_first).
 template <int VEC>
-__global__ void __launch_bounds__(256)
-update_r_dss_kernel(Box b, int64_t n, double *__restrict__ scal, const double *__restrict__ r,
-                    const double *__restrict__ wL, double *__restrict__ rnew, double *__restrict__ partials,
-                    float *__restrict__ r32) {
+__device__ __forceinline__ void
+update_r_dss_body(unsigned blk, const Box &b, int64_t n, double *__restrict__ scal, const double *__restrict__ r,
+                  const double *__restrict__ wL, double *__restrict__ rnew, double *__restrict__ partial,
+                  float *__restrict__ r32) {
   __shared__ double sm[4];
   const double alpha = scal[S_RZ] / scal[S_PW];
   double acc = 0.0;
-  const int64_t g0 = strided_first<VEC>(blockIdx.x);
+  const int64_t g0 = strided_first<VEC>(blk);
   if (g0 < n) {
     double rv[VEC], wv[VEC];
 #pragma unroll
@@ -1194,8 +1194,16 @@ update_r_dss_kernel(Box b, int64_t n, double *__restrict__ scal, const double *_
     }
   }
   const double t = block_sum(acc, sm);
-  if (threadIdx.x == 0) partials[blockIdx.x] = t;
-  if (blockIdx.x == 0 && threadIdx.x == 0) scal[S_ALPHA] = alpha;
+  if (threadIdx.x == 0) *partial = t;
+  if (blk == 0 && threadIdx.x == 0) scal[S_ALPHA] = alpha;
+}
+
+template <int VEC>
+__global__ void __launch_bounds__(256)
+update_r_dss_kernel(Box b, int64_t n, double *__restrict__ scal, const double *__restrict__ r,
+                    const double *__restrict__ wL, double *__restrict__ rnew, double *__restrict__ partials,
+                    float *__restrict__ r32) {
+  update_r_dss_body<VEC>(blockIdx.x, b, n, scal, r, wL, rnew, partials + blockIdx.x, r32);
 }
 
 __global__ void update_xp_kernel(int64_t n, const double *__restrict__ scal, double *__restrict__ x,
@@ -1373,17 +1381,19 @@ b_ax32_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int level, i
   else ax_body<N, float, uint16_t, PF>(xb, lbox(L), L.E, u, L.G, L.D, L.w);
 }
 
-// FP64 operator on the finest level applied to the Krylov direction p
+// FP64 operator on the finest level applied to the Krylov direction p, with the partial p . Ap of
+// every block (pdot: the partials of the launch's first block)
 template <int N, int V>
 __global__ void __launch_bounds__(AxShape<N>::block, ((V == 3 || V == 5) ? PencilShape<N>::occ : BVar<N, V>::occ))
-b_ax64_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
+b_ax64_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, double *__restrict__ pdot) {
   SEMCHEB_BATCH_SYS
   const BatchLevelDev &L = S.lev[0];
   constexpr int TILE = BVar<N, V>::tile, PF = BVar<N, V>::pf;
   if constexpr (V == 3 || V == 5)
-    ax_body_pencil<N, double, double, GEO_REG, PencilShape<N>::pfk, false, V == 5>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64);
-  else if constexpr (TILE == 1) ax_body_tile<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64);
-  else ax_body<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64);
+    ax_body_pencil<N, double, double, GEO_REG, PencilShape<N>::pfk, false, V == 5>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64,
+                                                                                   nullptr, pdot);
+  else if constexpr (TILE == 1) ax_body_tile<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64, pdot);
+  else ax_body<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64, nullptr, pdot);
 }
 
 // The pencil operator of every order of a level in one launch, the order selected per block. Systems
@@ -1470,17 +1480,16 @@ b_restrict_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
 // single precision as they are read)
 template <bool FINE>
 __global__ void __launch_bounds__(256)
-b_prolong_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int to_z) {
+b_prolong_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   float *lds = reinterpret_cast<float *>(smem_raw);
   SEMCHEB_BATCH_SYS
   const BatchLevelDev &F = S.lev[FINE ? 0 : 1], &C = S.lev[FINE ? 1 : 2];
   if constexpr (FINE) {
-    double *z = to_z ? S.z : nullptr;
 #define SEMCHEB_CASE(A, B)                                                                                    \
   case A:                                                                                                     \
-    prolong_rows_body<float, A, B, batch_ex<A>(), float>(blk, lbox(F), lbox(C), C.x, F.J, F.x, z, nullptr,   \
-                                                         nullptr, nullptr, lds);                              \
+    prolong_rows_body<float, A, B, batch_ex<A>(), float>(blk, lbox(F), lbox(C), C.x, F.J, F.x, nullptr,      \
+                                                         nullptr, nullptr, nullptr, lds);                     \
     break;
     switch (F.N) { SEMCHEB_BATCH_FINE(SEMCHEB_CASE) }
 #undef SEMCHEB_CASE
@@ -1508,15 +1517,6 @@ b_dss_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int level) {
   else L.b[g] = v;
 }
 
-// finest cycle result widened to the Krylov vector z
-__global__ void __launch_bounds__(256)
-b_widen_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
-  SEMCHEB_BATCH_SYS
-  const int64_t g = (int64_t)blk * blockDim.x + threadIdx.x;
-  const BatchLevelDev &F = S.lev[0];
-  if (g < F.n) S.z[g] = (double)F.x[g];
-}
-
 // exact coarse solve, one block per row of the dense inverse
 __global__ void __launch_bounds__(256)
 b_coarse_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
@@ -1524,19 +1524,11 @@ b_coarse_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
   gemv_row(blk, S.nc, S.nc, S.Minv, S.cb, 0, nullptr, nullptr, nullptr, S.cx, 0);
 }
 
-// Krylov apply: w = DSS(w64) with partials of p . w
-__global__ void __launch_bounds__(256)
-b_dssdot_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, double *__restrict__ partials) {
-  SEMCHEB_BATCH_SYS
-  const BatchLevelDev &L = S.lev[0];
-  dss_dot_body<double, 2>(blk, lbox(L), L.n, L.w64, S.w, S.p, partials + blockIdx.x);
-}
-
-// per-system reduction of the partials written by a launch with the same table
-__global__ void __launch_bounds__(256)
+// per-system reduction of nd values per block written by a launch with the same table
+__global__ void __launch_bounds__(1024)
 b_finalize_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, const double *__restrict__ partials,
                   int nd, int slot, int op) {
-  __shared__ double sm[4];
+  __shared__ double sm[16];
   __shared__ double res[3];
   const int k = blockIdx.x;
   double *scal = sys[tab.sys[k]].scal;
@@ -1560,67 +1552,95 @@ b_finalize_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, const do
   }
 }
 
-// u += alpha p; r[par^1] = r[par] - alpha w (also in FP32 into the cycle input); partial ||r||^2
+// The Krylov vectors are updated as in the single-system solver (update_r_dss, update_xp32): A p stays
+// element-local and is summed where r is updated, the cycle result z stays in single precision (its
+// widened value is exact), and u += alpha p waits for the pass that updates p, or for update_x when
+// the system stops. Separate w, z and u passes before: 16 systems, 2.9 M unknowns, 28 + 19 + 21 + 16
+// us and a widening pass per iteration, now 21 + 20 + 13 us.
+
+// r[0] = b, u = 0, cycle input = b in single precision; partial b . b
 __global__ void __launch_bounds__(256)
-b_update_xr_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int par, double *__restrict__ partials) {
+b_start_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, double *__restrict__ partials) {
   __shared__ double sm[4];
   SEMCHEB_BATCH_SYS
-  const int64_t n = S.lev[0].n;
-  const int64_t g = (int64_t)blk * blockDim.x + threadIdx.x;
+  const int64_t n = S.lev[0].n, g0 = strided_first<2>(blk);
   double acc = 0.0;
-  if (g < n) {
-    const double alpha = S.scal[S_RZ] / S.scal[S_PW];
-    S.u[g] = S.u[g] + alpha * S.p[g];
-    const double rv = S.r[par][g] - alpha * S.w[g];
-    S.r[par ^ 1][g] = rv;
-    S.lev[0].b[g] = (float)rv;
-    acc = rv * rv;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int64_t g = g0 + 64 * q;
+    if (g < n) {
+      const double v = S.b[g];
+      S.r[0][g] = v;
+      S.u[g] = 0.0;
+      S.lev[0].b[g] = (float)v;
+      acc += v * v;
+    }
   }
   const double s = block_sum(acc, sm);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-// dot products: what 0 -> (z.r[par], z.r[par^1]); 1 -> b.b; 2 -> r[par].z
+// r[par^1] = r[par] - alpha A p (also in single precision into the cycle input); partial ||r||^2
 __global__ void __launch_bounds__(256)
-b_dots_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int par, int what,
+b_update_r_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int par, double *__restrict__ partials) {
+  SEMCHEB_BATCH_SYS
+  const BatchLevelDev &L = S.lev[0];
+  update_r_dss_body<2>(blk, lbox(L), L.n, S.scal, S.r[par], L.w64, S.r[par ^ 1], partials + blockIdx.x, L.b);
+}
+
+// partial z . r[par] and, with two, z . r[par^1]
+__global__ void __launch_bounds__(256)
+b_dots_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int par, int two,
               double *__restrict__ partials) {
   __shared__ double sm[4];
   SEMCHEB_BATCH_SYS
-  const int64_t n = S.lev[0].n;
-  const int64_t g = (int64_t)blk * blockDim.x + threadIdx.x;
-  double a0 = 0.0, a1 = 0.0;
-  if (g < n) {
-    if (what == 0) {
-      a0 = S.z[g] * S.r[par][g];
-      a1 = S.z[g] * S.r[par ^ 1][g];
-    } else if (what == 1) {
-      a0 = S.b[g] * S.b[g];
-    } else {
-      a0 = S.r[par][g] * S.z[g];
-    }
+  const int64_t n = S.lev[0].n, g0 = strided_first<4>(blk);
+  const float *z = S.lev[0].x;
+  const double *r1 = S.r[par], *r2 = S.r[par ^ 1];
+  double zv[4], v1[4], v2[4], a0 = 0.0, a1 = 0.0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t g = g0 + 64 * q;
+    zv[q] = g < n ? (double)z[g] : 0.0;
+    v1[q] = g < n ? r1[g] : 0.0;
+    v2[q] = two && g < n ? r2[g] : 0.0;
   }
-  const int nd = what == 0 ? 2 : 1;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    a0 += zv[q] * v1[q];
+    a1 += zv[q] * v2[q];
+  }
+  const int nd = two ? 2 : 1;
   double s = block_sum(a0, sm);
   if (threadIdx.x == 0) partials[(int64_t)blockIdx.x * nd] = s;
-  if (nd > 1) {
+  if (two) {
     s = block_sum(a1, sm);
     if (threadIdx.x == 0) partials[(int64_t)blockIdx.x * nd + 1] = s;
   }
 }
 
-// op 0: p = z + beta p; op 1: p = z; op 2: start (r[0] = b, u = 0, cycle input = b in FP32)
+// op 0: u += alpha p, p = z + beta p; op 1: p = z; op 2: u += alpha p
 __global__ void __launch_bounds__(256)
-b_vec_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int op) {
+b_update_xp_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int op) {
   SEMCHEB_BATCH_SYS
-  const int64_t n = S.lev[0].n;
-  const int64_t g = (int64_t)blk * blockDim.x + threadIdx.x;
-  if (g >= n) return;
-  if (op == 0) S.p[g] = S.z[g] + S.scal[S_BETA] * S.p[g];
-  else if (op == 1) S.p[g] = S.z[g];
-  else {
-    S.r[0][g] = S.b[g];
-    S.u[g] = 0.0;
-    S.lev[0].b[g] = (float)S.b[g];
+  const int64_t n = S.lev[0].n, g0 = strided_first<2>(blk);
+  const float *z = S.lev[0].x;
+  const double alpha = S.scal[S_ALPHA], beta = S.scal[S_BETA];
+  double pv[2], uv[2], zv[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int64_t g = g0 + 64 * q;
+    pv[q] = op != 1 && g < n ? S.p[g] : 0.0;
+    uv[q] = op != 1 && g < n ? S.u[g] : 0.0;
+    zv[q] = op != 2 && g < n ? (double)z[g] : 0.0;
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int64_t g = g0 + 64 * q;
+    if (g >= n) continue;
+    if (op != 1) S.u[g] = uv[q] + alpha * pv[q];
+    if (op == 0) S.p[g] = zv[q] + beta * pv[q];
+    else if (op == 1) S.p[g] = zv[q];
   }
 }
 
@@ -2148,15 +2168,15 @@ void b_ax32_n(const LaunchTable &t, const BatchSysDev *sys, int level, int src, 
   }
 }
 template <int N>
-void b_ax64_n(const LaunchTable &t, const BatchSysDev *sys, int v, hipStream_t s) {
+void b_ax64_n(const LaunchTable &t, const BatchSysDev *sys, int v, double *pdot, hipStream_t s) {
   const dim3 g(tgrid(t)), b(AxShape<N>::block);
   switch (v) {
-    case 1: hipLaunchKernelGGL((b_ax64_kernel<N, 1>), g, b, 0, s, t, sys); break;
-    case 2: hipLaunchKernelGGL((b_ax64_kernel<N, 2>), g, b, 0, s, t, sys); break;
-    case 3: hipLaunchKernelGGL((b_ax64_kernel<N, 3>), g, b, 0, s, t, sys); break;
-    case 4: hipLaunchKernelGGL((b_ax64_kernel<N, 4>), g, b, 0, s, t, sys); break;
-    case 5: hipLaunchKernelGGL((b_ax64_kernel<N, 5>), g, b, 0, s, t, sys); break;
-    default: hipLaunchKernelGGL((b_ax64_kernel<N, 0>), g, b, 0, s, t, sys); break;
+    case 1: hipLaunchKernelGGL((b_ax64_kernel<N, 1>), g, b, 0, s, t, sys, pdot); break;
+    case 2: hipLaunchKernelGGL((b_ax64_kernel<N, 2>), g, b, 0, s, t, sys, pdot); break;
+    case 3: hipLaunchKernelGGL((b_ax64_kernel<N, 3>), g, b, 0, s, t, sys, pdot); break;
+    case 4: hipLaunchKernelGGL((b_ax64_kernel<N, 4>), g, b, 0, s, t, sys, pdot); break;
+    case 5: hipLaunchKernelGGL((b_ax64_kernel<N, 5>), g, b, 0, s, t, sys, pdot); break;
+    default: hipLaunchKernelGGL((b_ax64_kernel<N, 0>), g, b, 0, s, t, sys, pdot); break;
   }
 }
 }  // namespace
@@ -2218,12 +2238,12 @@ bool launch_b_ax32(int N, int variant, const LaunchTable &t, const BatchSysDev *
   }
 }
 
-bool launch_b_ax64(int N, int variant, const LaunchTable &t, const BatchSysDev *sys, hipStream_t s) {
+bool launch_b_ax64(int N, int variant, const LaunchTable &t, const BatchSysDev *sys, double *pdot, hipStream_t s) {
   if (t.count == 0) return true;
   ++g_batched_launches;
   switch (N) {
 #define SEMCHEB_BAX(n) \
-  case n: b_ax64_n<n>(t, sys, variant, s); return true;
+  case n: b_ax64_n<n>(t, sys, variant, pdot, s); return true;
     SEMCHEB_BAX(4) SEMCHEB_BAX(5) SEMCHEB_BAX(6) SEMCHEB_BAX(7) SEMCHEB_BAX(8) SEMCHEB_BAX(9) SEMCHEB_BAX(10)
     SEMCHEB_BAX(11) SEMCHEB_BAX(12)
 #undef SEMCHEB_BAX
@@ -2263,17 +2283,11 @@ void launch_b_dss(const LaunchTable &t, const BatchSysDev *sys, int level, hipSt
     hipLaunchKernelGGL(b_dss_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, level);
   }
 }
-void launch_b_prolong(const LaunchTable &t, const BatchSysDev *sys, int level, int to_z, size_t lds, hipStream_t s) {
+void launch_b_prolong(const LaunchTable &t, const BatchSysDev *sys, int level, size_t lds, hipStream_t s) {
   if (t.count) {
     ++g_batched_launches;
-    if (level == 0) hipLaunchKernelGGL((b_prolong_kernel<true>), dim3(tgrid(t)), dim3(256), lds, s, t, sys, to_z);
-    else hipLaunchKernelGGL((b_prolong_kernel<false>), dim3(tgrid(t)), dim3(256), lds, s, t, sys, 0);
-  }
-}
-void launch_b_widen(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s) {
-  if (t.count) {
-    ++g_batched_launches;
-    hipLaunchKernelGGL(b_widen_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys);
+    if (level == 0) hipLaunchKernelGGL((b_prolong_kernel<true>), dim3(tgrid(t)), dim3(256), lds, s, t, sys);
+    else hipLaunchKernelGGL((b_prolong_kernel<false>), dim3(tgrid(t)), dim3(256), lds, s, t, sys);
   }
 }
 void launch_b_coarse(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s) {
@@ -2282,35 +2296,35 @@ void launch_b_coarse(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s
     hipLaunchKernelGGL(b_coarse_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys);
   }
 }
-void launch_b_dssdot(const LaunchTable &t, const BatchSysDev *sys, double *partials, hipStream_t s) {
-  if (t.count) {
-    ++g_batched_launches;
-    hipLaunchKernelGGL(b_dssdot_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, partials);
-  }
-}
 void launch_b_finalize(const LaunchTable &t, const BatchSysDev *sys, const double *partials, int nd, int slot, int op,
                        hipStream_t s) {
   if (t.count) {
     ++g_batched_launches;
-    hipLaunchKernelGGL(b_finalize_kernel, dim3((unsigned)t.count), dim3(256), 0, s, t, sys, partials, nd, slot, op);
+    hipLaunchKernelGGL(b_finalize_kernel, dim3((unsigned)t.count), dim3(1024), 0, s, t, sys, partials, nd, slot, op);
   }
 }
-void launch_b_update_xr(const LaunchTable &t, const BatchSysDev *sys, int par, double *partials, hipStream_t s) {
+void launch_b_start(const LaunchTable &t, const BatchSysDev *sys, double *partials, hipStream_t s) {
   if (t.count) {
     ++g_batched_launches;
-    hipLaunchKernelGGL(b_update_xr_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, par, partials);
+    hipLaunchKernelGGL(b_start_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, partials);
   }
 }
-void launch_b_dots(const LaunchTable &t, const BatchSysDev *sys, int par, int what, double *partials, hipStream_t s) {
+void launch_b_update_r(const LaunchTable &t, const BatchSysDev *sys, int par, double *partials, hipStream_t s) {
   if (t.count) {
     ++g_batched_launches;
-    hipLaunchKernelGGL(b_dots_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, par, what, partials);
+    hipLaunchKernelGGL(b_update_r_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, par, partials);
   }
 }
-void launch_b_vec(const LaunchTable &t, const BatchSysDev *sys, int op, hipStream_t s) {
+void launch_b_dots(const LaunchTable &t, const BatchSysDev *sys, int par, int two, double *partials, hipStream_t s) {
   if (t.count) {
     ++g_batched_launches;
-    hipLaunchKernelGGL(b_vec_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, op);
+    hipLaunchKernelGGL(b_dots_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, par, two, partials);
+  }
+}
+void launch_b_update_xp(const LaunchTable &t, const BatchSysDev *sys, int op, hipStream_t s) {
+  if (t.count) {
+    ++g_batched_launches;
+    hipLaunchKernelGGL(b_update_xp_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, op);
   }
 }
 }  // namespace semcheb
