@@ -224,7 +224,6 @@ int batch_ax_shared(int N, size_t *lds);
 void launch_b_ax32_all(const LaunchTable &t, const BatchSysDev *sys, int level, int src, size_t lds, hipStream_t s);
 void launch_b_cheb(const LaunchTable &t, const BatchSysDev *sys, int level, int pp, int step, int flags, int mode,
                    hipStream_t s);
-void launch_b_resid(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s);
 void launch_b_restrict(const LaunchTable &t, const BatchSysDev *sys, int level, size_t lds, hipStream_t s);
 void launch_b_dss(const LaunchTable &t, const BatchSysDev *sys, int level, hipStream_t s);
 void launch_b_prolong(const LaunchTable &t, const BatchSysDev *sys, int level, size_t lds, hipStream_t s);

@@ -504,10 +504,12 @@ prolong_rows_body(unsigned blk, const Box &fb, const Box &cb, const TC *__restri
   const int ex0 = gx * EX;
   const int nel = fb.nex - ex0 < EX ? fb.nex - ex0 : EX;
   const int t = threadIdx.x;
-  // owned fine nodes (local i, j, k < NF) of the run: rows of nel*NF contiguous unknowns.
+  // owned fine nodes (local i, j, k < NF) of the run: rows of EX*NF contiguous unknowns, those past
+  // a ragged end lie outside the lattice (the divisions of the index then are by constants: the
+  // kernel issues mostly integer instructions; 32^3, N = 7, mixed solve: 14.16 -> 14.06 ms).
   // When a thread's share is small (kIt nodes) their operands are loaded first, before
   // the contractions, so that all of the thread's loads are in flight together
-  const int RL = nel * NF, nown = NF * NF * RL;
+  constexpr int RL = EX * NF, nown = NF * NF * RL;
   constexpr int kIt = (NF * NF * EX * NF + 255) / 256;
   constexpr bool kPre = kIt <= 12;
   int64_t gq[kPre ? kIt : 1];
@@ -1435,37 +1437,32 @@ b_cheb_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int level, i
                             (float)cf[2], flags, mode, cprev);
 }
 
-__global__ void __launch_bounds__(256)
-b_resid_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
-  SEMCHEB_BATCH_SYS
-  const BatchLevelDev &L = S.lev[0];
-  resid_weight_body<float, 4>(blk, lbox(L), L.n, L.w, L.b, L.r);
-}
-
 // Order transfers: the row bodies of the single-system transfers, compiled for every batched order
 // (pairs N -> N/2 on the finest level, N/2 -> 1 below it) and selected per block, so one launch
 // serves systems of all orders; run lengths of about 1000 fine values per block, at most 4 elements
-// (systems are small: longer runs end ragged). With the orders read at run time (one element per
-// block, index divisions by variables) 16 systems of orders 5, 7, 9 with 6.3 K elements took 31 us
-// down and 32 us up on the finest level, 10 and 11 us below it; now 15.8 and 21.8 us, and 8.8 (with
-// the residual, 6.5 us before as a launch of its own) and 7.7 us.
+// (systems are small: longer runs end ragged; 2800 values and 8 elements were no faster). The
+// blocks of a system go to the XCDs in runs: the short rows of neighbouring blocks end inside the
+// same cache lines. The residual is formed while the restriction reads. With the orders read at run
+// time (one element per block, index divisions by variables) 16 systems of orders 5, 7, 9 with 6.3 K
+// elements took 31 us down and 32 us up on the finest level (15 and 6.5 us more for the residuals),
+// 10 and 11 us below it; now 23.3 and 16.0 us, 8.8 and 7.0 us.
 template <int N>
 constexpr int batch_ex() {
   constexpr int e = 1000 / ((N + 1) * (N + 1) * N);
   return e < 1 ? 1 : (e > 4 ? 4 : e);
 }
 
-// from the weighted residual of the finest level; below it the residual is formed while reading
 template <bool FINE>
 __global__ void __launch_bounds__(256)
 b_restrict_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   float *lds = reinterpret_cast<float *>(smem_raw);
   SEMCHEB_BATCH_SYS
+  const unsigned xb = xcd_block(blk, (unsigned)(tab.begin[slot_ + 1] - tab.begin[slot_]));
   const BatchLevelDev &F = S.lev[FINE ? 0 : 1], &C = S.lev[FINE ? 1 : 2];
 #define SEMCHEB_CASE(A, B)                                                                                      \
   case A:                                                                                                       \
-    restrict_rows_body<float, A, B, batch_ex<A>()>(blk, lbox(F), lbox(C), FINE ? F.r : nullptr, F.J, C.w, F.w, \
+    restrict_rows_body<float, A, B, batch_ex<A>()>(xb, lbox(F), lbox(C), nullptr, F.J, C.w, F.w, \
                                                    F.b, lds);                                                   \
     break;
   if constexpr (FINE) {
@@ -1484,11 +1481,12 @@ b_prolong_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   float *lds = reinterpret_cast<float *>(smem_raw);
   SEMCHEB_BATCH_SYS
+  const unsigned xb = xcd_block(blk, (unsigned)(tab.begin[slot_ + 1] - tab.begin[slot_]));
   const BatchLevelDev &F = S.lev[FINE ? 0 : 1], &C = S.lev[FINE ? 1 : 2];
   if constexpr (FINE) {
 #define SEMCHEB_CASE(A, B)                                                                                    \
   case A:                                                                                                     \
-    prolong_rows_body<float, A, B, batch_ex<A>(), float>(blk, lbox(F), lbox(C), C.x, F.J, F.x, nullptr,      \
+    prolong_rows_body<float, A, B, batch_ex<A>(), float>(xb, lbox(F), lbox(C), C.x, F.J, F.x, nullptr,      \
                                                          nullptr, nullptr, nullptr, lds);                     \
     break;
     switch (F.N) { SEMCHEB_BATCH_FINE(SEMCHEB_CASE) }
@@ -1496,7 +1494,7 @@ b_prolong_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys) {
   } else {
 #define SEMCHEB_CASE(A, B)                                                                                    \
   case A:                                                                                                     \
-    prolong_rows_body<float, A, B, batch_ex<A>(), double>(blk, lbox(F), lbox(C), S.cx, F.J, F.x, nullptr,    \
+    prolong_rows_body<float, A, B, batch_ex<A>(), double>(xb, lbox(F), lbox(C), S.cx, F.J, F.x, nullptr,    \
                                                           nullptr, nullptr, nullptr, lds);                    \
     break;
     switch (F.N) { SEMCHEB_BATCH_MID(SEMCHEB_CASE) }
@@ -2262,12 +2260,6 @@ void launch_b_cheb(const LaunchTable &t, const BatchSysDev *sys, int level, int 
   if (t.count) {
     ++g_batched_launches;
     hipLaunchKernelGGL(b_cheb_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys, level, pp, step, flags, mode);
-  }
-}
-void launch_b_resid(const LaunchTable &t, const BatchSysDev *sys, hipStream_t s) {
-  if (t.count) {
-    ++g_batched_launches;
-    hipLaunchKernelGGL(b_resid_kernel, dim3(tgrid(t)), dim3(256), 0, s, t, sys);
   }
 }
 void launch_b_restrict(const LaunchTable &t, const BatchSysDev *sys, int level, size_t lds, hipStream_t s) {
