@@ -365,16 +365,15 @@ constexpr int rows_ex() {
 }
 
 // Elements per block of the prolongation: row runs of about 450-500 bytes (the partial
-// cache lines at the run ends cost less the longer the run), within 32 KB of LDS per block.
-// FP64 runs stop at 56 unknowns so that a thread's share of the owned nodes (at order 7)
-// still fits the register preload.
+// cache lines at the run ends cost less the longer the run), within 36 KB of LDS per block.
+// FP64 runs stop at 56 unknowns: the contractions of a longer run take more than one pass of the block.
 template <int NF, int NC, typename T>
 constexpr int prolong_ex() {
   constexpr int nf = NF + 1, nc = NC + 1;
-  constexpr int per = (int)sizeof(T) * (nc * nc * nc + nc * nc * nf + nc * nf * nf);
+  constexpr int per = (int)sizeof(T) * (nc * nc * nc + nc * nf * (nc + 1) + nc * nf * (nf + 1) + nf);
   int ex = (sizeof(T) == 4 ? 128 : 56) / NF;
   if (ex > 16) ex = 16;
-  while (ex > 1 && (int)sizeof(T) * nf * nc + ex * per > 32768) --ex;
+  while (ex > 1 && ex * per > 36864) --ex;
   return ex < 1 ? 1 : ex;
 }
 
@@ -389,12 +388,20 @@ inline bool short_runs(const Level &F, int ex) {
   return ex > 1 && (int64_t)((F.nex + ex - 1) / ex) * F.ney * F.nez < 256;
 }
 
-// LDS values of a block: the interpolation matrix and the staged rows with their partial contractions
+// A thread of the contractions reads one line of the element and forms all of its products, the
+// interpolation matrix in scalar registers: an LDS read per value and direction instead of two per
+// multiply-add, which bounded the kernels. LDS values of a block: down, the staged rows and the
+// results of the first two contractions; up, the coarse values and the results; the pitches put the
+// lines that a wave reads together into distinct banks. 24 x 16 x 20 elements, FP64, 7 -> 5:
+// restriction 34.9 -> 25.5 us, prolongation 25.0 -> 20.9 us; 32^3, single precision, 7 -> 3: 26.9 ->
+// 24.4 and 65.9 -> 59.5 us (the latter with the Krylov reductions, near its HBM bytes).
 template <int NF, int NC, int EX>
 struct RowsLds {
   static constexpr int nf = NF + 1, nc = NC + 1, RW = EX * NF + 1;
-  static constexpr int down = nf * nc + nf * nf * RW + EX * nf * nf * nc + EX * nf * nc * nc;
-  static constexpr int up = nf * nc + EX * nc * nc * nc + EX * nc * nc * nf + EX * nc * nf * nf;
+  static constexpr int p1 = nc * (nf + 1);                          // down: per k of t1
+  static constexpr int down = nf * nf * RW + EX * nf * p1 + EX * nf * nc * nc;
+  static constexpr int u1 = nf * (nc + 1), u2 = nf * (nf + 1);      // up: per c of t1 and of t2
+  static constexpr int up = EX * (nc * nc * nc + nc * u1 + nc * u2 + nf);
 };
 
 template <typename T, int NF, int NC, int EX>
@@ -402,10 +409,11 @@ __device__ __forceinline__ void
 restrict_rows_body(unsigned blk, const Box &fb, const Box &cb, const T *__restrict__ rw, const T *__restrict__ Jm,
                    T *__restrict__ rcL, const T *__restrict__ wL, const T *__restrict__ bvec, T *lds) {
   constexpr int nf = NF + 1, nc = NC + 1, RW = EX * NF + 1;
-  T *sJ = lds;
-  T *srow = sJ + nf * nc;                  // fine rows [k][j][i_global]
-  T *t1 = srow + nf * nf * RW;             // [el][k][j][a]
-  T *t2 = t1 + EX * nf * nf * nc;          // [el][k][b][a]
+  using X = RowsLds<NF, NC, EX>;
+  ConstTable<T> *J = (ConstTable<T> *)Jm;
+  T *srow = lds;                           // fine rows [k][j][i_global]
+  T *t1 = srow + nf * nf * RW;             // [el][k](p1) [j][a]
+  T *t2 = t1 + EX * nf * X::p1;            // [el][k][b][a]
   const int ngx = (fb.nex + EX - 1) / EX;
   const int gx = blk % ngx;
   const int ey = (blk / ngx) % fb.ney, ez = blk / (ngx * fb.ney);
@@ -451,32 +459,52 @@ restrict_rows_body(unsigned blk, const Box &fb, const Box &cb, const T *__restri
       srow[q] = g >= 0 ? fine(g, I, J, K) : T(0);
     }
   }
-  for (int q = t; q < nf * nc; q += 256) sJ[q] = Jm[q];
   __syncthreads();
-  for (int q = t; q < EX * nf * nf * nc; q += 256) {  // t1[el][k][j][a] = sum_i J[i][a] f[k][j][i]
-    const int a = q % nc, j = (q / nc) % nf, k = (q / (nc * nf)) % nf, el = q / (nc * nf * nf);
-    const T *row = srow + (k * nf + j) * RW + el * NF;
-    T acc = 0;
+  for (int q = t; q < EX * nf * nf; q += 256) {  // t1[el][k][j][a] = sum_i J[i][a] f[k][j][i]
+    const int jk = q % (nf * nf), el = q / (nf * nf), j = jk % nf, k = jk / nf;
+    const T *row = srow + jk * RW + el * NF;
+    T v[nf];
 #pragma unroll
-    for (int i = 0; i < nf; ++i) acc += sJ[i * nc + a] * row[i];
-    t1[q] = acc;
+    for (int i = 0; i < nf; ++i) v[i] = row[i];
+    T *o = t1 + (el * nf + k) * X::p1 + j * nc;
+#pragma unroll
+    for (int a = 0; a < nc; ++a) {
+      T acc = 0;
+#pragma unroll
+      for (int i = 0; i < nf; ++i) acc += J[i * nc + a] * v[i];
+      o[a] = acc;
+    }
   }
   __syncthreads();
-  for (int q = t; q < EX * nf * nc * nc; q += 256) {  // t2[el][k][b][a] = sum_j J[j][b] t1[el][k][j][a]
-    const int a = q % nc, bq = (q / nc) % nc, k = (q / (nc * nc)) % nf, el = q / (nc * nc * nf);
-    T acc = 0;
+  for (int q = t; q < EX * nf * nc; q += 256) {  // t2[el][k][b][a] = sum_j J[j][b] t1[el][k][j][a]
+    const int a = q % nc, ek = q / nc;
+    T v[nf];
 #pragma unroll
-    for (int j = 0; j < nf; ++j) acc += sJ[j * nc + bq] * t1[((el * nf + k) * nf + j) * nc + a];
-    t2[q] = acc;
+    for (int j = 0; j < nf; ++j) v[j] = t1[ek * X::p1 + j * nc + a];
+    T *o = t2 + ek * nc * nc + a;
+#pragma unroll
+    for (int bq = 0; bq < nc; ++bq) {
+      T acc = 0;
+#pragma unroll
+      for (int j = 0; j < nf; ++j) acc += J[j * nc + bq] * v[j];
+      o[bq * nc] = acc;
+    }
   }
   __syncthreads();
   const int64_t e0 = ex0 + (int64_t)fb.nex * (ey + (int64_t)fb.ney * ez);
-  for (int q = t; q < nel * nc * nc * nc; q += 256) {  // out[el][c][b][a] = sum_k J[k][c] t2[el][k][b][a]
-    const int a = q % nc, bq = (q / nc) % nc, c = (q / (nc * nc)) % nc, el = q / (nc * nc * nc);
-    T acc = 0;
+  for (int q = t; q < nel * nc * nc; q += 256) {  // out[el][c][b][a] = sum_k J[k][c] t2[el][k][b][a]
+    const int ab = q % (nc * nc), el = q / (nc * nc);
+    T v[nf];
 #pragma unroll
-    for (int k = 0; k < nf; ++k) acc += sJ[k * nc + c] * t2[((el * nf + k) * nc + bq) * nc + a];
-    rcL[(e0 + el) * (nc * nc * nc) + (c * nc + bq) * nc + a] = acc;
+    for (int k = 0; k < nf; ++k) v[k] = t2[(el * nf + k) * nc * nc + ab];
+    T *o = rcL + (e0 + el) * (nc * nc * nc) + ab;
+#pragma unroll
+    for (int c = 0; c < nc; ++c) {
+      T acc = 0;
+#pragma unroll
+      for (int k = 0; k < nf; ++k) acc += J[k * nc + c] * v[k];
+      o[c * nc * nc] = acc;
+    }
   }
 }
 
@@ -494,44 +522,44 @@ prolong_rows_body(unsigned blk, const Box &fb, const Box &cb, const TC *__restri
                   T *__restrict__ xf, double *__restrict__ zout, const double *__restrict__ dr1,
                   const double *__restrict__ dr2, double *__restrict__ partials, T *lds) {
   constexpr int nf = NF + 1, nc = NC + 1;
-  T *sJ = lds;
-  T *sc = sJ + nf * nc;                    // [el][c][b][a]
-  T *t1 = sc + EX * nc * nc * nc;          // [el][c][b][i]
-  T *t2 = t1 + EX * nc * nc * nf;          // [el][c][j][i]
+  using X = RowsLds<NF, NC, EX>;
+  ConstTable<T> *J = (ConstTable<T> *)Jm;
+  T *sc = lds;                             // [el][c][b][a]
+  T *t1 = sc + EX * nc * nc * nc;          // [el][c](u1) [b][i]
+  T *t2 = t1 + EX * nc * X::u1;            // [el](nc * u2 + nf) [c](u2) [j][i]
   const int ngx = (fb.nex + EX - 1) / EX;
   const int gx = blk % ngx;
   const int ey = (blk / ngx) % fb.ney, ez = blk / (ngx * fb.ney);
   const int ex0 = gx * EX;
   const int nel = fb.nex - ex0 < EX ? fb.nex - ex0 : EX;
   const int t = threadIdx.x;
-  // owned fine nodes (local i, j, k < NF) of the run: rows of EX*NF contiguous unknowns, those past
-  // a ragged end lie outside the lattice (the divisions of the index then are by constants: the
-  // kernel issues mostly integer instructions; 32^3, N = 7, mixed solve: 14.16 -> 14.06 ms).
-  // When a thread's share is small (kIt nodes) their operands are loaded first, before
-  // the contractions, so that all of the thread's loads are in flight together
-  constexpr int RL = EX * NF, nown = NF * NF * RL;
-  constexpr int kIt = (NF * NF * EX * NF + 255) / 256;
-  constexpr bool kPre = kIt <= 12;
-  int64_t gq[kPre ? kIt : 1];
-  T xq[kPre ? kIt : 1];
-  double r1q[kPre ? kIt : 1], r2q[kPre ? kIt : 1];
-  if constexpr (kPre) {
+  // owned fine nodes (local i, j, k < NF) of the run in columns along k: rows of EX*NF contiguous
+  // unknowns, those past a ragged end lie outside the lattice (the divisions of the index then are
+  // by constants). A thread's operands are loaded before the contractions where it has one column
+  constexpr int RL = EX * NF, ncol = NF * RL;
+  constexpr int kIt = (ncol + 255) / 256;
+  const int64_t plane = (int64_t)fb.nx * fb.ny;
+  T xq[NF];
+  double r1q[NF], r2q[NF];
+  auto column = [&](int q, int64_t &g0) {  // unknown at k = 0 of the column (may lie below the lattice)
+    const int ig = q % RL, j = q / RL;
+    const int I = ex0 * NF + ig, Jy = ey * NF + j;
+    g0 = (I - 1) + (int64_t)fb.nx * ((Jy - 1) + (int64_t)fb.ny * (ez * NF - 1));
+    return q < ncol && I >= 1 && I <= fb.nx && Jy >= 1 && Jy <= fb.ny;
+  };
+  auto inside = [&](int k) { return ez * NF + k >= 1 && ez * NF + k <= fb.nz; };
+  auto load = [&](bool ok, int64_t g0) {
 #pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-      const int q = t + 256 * it;
-      int64_t g = -1;
-      if (q < nown) {
-        const int ig = q % RL, j = (q / RL) % NF, k = q / (RL * NF);
-        g = lattice_index(fb, ex0 * NF + ig, ey * NF + j, ez * NF + k);
-      }
-      gq[it] = g;
-      const int64_t gs = g >= 0 ? g : 0;  // in bounds; the value is not used
-      xq[it] = xf[gs];
-      r1q[it] = dr1 ? dr1[gs] : 0.0;
-      r2q[it] = dr2 ? dr2[gs] : 0.0;
+    for (int k = 0; k < NF; ++k) {
+      const int64_t gs = ok && inside(k) ? g0 + plane * k : 0;  // in bounds; the value is not used
+      xq[k] = xf[gs];
+      r1q[k] = dr1 ? dr1[gs] : 0.0;
+      r2q[k] = dr2 ? dr2[gs] : 0.0;
     }
-  }
-  for (int q = t; q < nf * nc; q += 256) sJ[q] = Jm[q];
+  };
+  int64_t g0 = 0;
+  bool ok = column(t, g0);
+  if constexpr (kIt == 1) load(ok, g0);
   for (int q = t; q < EX * nc * nc * nc; q += 256) {
     const int a = q % nc, bq = (q / nc) % nc, c = (q / (nc * nc)) % nc, el = q / (nc * nc * nc);
     const int64_t g = el < nel ? lattice_index(cb, (ex0 + el) * NC + a, ey * NC + bq, ez * NC + c) : -1;
@@ -539,44 +567,59 @@ prolong_rows_body(unsigned blk, const Box &fb, const Box &cb, const TC *__restri
     sc[q] = g >= 0 ? v : T(0);
   }
   __syncthreads();
-  for (int q = t; q < EX * nc * nc * nf; q += 256) {  // t1[el][c][b][i] = sum_a J[i][a] sc[el][c][b][a]
-    const int i = q % nf, bq = (q / nf) % nc, c = (q / (nf * nc)) % nc, el = q / (nf * nc * nc);
-    T acc = 0;
+  for (int q = t; q < EX * nc * nc; q += 256) {  // t1[el][c][b][i] = sum_a J[i][a] sc[el][c][b][a]
+    const int bq = q % nc, ecl = q / nc;
+    T v[nc];
 #pragma unroll
-    for (int a = 0; a < nc; ++a) acc += sJ[i * nc + a] * sc[((el * nc + c) * nc + bq) * nc + a];
-    t1[q] = acc;
+    for (int a = 0; a < nc; ++a) v[a] = sc[q * nc + a];
+    T *o = t1 + ecl * X::u1 + bq * nf;
+#pragma unroll
+    for (int i = 0; i < nf; ++i) {
+      T acc = 0;
+#pragma unroll
+      for (int a = 0; a < nc; ++a) acc += J[i * nc + a] * v[a];
+      o[i] = acc;
+    }
   }
   __syncthreads();
-  for (int q = t; q < EX * nc * nf * nf; q += 256) {  // t2[el][c][j][i] = sum_b J[j][b] t1[el][c][b][i]
-    const int i = q % nf, j = (q / nf) % nf, c = (q / (nf * nf)) % nc, el = q / (nf * nf * nc);
-    T acc = 0;
+  for (int q = t; q < EX * nc * nf; q += 256) {  // t2[el][c][j][i] = sum_b J[j][b] t1[el][c][b][i]
+    const int i = q % nf, ecl = q / nf, c = ecl % nc, el = ecl / nc;
+    T v[nc];
 #pragma unroll
-    for (int bq = 0; bq < nc; ++bq) acc += sJ[j * nc + bq] * t1[((el * nc + c) * nc + bq) * nf + i];
-    t2[q] = acc;
+    for (int bq = 0; bq < nc; ++bq) v[bq] = t1[ecl * X::u1 + bq * nf + i];
+    T *o = t2 + el * (nc * X::u2 + nf) + c * X::u2 + i;
+#pragma unroll
+    for (int j = 0; j < nf; ++j) {
+      T acc = 0;
+#pragma unroll
+      for (int bq = 0; bq < nc; ++bq) acc += J[j * nc + bq] * v[bq];
+      o[j * nf] = acc;
+    }
   }
   __syncthreads();
   double d1 = 0.0, d2 = 0.0;
-  auto finish = [&](int q, int64_t g, T xl, double r1, double r2) {
-    const int ig = q % RL, j = (q / RL) % NF, k = q / (RL * NF);
-    const int el = ig / NF, i = ig - el * NF;
-    T acc = 0;
+  for (int q = t; q < ncol; q += 256) {
+    if constexpr (kIt > 1) {
+      ok = column(q, g0);
+      load(ok, g0);
+    }
+    const int ig = q % RL, j = q / RL, el = ig / NF, i = ig - el * NF;
+    T v[nc];
 #pragma unroll
-    for (int c = 0; c < nc; ++c) acc += sJ[k * nc + c] * t2[((el * nc + c) * nf + j) * nf + i];
-    const T xv = xl + acc;
-    if (zout) zout[g] = (double)xv;
-    else xf[g] = xv;
-    d1 += (double)xv * r1;
-    d2 += (double)xv * r2;
-  };
-  if constexpr (kPre) {
+    for (int c = 0; c < nc; ++c) v[c] = t2[el * (nc * X::u2 + nf) + c * X::u2 + j * nf + i];
 #pragma unroll
-    for (int it = 0; it < kIt; ++it)
-      if (gq[it] >= 0) finish(t + 256 * it, gq[it], xq[it], r1q[it], r2q[it]);
-  } else {
-    for (int q = t; q < nown; q += 256) {
-      const int ig = q % RL, j = (q / RL) % NF, k = q / (RL * NF);
-      const int64_t g = lattice_index(fb, ex0 * NF + ig, ey * NF + j, ez * NF + k);
-      if (g >= 0) finish(q, g, xf[g], dr1 ? dr1[g] : 0.0, dr2 ? dr2[g] : 0.0);
+    for (int k = 0; k < NF; ++k) {
+      T acc = 0;
+#pragma unroll
+      for (int c = 0; c < nc; ++c) acc += J[k * nc + c] * v[c];
+      if (ok && inside(k)) {
+        const int64_t g = g0 + plane * k;
+        const T xv = xq[k] + acc;
+        if (zout) zout[g] = (double)xv;
+        else xf[g] = xv;
+        d1 += (double)xv * r1q[k];
+        d2 += (double)xv * r2q[k];
+      }
     }
   }
   // optional Krylov reductions over the written result z (z . r1, z . r2): one partial per block
@@ -1445,7 +1488,7 @@ b_cheb_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, int level, i
 // same cache lines. The residual is formed while the restriction reads. With the orders read at run
 // time (one element per block, index divisions by variables) 16 systems of orders 5, 7, 9 with 6.3 K
 // elements took 31 us down and 32 us up on the finest level (15 and 6.5 us more for the residuals),
-// 10 and 11 us below it; now 23.3 and 16.0 us, 8.8 and 7.0 us.
+// 10 and 11 us below it; now 25.5 and 15.9 us, 8.2 and 7.3 us.
 template <int N>
 constexpr int batch_ex() {
   constexpr int e = 1000 / ((N + 1) * (N + 1) * N);
