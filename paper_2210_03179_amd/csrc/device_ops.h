@@ -476,7 +476,8 @@ __device__ __forceinline__ void tri_factors(const TriColumn<T> &c, T tk, T wk, T
 template <int N, typename T>
 __device__ __forceinline__ void ax_body_tri(unsigned blk, const Box &b, int64_t E, const T *__restrict__ u,
                                             const T *__restrict__ tri, const T *__restrict__ gxw,
-                                            const T *__restrict__ Dm, T *__restrict__ wL) {
+                                            const T *__restrict__ Dm, T *__restrict__ wL,
+                                            double *__restrict__ pdot = nullptr) {
   using S = AxShape<N>;
   constexpr int n1 = S::n1, n3 = n1 * n1 * n1;
   __shared__ T sD[n1 * n1];
@@ -517,6 +518,7 @@ __device__ __forceinline__ void ax_body_tri(unsigned blk, const Box &b, int64_t 
 #pragma unroll
   for (int l = 0; l < n1; ++l) Di[l] = sD[i * n1 + l];
   const int lec = active ? le : 0;
+  double dacc = 0.0;
 #pragma unroll 1
   for (int k = 0; k < n1; ++k) {
     T uk = ureg[0];
@@ -536,6 +538,7 @@ __device__ __forceinline__ void ax_body_tri(unsigned blk, const Box &b, int64_t 
     const T wr = g0 * ur + g1 * us + g2 * ut;
     const T ws = g1 * ur + g3 * us + g4 * ut;
     const T wt = g2 * ur + g4 * us + g5 * ut;
+    if (pdot && active) dacc += (double)(ur * wr + us * ws + ut * wt);
     if (active) {
       sr[lec][j][i] = wr;
       ss[lec][j][i] = ws;
@@ -553,6 +556,7 @@ __device__ __forceinline__ void ax_body_tri(unsigned blk, const Box &b, int64_t 
 #pragma unroll
     for (int k = 0; k < n1; ++k) st_out(we + (k * n1 + j) * n1 + i, wreg[k]);
   }
+  if (pdot) block_sum_store(dacc, pdot + blockIdx.x);
 }
 
 // Same operator with the element's whole u tile resident in LDS: plane k of the tile

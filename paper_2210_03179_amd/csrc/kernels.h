@@ -49,9 +49,8 @@ bool launch_ax(const Level &L, const float *u, float *wL, hipStream_t s);
 // The next operator launch of this host thread fills start and stop with its kernel's own start
 // and end timestamps (used to time the Krylov operator inside a solve).
 void set_ax_launch_events(hipEvent_t start, hipEvent_t stop);
-// FP64 operator of a box level with stored factors that also reduces u . A_L u (p . Ap) into
-// one partial per block; returns the number of partials, 0 (nothing launched) when the level
-// cannot (trilinear factors, other level types)
+// FP64 operator of a box level that also reduces u . A_L u (p . Ap) into one partial per block;
+// returns the number of partials, 0 (nothing launched) for other level types
 int launch_ax_dot(const Level &L, const double *u, double *wL, double *partials, hipStream_t s);
 int ax_elems_per_block(int N);
 // r_new = r - alpha * DSS(wL) with alpha = scal[S_RZ] / scal[S_PW], partials of ||r_new||^2 and

@@ -54,10 +54,10 @@ ax_local_kernel(Box b, int64_t E, const T *__restrict__ u, const GT *__restrict_
 template <int N, typename T, int OCC, int TILE = 0>
 __global__ void __launch_bounds__(AxShape<N>::block, OCC)
 ax_tri_kernel(Box b, int64_t E, const T *__restrict__ u, const T *__restrict__ tri, const T *__restrict__ gxw,
-              const T *__restrict__ Dm, T *__restrict__ wL) {
+              const T *__restrict__ Dm, T *__restrict__ wL, double *__restrict__ pdot) {
   if constexpr (TILE == 1)
-    ax_body_pencil<N, T, T, GEO_TRI, 0>(xcd_block(blockIdx.x, gridDim.x), b, E, u, tri, Dm, wL, nullptr, nullptr, gxw);
-  else ax_body_tri<N, T>(xcd_block(blockIdx.x, gridDim.x), b, E, u, tri, gxw, Dm, wL);
+    ax_body_pencil<N, T, T, GEO_TRI, 0>(xcd_block(blockIdx.x, gridDim.x), b, E, u, tri, Dm, wL, nullptr, pdot, gxw);
+  else ax_body_tri<N, T>(xcd_block(blockIdx.x, gridDim.x), b, E, u, tri, gxw, Dm, wL, pdot);
 }
 
 // ------------------------------------------------------------------ summation / vector kernels
@@ -1759,7 +1759,7 @@ void launch_ax_n(const Level &L, const T *u, const GT *G, const T *D, T *wL, int
 
 template <int N, typename T>
 void launch_ax_tri_n(const Level &L, const T *u, const T *tri, const T *gxw, const T *D, T *wL, int variant,
-                     hipStream_t s) {
+                     hipStream_t s, double *pdot) {
   using S = AxShape<N>;
   const unsigned grid = (unsigned)((L.E + S::epb - 1) / S::epb);
   // the pencil form holds whole lines and the column's edge sums: FP64 asks for 2 waves per
@@ -1767,21 +1767,22 @@ void launch_ax_tri_n(const Level &L, const T *u, const T *tri, const T *gxw, con
   constexpr int kTileOcc = sizeof(T) == 8 ? 2 : S::min_waves;
   if (variant == 2)
     hipLaunchKernelGGL((ax_tri_kernel<N, T, kTileOcc, 1>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u,
-                       tri, gxw, D, wL);
+                       tri, gxw, D, wL, pdot);
   else if (variant == 1)
     hipLaunchKernelGGL((ax_tri_kernel<N, T, 1>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u, tri, gxw, D,
-                       wL);
+                       wL, pdot);
   else
     hipLaunchKernelGGL((ax_tri_kernel<N, T, S::min_waves>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u, tri,
-                       gxw, D, wL);
+                       gxw, D, wL, pdot);
 }
 
 template <typename T>
-bool launch_ax_tri(const Level &L, const T *u, const T *tri, const T *gxw, const T *D, T *wL, hipStream_t s) {
+bool launch_ax_tri(const Level &L, const T *u, const T *tri, const T *gxw, const T *D, T *wL, hipStream_t s,
+                   double *pdot = nullptr) {
   const int variant = sizeof(T) == 8 ? L.ax_variant64 : L.ax_variant32;
   switch (L.N) {
 #define SEMCHEB_AXT_CASE(n) \
-  case n: launch_ax_tri_n<n, T>(L, u, tri, gxw, D, wL, variant, s); return true;
+  case n: launch_ax_tri_n<n, T>(L, u, tri, gxw, D, wL, variant, s, pdot); return true;
     SEMCHEB_AXT_CASE(1) SEMCHEB_AXT_CASE(2) SEMCHEB_AXT_CASE(3) SEMCHEB_AXT_CASE(4)
     SEMCHEB_AXT_CASE(5) SEMCHEB_AXT_CASE(6) SEMCHEB_AXT_CASE(7) SEMCHEB_AXT_CASE(8)
     SEMCHEB_AXT_CASE(9) SEMCHEB_AXT_CASE(10) SEMCHEB_AXT_CASE(11) SEMCHEB_AXT_CASE(12)
@@ -1841,8 +1842,10 @@ void set_ax_launch_events(hipEvent_t start, hipEvent_t stop) {
 }
 
 int launch_ax_dot(const Level &L, const double *u, double *wL, double *partials, hipStream_t s) {
-  if (L.type != LVL_SEM || L.tri64 || !L.G64) return 0;
-  if (!launch_ax_t<double, double>(L, u, L.G64, L.D64, wL, s, partials)) return 0;
+  if (L.type != LVL_SEM || !(L.tri64 || L.G64)) return 0;
+  if (L.tri64 ? !launch_ax_tri<double>(L, u, L.tri64, L.gxw64, L.D64, wL, s, partials)
+              : !launch_ax_t<double, double>(L, u, L.G64, L.D64, wL, s, partials))
+    return 0;
   return (int)((L.E + ax_elems_per_block(L.N) - 1) / ax_elems_per_block(L.N));
 }
 
