@@ -226,15 +226,6 @@ resid_weight_kernel(Box b, int64_t n, const T *__restrict__ wL, const T *__restr
   resid_weight_body<T, VEC>(blockIdx.x, b, n, wL, bvec, rw);
 }
 
-// FD: residual r = b - Ad (plain global vectors)
-template <typename T>
-__global__ void resid_plain_kernel(int64_t n, const T *__restrict__ ad, const T *__restrict__ bvec,
-                                   T *__restrict__ r) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= n) return;
-  r[g] = ad ? bvec[g] - ad[g] : bvec[g];
-}
-
 // ------------------------------------------------------------------ order transfers
 // Restriction P^T: for every coarse element, gather the weighted fine residual,
 // contract with J^T along i, j, k and write coarse element-local values.
@@ -1046,9 +1037,9 @@ finalize_kernel(int nblocks, int nd, const double *__restrict__ partials, double
 // Classical Gram-Schmidt projections V_q . w for all q < k in one pass over w. A thread takes two
 // consecutive entries per round (16-byte loads) and the basis in chunks of four vectors, whose
 // loads are all requested before the first product (a chunk past k repeats vector k - 1; its sums
-// are not stored). KM (8, 16 or 32) bounds k: the sums of 32 vectors would leave two waves per SIMD. The former loop tested every vector on its own, so each load waited for the
-// last: 4.66 M unknowns, 4.5 vectors on average, 63.0 -> 39.4 us per launch
-// (the update 63.8 -> 44.0).
+// are not stored). KM (8, 16 or 32) bounds k: the sums of 32 vectors would leave two waves per
+// SIMD. The former loop tested every vector on its own, so each load waited for the last: 4.66 M
+// unknowns, 4.5 vectors on average, 63.0 -> 39.4 us per launch (the update 63.8 -> 44.0).
 constexpr int kChunk = 4;
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 template <int KM>
@@ -1435,8 +1426,8 @@ b_ax64_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, double *__re
   const BatchLevelDev &L = S.lev[0];
   constexpr int TILE = BVar<N, V>::tile, PF = BVar<N, V>::pf;
   if constexpr (V == 3 || V == 5)
-    ax_body_pencil<N, double, double, GEO_REG, PencilShape<N>::pfk, false, V == 5>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64,
-                                                                                   nullptr, pdot);
+    ax_body_pencil<N, double, double, GEO_REG, PencilShape<N>::pfk, false, V == 5>(
+        blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64, nullptr, pdot);
   else if constexpr (TILE == 1) ax_body_tile<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64, pdot);
   else ax_body<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64, nullptr, pdot);
 }
@@ -1712,29 +1703,34 @@ void launch_ax_n(const Level &L, const T *u, const GT *G, const T *D, T *wL, int
   const unsigned grid = (unsigned)((L.E + S::epb - 1) / S::epb);
   if constexpr (sizeof(GT) == 8) {
     if (variant == 6) {
-      ax_launch((ax_local_kernel<N, T, GT, 1, S::min_waves, 5>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
+      ax_launch((ax_local_kernel<N, T, GT, 1, S::min_waves, 5>), dim3(grid), dim3(S::block), s,
+                mkbox(L), L.E, u, G, D, wL, pdot);
       return;
     }
   }
   if constexpr (sizeof(GT) == 8) {
     if (variant == 3) {
-      ax_launch((ax_local_kernel<N, T, GT, PencilShape<N>::pfk, PencilShape<N>::occ, 7>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
+      ax_launch((ax_local_kernel<N, T, GT, PencilShape<N>::pfk, PencilShape<N>::occ, 7>), dim3(grid), dim3(S::block), s,
+                mkbox(L), L.E, u, G, D, wL, pdot);
       return;
     }
     if (variant == 5) {
-      ax_launch((ax_local_kernel<N, T, GT, PencilShape<N>::pfk, PencilShape<N>::occ, 3>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
+      ax_launch((ax_local_kernel<N, T, GT, PencilShape<N>::pfk, PencilShape<N>::occ, 3>), dim3(grid), dim3(S::block), s,
+                mkbox(L), L.E, u, G, D, wL, pdot);
       return;
     }
   }
   if constexpr (sizeof(GT) == 2 && N == 7) {
     if (variant == 6) {
-      ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves, 4>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
+      ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves, 4>), dim3(grid), dim3(S::block), s,
+                mkbox(L), L.E, u, G, D, wL, pdot);
       return;
     }
   }
   if constexpr (sizeof(GT) == 2) {
     if (variant >= 5) {
-      ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves, 2>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
+      ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves, 2>), dim3(grid), dim3(S::block), s,
+                mkbox(L), L.E, u, G, D, wL, pdot);
       return;
     }
   }
@@ -1743,9 +1739,11 @@ void launch_ax_n(const Level &L, const T *u, const GT *G, const T *D, T *wL, int
       ax_launch((ax_local_kernel<N, T, GT, 1, 1, 1>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
   } else if (sizeof(GT) == 2 && variant == 4) {
     if constexpr (sizeof(GT) == 2)
-      ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves, 6>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
+      ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves, 6>), dim3(grid), dim3(S::block), s,
+                mkbox(L), L.E, u, G, D, wL, pdot);
   } else if (variant == 4)
-    ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves, 1>), dim3(grid), dim3(S::block), s, mkbox(L), L.E, u, G, D, wL, pdot);
+    ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves, 1>), dim3(grid), dim3(S::block), s,
+              mkbox(L), L.E, u, G, D, wL, pdot);
   else if (variant == 1)
     ax_launch((ax_local_kernel<N, T, GT, 0, S::min_waves>), dim3(grid), dim3(S::block), s, mkbox(L),
                        L.E, u, G, D, wL, pdot);
@@ -1923,13 +1921,11 @@ void launch_resid_weight(const Level &L, const T *wL, const T *b, T *rw, hipStre
     return;
   }
   constexpr int VEC = 16 / sizeof(T);
-  if (L.type == LVL_SEM && al16(b) && al16(rw))
+  if (al16(b) && al16(rw))
     hipLaunchKernelGGL((resid_weight_kernel<T, VEC>), dim3(nblk((L.n + VEC - 1) / VEC)), dim3(256), 0, s,
                        mkbox(L), L.n, wL, b, rw);
-  else if (L.type == LVL_SEM)
-    hipLaunchKernelGGL((resid_weight_kernel<T, 1>), dim3(nblk(L.n)), dim3(256), 0, s, mkbox(L), L.n, wL, b, rw);
   else
-    hipLaunchKernelGGL((resid_plain_kernel<T>), dim3(nblk(L.n)), dim3(256), 0, s, L.n, wL, b, rw);
+    hipLaunchKernelGGL((resid_weight_kernel<T, 1>), dim3(nblk(L.n)), dim3(256), 0, s, mkbox(L), L.n, wL, b, rw);
 }
 template void launch_resid_weight<double>(const Level &, const double *, const double *, double *, hipStream_t);
 template void launch_resid_weight<float>(const Level &, const float *, const float *, float *, hipStream_t);
