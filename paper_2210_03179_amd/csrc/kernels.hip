@@ -1763,6 +1763,8 @@ void launch_ax_tri_n(const Level &L, const T *u, const T *tri, const T *gxw, con
   // the pencil form holds whole lines and the column's edge sums: FP64 asks for 2 waves per
   // SIMD so they fit without spilling
   constexpr int kTileOcc = sizeof(T) == 8 ? 2 : S::min_waves;
+  // (the plane loop with the p . Ap sums would spill in FP64 at order 7 with 4 waves: 3)
+  constexpr int kLoopOcc = sizeof(T) == 8 && S::min_waves > 3 ? 3 : S::min_waves;
   if (variant == 2)
     hipLaunchKernelGGL((ax_tri_kernel<N, T, kTileOcc, 1>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u,
                        tri, gxw, D, wL, pdot);
@@ -1770,7 +1772,7 @@ void launch_ax_tri_n(const Level &L, const T *u, const T *tri, const T *gxw, con
     hipLaunchKernelGGL((ax_tri_kernel<N, T, 1>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u, tri, gxw, D,
                        wL, pdot);
   else
-    hipLaunchKernelGGL((ax_tri_kernel<N, T, S::min_waves>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u, tri,
+    hipLaunchKernelGGL((ax_tri_kernel<N, T, kLoopOcc>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u, tri,
                        gxw, D, wL, pdot);
 }
 
