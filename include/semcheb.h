@@ -295,7 +295,8 @@ sem_status sem_reset_counts(sem_ctx *ctx);
 /* Host copies of setup arrays, for inspection and testing. `what` is one of
  * "gll_nodes", "gll_weights", "deriv", "interp" (to level+1), "factors",
  * "diag", "mass", "coords", "lambda_max", "coarse_matrix" (dense, small
- * problems only), "krylov_operator_us" (the durations in microseconds of the
+ * problems only), "coarse_steps" (nested-dissection coarse solve: per step its row
+ * groups and stored factor entries; empty for the others), "krylov_operator_us" (the durations in microseconds of the
  * Krylov operator launches of the last sem_solve, one per iteration, timed with
  * events on the solve's stream when the environment sets SEMCHEB_TIME_KRYLOV_OP=1;
  * empty otherwise; box meshes with stored factors), "ax_tuning" (all levels, `level` ignored: per level the

@@ -1276,6 +1276,7 @@ sem_status setup_box_impl(const sem_box_mesh *mesh, const sem_options *opt, hipS
   c->coarse.nd = !lattice && opt->coarse_planes <= 0 && start.size() > 2 && ncoarse < (int64_t(1) << 30);
   if (c->coarse.nd) {
     if (!nested_dissection_factor(Ac, H.nx, H.ny, H.nz, nd, c->err)) return SEM_EINVAL;
+    c->coarse.nd_steps = nd.steps;
   } else if (!block_tridiag_factor(Ac, start, bt, c->err)) {
     return SEM_EINVAL;
   }
@@ -1451,7 +1452,6 @@ sem_status setup_box_impl(const sem_box_mesh *mesh, const sem_options *opt, hipS
       TRY(upload(c, &C.Minv, bt.Minv[0].data(), bt.Minv[0].size(), s));
       TRY(up32(&C.Minv32, bt.Minv[0]));
     } else if (C.nd) {
-      C.nd_steps = nd.steps;
       TRY(upload(c, &C.nd_groups, nd.groups.data(), nd.groups.size(), s));
       TRY(upload(c, &C.nd_col, nd.col.data(), nd.col.size(), s));
       // one copy of the values: the one the context's cycle reads
@@ -2390,6 +2390,12 @@ sem_status sem_host_array(const sem_ctx *c, const char *what, int32_t j, double 
     src = &tmp;
   } else if (w == "coarse_matrix") {
     src = &c->coarse.host_dense;
+  } else if (w == "coarse_steps") {
+    for (const NdStep &st : c->coarse.nd_steps) {
+      tmp.push_back((double)st.ngroups);
+      tmp.push_back((double)st.nval);
+    }
+    src = &tmp;
   } else if (sem) {
     if (j < 0 || j >= (int32_t)c->host_levels.size()) return SEM_EINVAL;
     const BoxLevelHost &h = c->host_levels[j];

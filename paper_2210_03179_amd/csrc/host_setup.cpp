@@ -496,7 +496,7 @@ Csr assemble_q1(const BoxLevelHost &L) {
 }
 
 // ------------------------------------------------------------------ dense SPD inverse
-// Dot products of row a with four rows at once, sums in eight interleaved partial sums each (the
+// Dot products of row a with four rows at once, four interleaved partial sums each (the
 // compiler keeps a single floating-point sum in order and cannot vectorise it).
 static inline void dot4(const double *a, const double *b0, const double *b1, const double *b2, const double *b3,
                         int64_t n, double out[4]) {
@@ -1024,6 +1024,7 @@ struct NdNode {
 
 struct NdTree {
   int dom[3];
+  bool long_axes;  // cut only the axes of at least half the box's longest one
   std::vector<NdNode> nodes;
   int64_t border(const NdNode &s) const {  // lattice points around the box
     int64_t in = 1, out = 1;
@@ -1041,7 +1042,8 @@ struct NdTree {
     }
     return s.child.empty() ? n : n - inner;
   }
-  // cuts every axis of at least three points, `levels` times; boxes of at most 64 points are leaves
+  // cuts every axis of at least three points (and, with long_axes, of half the longest one's), `levels`
+  // times; boxes of at most 64 points are leaves
   int split(const int lo[3], const int hi[3], int depth, int levels) {
     NdNode s{};
     int64_t n = 1;
@@ -1051,9 +1053,12 @@ struct NdTree {
       s.hi[d] = hi[d];
       n *= hi[d] - lo[d];
     }
+    const int longest = std::max({hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2]});
     for (int d = 0; d < 3; ++d) {
-      s.cut[d] = depth < levels && n > 64 && hi[d] - lo[d] >= 3 ? lo[d] + (hi[d] - lo[d]) / 2 : -1;
-      any = any || s.cut[d] >= 0;
+      const int len = hi[d] - lo[d];
+      const bool cut = depth < levels && n > 64 && len >= 3 && (!long_axes || 2 * len >= longest);
+      s.cut[d] = cut ? lo[d] + len / 2 : -1;
+      any = any || cut;
     }
     s.depth = depth;
     if (any)
@@ -1082,30 +1087,45 @@ struct NdTree {
 }  // namespace
 
 bool nested_dissection_factor(const Csr &A, int nx, int ny, int nz, NestedDissection &out, std::string &err) {
-  // Levels of cuts: a step costs about 8 us (launch and dependent memory latencies), its factor
-  // entries 8 bytes at about 5.5 TB/s; the smallest total decides (31^3 unknowns: three levels,
-  // 7 steps, 210 MB; cutting one axis per level would take 13 to 17 steps).
+  // The tree: a step costs about 8 us (launch and dependent memory latencies), its factor entries
+  // 8 bytes at about 5.5 TB/s; the smallest total decides (31^3 unknowns: three levels, 7 steps,
+  // 210 MB; cutting one axis per level would take 13 to 17 steps). Cutting every axis of a long box
+  // separates it by whole length-wise planes, whose dense blocks dominate: 17 x 17 x 200 elements
+  // 1.02 GB and 18.8 s of setup (2.8 GB on the host), cutting the long axis first 277 MB, 2.4 s and
+  // 1.2 GB, while boxes near a cube take fewer steps with all axes cut. So both are candidates, as far as
+  // their factorisation costs at most twice that of the z-plane chain (three dense blocks per
+  // plane) or about half a second on eight cores.
+  const double plane = (double)nx * ny;
+  const double work_limit = std::max(1.25e10, 2.0 * 3.0 * nz * plane * plane * plane);
   NdTree T;
-  double best = 0.0;
-  for (int levels = 1; levels <= 5; ++levels) {
-    NdTree C;
-    C.dom[0] = nx;
-    C.dom[1] = ny;
-    C.dom[2] = nz;
-    const int zero[3] = {0, 0, 0};
-    C.split(zero, C.dom, 0, levels);
-    double entries = 0.0;
-    int H = 0, D = 0;
-    for (const NdNode &s : C.nodes) {
-      const double n = (double)C.own(s);
-      entries += n * (n + 2.0 * (double)C.border(s));
-      H = std::max(H, s.height);
-      D = std::max(D, s.depth);
-    }
-    const double cost = 8.0 * (H + 1 + D) + entries * 8.0 / 5.5e6;
-    if (T.nodes.empty() || cost < best) {
-      best = cost;
-      T = C;
+  double best = 0.0, best_work = 0.0;
+  for (bool long_axes : {false, true}) {
+    bool deeper = true;  // the last tree used all the levels it was given
+    for (int levels = 1; deeper && levels <= 16; ++levels) {
+      NdTree C;
+      C.dom[0] = nx;
+      C.dom[1] = ny;
+      C.dom[2] = nz;
+      C.long_axes = long_axes;
+      const int zero[3] = {0, 0, 0};
+      C.split(zero, C.dom, 0, levels);
+      double entries = 0.0, work = 0.0;
+      int H = 0, D = 0;
+      for (const NdNode &s : C.nodes) {
+        const double n = (double)C.own(s), nb = (double)C.border(s);
+        entries += n * (n + 2.0 * nb);
+        work += n * n * n + nb * n * (n + nb);
+        H = std::max(H, s.height);
+        D = std::max(D, s.depth);
+      }
+      deeper = D == levels;
+      const double cost = 8.0 * (H + 1 + D) + entries * 8.0 / 5.5e6;
+      const bool fits = work <= work_limit, best_fits = best_work <= work_limit;
+      if (T.nodes.empty() || (fits == best_fits ? (fits ? cost < best : work < best_work) : fits)) {
+        best = cost;
+        best_work = work;
+        T = C;
+      }
     }
   }
   const int nn = (int)T.nodes.size();
@@ -1225,7 +1245,7 @@ bool nested_dissection_factor(const Csr &A, int nx, int ny, int nz, NestedDissec
     }
   };
   auto add_step = [&](const std::vector<int> &qs, bool up) {
-    const int64_t g0 = (int64_t)out.groups.size();
+    const int64_t g0 = (int64_t)out.groups.size(), v0 = nval;
     for (int q : qs) {
       if (!up) {
         const int64_t list = (int64_t)out.col.size();
@@ -1248,7 +1268,7 @@ bool nested_dissection_factor(const Csr &A, int nx, int ny, int nz, NestedDissec
         add_rows(q, kv.second, list, (int64_t)out.col.size() - list, true);
       }
     }
-    out.steps.push_back(NdStep{g0, (int64_t)out.groups.size() - g0, up});
+    out.steps.push_back(NdStep{g0, (int64_t)out.groups.size() - g0, nval - v0, up});
   };
   for (int h = 1; h <= H; ++h) add_step(by_height[h], true);
   for (int d = 0; d <= D; ++d) add_step(by_depth[d], false);

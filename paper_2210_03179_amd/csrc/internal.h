@@ -108,6 +108,7 @@ struct NdGroup {
 };
 struct NdStep {
   int64_t group0, ngroups;
+  int64_t nval;  // stored factor entries
   bool up;
 };
 struct NestedDissection {
