@@ -50,11 +50,15 @@ ax_local_kernel(Box b, int64_t E, const T *__restrict__ u, const GT *__restrict_
 
 // Operator of trilinear elements with factors computed in the kernel; OCC as above and
 // TILE 0 (ax_body_tri, u column in registers) or 1 (one thread per pencil).
-// Variants: 0 = (min_waves, 0), 1 = (1, 0), 2 = (min_waves, 1; FP64: 2 waves per SIMD).
-template <int N, typename T, int OCC, int TILE = 0>
+// Variants: 0 = (kLoopOcc, 0), 1 = (1, 0), 2 = (min_waves, 1; FP64: 2 waves per SIMD).
+// DOT: with the p . Ap sums, whose registers a plain application does without. Order 12, 8.8 M
+// nodes, plain: 184 registers and 197 us with the sums' code in the kernel, 168, one wave per SIMD
+// more and 139 us without it; pencils at order 10: 40 registers spilled and 102 us, none and 85 us.
+template <int N, typename T, int OCC, int TILE, bool DOT>
 __global__ void __launch_bounds__(AxShape<N>::block, OCC)
 ax_tri_kernel(Box b, int64_t E, const T *__restrict__ u, const T *__restrict__ tri, const T *__restrict__ gxw,
-              const T *__restrict__ Dm, T *__restrict__ wL, double *__restrict__ pdot) {
+              const T *__restrict__ Dm, T *__restrict__ wL, double *__restrict__ pdot_arg) {
+  double *pdot = DOT ? pdot_arg : nullptr;
   if constexpr (TILE == 1)
     ax_body_pencil<N, T, T, GEO_TRI, 0>(xcd_block(blockIdx.x, gridDim.x), b, E, u, tri, Dm, wL, nullptr, pdot, gxw);
   else ax_body_tri<N, T>(xcd_block(blockIdx.x, gridDim.x), b, E, u, tri, gxw, Dm, wL, pdot);
@@ -1755,25 +1759,34 @@ void launch_ax_n(const Level &L, const T *u, const GT *G, const T *D, T *wL, int
                        D, wL, pdot);
 }
 
-template <int N, typename T>
+template <int N, typename T, bool DOT>
 void launch_ax_tri_n(const Level &L, const T *u, const T *tri, const T *gxw, const T *D, T *wL, int variant,
                      hipStream_t s, double *pdot) {
   using S = AxShape<N>;
   const unsigned grid = (unsigned)((L.E + S::epb - 1) / S::epb);
   // the pencil form holds whole lines and the column's edge sums: FP64 asks for 2 waves per
   // SIMD so they fit without spilling
-  constexpr int kTileOcc = sizeof(T) == 8 ? 2 : S::min_waves;
-  // (the plane loop with the p . Ap sums would spill in FP64 at order 7 with 4 waves: 3)
-  constexpr int kLoopOcc = sizeof(T) == 8 && S::min_waves > 3 ? 3 : S::min_waves;
-  if (variant == 2)
-    hipLaunchKernelGGL((ax_tri_kernel<N, T, kTileOcc, 1>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u,
-                       tri, gxw, D, wL, pdot);
-  else if (variant == 1)
-    hipLaunchKernelGGL((ax_tri_kernel<N, T, 1>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u, tri, gxw, D,
-                       wL, pdot);
-  else
-    hipLaunchKernelGGL((ax_tri_kernel<N, T, kLoopOcc>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u, tri,
-                       gxw, D, wL, pdot);
+  constexpr int kPencilOcc = sizeof(T) == 8 ? 2 : S::min_waves;
+  // the plane loop with the p . Ap sums would spill in FP64 at order 7 with 4 waves, and would lose
+  // its third wave at order 12: 3 for both
+  constexpr int kLoopOcc = DOT && (N == 7 || N == 12) ? 3 : S::min_waves;
+  // from order 10 on launches with the sums take the plane loop of variant 0: the pencils would spill
+  // 40 to 93 registers (order 10, 5832 elements, 505 -> 485 us per FP64 iteration; order 12, 4096
+  // elements, 743 -> 645), and variant 1 leave order 12 two waves (mixed, 553 -> 506 us)
+  if constexpr (!(DOT && N >= 10)) {
+    if (variant == 2) {
+      hipLaunchKernelGGL((ax_tri_kernel<N, T, kPencilOcc, 1, DOT>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E,
+                         u, tri, gxw, D, wL, pdot);
+      return;
+    }
+    if (variant == 1) {
+      hipLaunchKernelGGL((ax_tri_kernel<N, T, 1, 0, DOT>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u, tri,
+                         gxw, D, wL, pdot);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((ax_tri_kernel<N, T, kLoopOcc, 0, DOT>), dim3(grid), dim3(S::block), 0, s, mkbox(L), L.E, u, tri,
+                     gxw, D, wL, pdot);
 }
 
 template <typename T>
@@ -1782,7 +1795,15 @@ bool launch_ax_tri(const Level &L, const T *u, const T *tri, const T *gxw, const
   const int variant = sizeof(T) == 8 ? L.ax_variant64 : L.ax_variant32;
   switch (L.N) {
 #define SEMCHEB_AXT_CASE(n) \
-  case n: launch_ax_tri_n<n, T>(L, u, tri, gxw, D, wL, variant, s, pdot); return true;
+  case n:                                                                                     \
+    if constexpr (sizeof(T) == 8) {                                                           \
+      if (pdot) {                                                                             \
+        launch_ax_tri_n<n, T, true>(L, u, tri, gxw, D, wL, variant, s, pdot);                 \
+        return true;                                                                          \
+      }                                                                                       \
+    }                                                                                         \
+    launch_ax_tri_n<n, T, false>(L, u, tri, gxw, D, wL, variant, s, nullptr);                 \
+    return true;
     SEMCHEB_AXT_CASE(1) SEMCHEB_AXT_CASE(2) SEMCHEB_AXT_CASE(3) SEMCHEB_AXT_CASE(4)
     SEMCHEB_AXT_CASE(5) SEMCHEB_AXT_CASE(6) SEMCHEB_AXT_CASE(7) SEMCHEB_AXT_CASE(8)
     SEMCHEB_AXT_CASE(9) SEMCHEB_AXT_CASE(10) SEMCHEB_AXT_CASE(11) SEMCHEB_AXT_CASE(12)
