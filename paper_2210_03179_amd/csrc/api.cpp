@@ -1595,18 +1595,38 @@ sem_status setup_mesh_impl(const sem_mesh *mesh, const sem_options *opt, hipStre
     TRY(upload(c, &L.winv32, winv32.data(), winv32.size(), s));
     TRY(upload(c, &L.map, h.l2g.data(), h.l2g.size(), s));
     {  // copy lists and the map of the first copies
-      int64_t width = 2;
-      for (int64_t g = 0; g < h.n; ++g) width = std::max(width, h.lrow[g + 1] - h.lrow[g]);
-      L.copies.width = (int32_t)width;
-      L.copies.ld = (h.n + 63) / 64 * 64;
-      std::vector<int32_t> idx((size_t)(width * L.copies.ld), -1), own(h.l2g.size(), -1);
+      int64_t shared = 0;
+      for (int64_t g = 0; g < h.n; ++g) shared += h.lrow[g + 1] - h.lrow[g] > 2;
+      CopyLists &C = L.copies;
+      C.ld = (shared + 63) / 64 * 64;
+      std::vector<int32_t> first(h.n), second(h.n, -1), more((size_t)(kCopySlots * C.ld), -1), tail;
+      std::vector<int32_t> own(h.l2g.size(), -1);
+      int32_t m = 0;
       for (int64_t g = 0; g < h.n; ++g) {
-        for (int64_t p = h.lrow[g]; p < h.lrow[g + 1]; ++p) idx[(p - h.lrow[g]) * L.copies.ld + g] = h.lidx[p];
-        own[h.lidx[h.lrow[g]]] = (int32_t)g;
+        const int32_t *copy = &h.lidx[h.lrow[g]];
+        const int64_t copies = h.lrow[g + 1] - h.lrow[g];
+        first[g] = copy[0];
+        own[copy[0]] = (int32_t)g;
+        if (copies == 2) second[g] = copy[1];
+        if (copies <= 2) continue;
+        const int64_t slots = copies - 1 <= kCopySlots ? copies - 1 : kCopySlots - 1;
+        for (int64_t k = 0; k < slots; ++k) more[k * C.ld + m] = copy[1 + k];
+        if (slots < copies - 1) {
+          more[slots * C.ld + m] = -2 - (int32_t)tail.size();
+          tail.insert(tail.end(), copy + 1 + slots, copy + copies);
+          tail.back() = ~tail.back();
+        }
+        second[g] = -2 - m++;
       }
-      int32_t *dev = nullptr;
-      TRY(upload(c, &dev, idx.data(), idx.size(), s));
-      L.copies.idx = dev;
+      int32_t *dev[4] = {};
+      TRY(upload(c, &dev[0], first.data(), first.size(), s));
+      TRY(upload(c, &dev[1], second.data(), second.size(), s));
+      TRY(upload(c, &dev[2], more.data(), more.size(), s));
+      TRY(upload(c, &dev[3], tail.data(), tail.size(), s));
+      C.first = dev[0];
+      C.second = dev[1];
+      C.more = dev[2];
+      C.tail = dev[3];
       TRY(upload(c, &L.omap, own.data(), own.size(), s));
     }
     if (mixed && !coarse) {

@@ -177,12 +177,16 @@ struct TailArgs {
   double beta_pre[32], beta_post[32];
 };
 
-// The element copies of every unknown of an unstructured mesh, in increasing local index: copy k of
-// unknown g at idx[k * ld + g], -1 past its last one (width >= 2).
+// The element copies of every unknown of an unstructured mesh, in increasing local index: first[g]
+// and second[g], -1 where there is no second. Unknowns of three copies or more are numbered by m
+// (second[g] = -2 - m) and have their further copies at more[k * ld + m], k < kCopySlots, -1 past the
+// last one; if even these do not hold all, the last slot is -2 - t and the list goes on at tail[t], its
+// last entry complemented. 8 bytes per unknown, 28 more per shared edge or vertex unknown and 4 per
+// copy past the eighth, however many elements meet at one vertex.
+constexpr int kCopySlots = 7;
 struct CopyLists {
   int64_t ld = 0;
-  int32_t width = 0;
-  const int32_t *idx = nullptr;
+  const int32_t *first = nullptr, *second = nullptr, *more = nullptr, *tail = nullptr;
 };
 
 struct Level {

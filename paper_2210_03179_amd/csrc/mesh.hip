@@ -34,27 +34,35 @@ ax_map32_kernel(Box b, int64_t E, const int32_t *__restrict__ map, const float *
   ax_body_pencil<N, float, uint16_t, GEO_DMA, 0, true>(xcd_block(blockIdx.x, gridDim.x), b, E, u, G, Dm, wL, map);
 }
 
-// Sum of the copies of unknown g. Two thirds of the unknowns of a high-order element are interior
-// and have one copy, so two list entries are read at once and the rest (up to eight together) only
-// where the second exists.
+// Sum of the copies of unknown g. Two thirds of the unknowns of a high-order element are interior and
+// have one copy, so the further ones are read only where a second exists: two copies' second together
+// with the slots of more, then the slots' values. The slots of consecutive shared unknowns are
+// consecutive: as one list per unknown (7 entries at its own offset) they made cycles of 0.3 M
+// unknowns 3 to 12 % slower; as slots of every unknown they took 32 bytes or more of each (order 7,
+// 12^3 elements, FP64 cycle 123.0 -> 120.0 us with these).
 template <typename T>
 __device__ __forceinline__ T list_sum(const T *__restrict__ w, const CopyLists &S, int64_t g) {
-  const int32_t i0 = S.idx[g], i1 = S.idx[S.ld + g];
+  const int32_t i0 = S.first[g], i1 = S.second[g];
   T s = w[i0];
-  if (i1 >= 0) {
-    int32_t j[6];
-    T v[6];
+  if (i1 != -1) {
+    const bool shared = i1 < 0;
+    int32_t j[kCopySlots];
+    T v[kCopySlots];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) j[k] = k + 2 < S.width ? S.idx[(k + 2) * S.ld + g] : -1;
-    s += w[i1];
+    for (int k = 0; k < kCopySlots; ++k) j[k] = shared ? S.more[k * S.ld + (-2 - i1)] : -1;
+    const T v1 = shared ? T(0) : w[i1];
+    s += v1;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) v[k] = j[k] >= 0 ? w[j[k]] : T(0);
+    for (int k = 0; k < kCopySlots; ++k) v[k] = j[k] >= 0 ? w[j[k]] : T(0);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) s += v[k];
-    for (int k = 8; k < S.width; ++k) {
-      const int32_t i = S.idx[k * S.ld + g];
-      if (i < 0) break;
-      s += w[i];
+    for (int k = 0; k < kCopySlots; ++k) s += v[k];
+    if (j[kCopySlots - 1] < -1) {
+      const int32_t *t = S.tail + (-2 - j[kCopySlots - 1]);
+      int32_t i;
+      do {
+        i = *t++;
+        s += w[i >= 0 ? i : ~i];
+      } while (i >= 0);
     }
   }
   return s;
