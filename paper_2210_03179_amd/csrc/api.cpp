@@ -913,16 +913,10 @@ sem_status autotune_operator(sem_ctx *c, hipStream_t s) {
   // choice. A batch is three launches, or as many as make it last about 300 us (small
   // levels: a 10 us kernel is otherwise timed at the resolution of the events)
   const int rounds = 5;
-  // Levels whose streamed data fits the device's last-level cache many times over would be
-  // timed warm by back-to-back launches, while inside a solve their data arrives from HBM
-  // (the finer level's passes evict it). They are timed one launch at a time after an
-  // eviction: a 512 MB scratch buffer is overwritten before each timed launch. Where the
-  // finest level's own data fits as well, nothing evicts anything inside a solve either
-  // and the warm time decides (16^3, N = 7, FP64: 21 against 24 us for two variants that
-  // rank the other way after an eviction).
+  // levels that autotune_cold names are timed one launch at a time after an eviction: a 512 MB
+  // scratch buffer is overwritten before each timed launch
   constexpr size_t kEvictBytes = size_t(512) << 20;
-  constexpr double kColdBelow = 192.0 * (1 << 20);
-  double finest_bytes[2] = {0.0, 0.0};
+  auto nodes_of = [](const Level &L) { return (int64_t)L.E * (L.N + 1) * (L.N + 1) * (L.N + 1); };
   void *evict = nullptr;
   sem_status st = SEM_OK;
   for (size_t j = 0; j + 1 < c->levels.size() && st == SEM_OK; ++j) {
@@ -938,10 +932,7 @@ sem_status autotune_operator(sem_ctx *c, hipStream_t s) {
                                  : (fp64 ? kAxVariants64 : (L.N == 7 ? kAxVariants : kAxVariantMfma));
       float *times = fp64 ? L.ax_time64_us : L.ax_time32_us;
       for (int v = 0; v < kAxVariants; ++v) times[v] = v < nvar ? 1e30f : -1.0f;
-      const double nodes = (double)L.E * (L.N + 1) * (L.N + 1) * (L.N + 1);
-      const double level_bytes = nodes * (trilinear ? (fp64 ? 16.0 : 8.0) : (fp64 ? 56.0 : 16.0));
-      if (j == 0) finest_bytes[prec] = level_bytes;
-      bool cold = level_bytes < kColdBelow && finest_bytes[prec] >= kColdBelow;
+      bool cold = autotune_cold(nodes_of(L), nodes_of(c->levels[0]), fp64, mixed, trilinear);
       if (cold && !evict && hipMalloc(&evict, kEvictBytes) != hipSuccess) {
         (void)hipGetLastError();
         evict = nullptr;

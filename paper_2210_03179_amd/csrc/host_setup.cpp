@@ -1013,6 +1013,15 @@ void build_fd_hierarchy(int n, double Lx, double Ly, int factor, int coarsest_n,
   }
 }
 
+// ------------------------------------------------------------------ operator timing
+bool autotune_cold(int64_t level_nodes, int64_t finest_nodes, bool fp64, bool mixed, bool trilinear) {
+  constexpr double kCacheBytes = 192.0 * (1 << 20);
+  // bytes per local node: factors, gather and result
+  const double b64 = trilinear ? 16.0 : 56.0, b32 = trilinear ? 8.0 : 16.0;
+  const double finest = finest_nodes * (b64 + (mixed ? b32 : 0.0));
+  return level_nodes * (fp64 ? b64 : b32) < kCacheBytes && finest >= kCacheBytes;
+}
+
 // ------------------------------------------------------------------ nested dissection
 namespace {
 struct NdNode {

@@ -243,6 +243,14 @@ constexpr int kAxVariants64 = 7;
 constexpr int kAxVariantMfma = 6;
 constexpr int kAxTriVariants = 3;  // trilinear operator: register column (min_waves | 1 wave per SIMD), pencils
 
+// Whether setup times the operator variants of a level (local nodes) on evicted data. Levels whose
+// streamed data fits the device's last-level cache many times over would be timed warm by back-to-back
+// launches, while inside a solve their data arrives from HBM: the finest level's passes evict it. Where
+// all that an iteration streams on the finest level fits as well (the operators of both precisions in a
+// mixed context), nothing evicts anything and the warm time decides (16^3, N = 7, FP64: 21 against 24 us
+// for two variants that rank the other way after an eviction).
+bool autotune_cold(int64_t level_nodes, int64_t finest_nodes, bool fp64, bool mixed, bool trilinear);
+
 struct CoarseSolver {
   bool dense = true;
   int64_t n = 0;
