@@ -1172,9 +1172,11 @@ sem_status init_device(sem_ctx *c, hipStream_t s) {
   return SEM_OK;
 }
 
-// First level from which on every sparse level fits one block (see ell_tail_kernel), -1 if none
-// of the smoothed levels does: at most kTailRows unknowns and kTailWidth entries per row each, a
-// dense last level of at most kTailDense unknowns (its inverse is read by one compute unit).
+// First level of a finite-difference hierarchy from which on every level fits one block (see
+// ell_tail_kernel), -1 if none of the smoothed levels does: at most kTailRows unknowns and kTailWidth
+// entries per row each, a dense last level of at most kTailDense unknowns (its inverse is read by one
+// compute unit). Lattice levels never do: a smoothed one has at least three interior points per axis,
+// hence rows of 27 entries.
 int find_tail(const sem_ctx *c) {
   const int last = (int)c->levels.size() - 1;
   if (last < 1 || !c->coarse.dense || c->coarse.n > kTailDense || c->coarse.n != c->levels[last].n) return -1;
@@ -1471,7 +1473,6 @@ sem_status setup_box_impl(const sem_box_mesh *mesh, const sem_options *opt, hipS
       TRY(up32(&C.Xbot32, bt.Xbot));
     }
   }
-  if (lattice) c->tail_from = find_tail(c);
   TRY(alloc_krylov(c, c->levels[0].n));
   HIPCHK(c, hipStreamSynchronize(s));
   TRY(autotune_operator(c, s));

@@ -275,13 +275,10 @@ struct PencilShape {
 // PF = 0: each plane loads its own factors (fewer registers, latency hidden by occupancy).
 // The plane loop stays rolled (the FP64 kernel would not fit its registers
 // unrolled); register arrays are then indexed through selects on k.
-// MAP = true (unstructured meshes): the element's input values are gathered through the
-// local-to-global map (-1: Dirichlet node, value 0) instead of the box lattice arithmetic.
-template <int N, typename T, typename GT, int PF = 1, bool MAP = false>
+template <int N, typename T, typename GT, int PF = 1>
 __device__ __forceinline__ void ax_body(unsigned blk, const Box &b, int64_t E, const T *__restrict__ u,
                                         const GT *__restrict__ G, const T *__restrict__ Dm,
-                                        T *__restrict__ wL, const int32_t *__restrict__ map = nullptr,
-                                        double *__restrict__ pdot = nullptr) {
+                                        T *__restrict__ wL, double *__restrict__ pdot = nullptr) {
   using S = AxShape<N>;
   constexpr int n1 = S::n1, n3 = n1 * n1 * n1;
   __shared__ T sD[n1 * n1];
@@ -314,16 +311,10 @@ __device__ __forceinline__ void ax_body(unsigned blk, const Box &b, int64_t E, c
   for (int k = 0; k < n1; ++k) {
     // unconditional load from a valid index, then select: no branch per load, so the
     // whole column is in flight at once
-    if constexpr (MAP) {
-      const int32_t gi = active ? map[e * n3 + (k * n1 + j) * n1 + i] : -1;
-      const T v = u[gi >= 0 ? gi : 0];
-      ureg[k] = gi >= 0 ? v : T(0);
-    } else {
-      const int K = ez * N + k;
-      const bool ok = inIJ && K >= 1 && K <= b.nz;
-      const T v = u[ok ? gIJ + plane * (K - 1) : 0];
-      ureg[k] = ok ? v : T(0);
-    }
+    const int K = ez * N + k;
+    const bool ok = inIJ && K >= 1 && K <= b.nz;
+    const T v = u[ok ? gIJ + plane * (K - 1) : 0];
+    ureg[k] = ok ? v : T(0);
     wreg[k] = T(0);
   }
   __syncthreads();
@@ -1072,8 +1063,9 @@ struct BlockShape {
 // NT = false reads the factors with ordinary loads: at small odd sizes a plane of factors ends
 // inside a cache line whose rest the next plane's load finds in L1 (order 2: 98 -> 73 us, order
 // 4: 81 -> 71 us on 7 M local nodes; whole-line planes, order 7: no difference).
-// S, lds: elements per block and LDS of a kernel that serves several orders (BlockShape), by
-// default the order's own.
+// MAP (unstructured meshes): the column is gathered through the local-to-global map (-1: Dirichlet
+// node, value 0). S, lds: elements per block and LDS of a kernel that serves several orders
+// (BlockShape), by default the order's own.
 template <int N, typename T, typename GT, int GEO, int PFK, bool MAP = false, bool NT = true, class S = AxShape<N>>
 __device__ __forceinline__ void ax_body_pencil(unsigned blk, const Box &b, int64_t E, const T *__restrict__ u,
                                                const GT *__restrict__ G, const T *__restrict__ Dm,

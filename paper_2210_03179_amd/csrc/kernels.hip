@@ -36,7 +36,7 @@ template <int N, typename T, typename GT, int PF, int OCC, int TILE = 0>
 __global__ void __launch_bounds__(AxShape<N>::block, OCC)
 ax_local_kernel(Box b, int64_t E, const T *__restrict__ u, const GT *__restrict__ G,
                 const T *__restrict__ Dm, T *__restrict__ wL, double *__restrict__ pdot) {
-  if constexpr (TILE == 5) ax_body<N, T, GT, PF>(blockIdx.x, b, E, u, G, Dm, wL, nullptr, pdot);
+  if constexpr (TILE == 5) ax_body<N, T, GT, PF>(blockIdx.x, b, E, u, G, Dm, wL, pdot);
   else if constexpr (TILE == 4) ax_body_mfma<N>(xcd_block(blockIdx.x, gridDim.x), b, E, u, G, Dm, wL);
   else if constexpr (TILE == 3) ax_body_pencil<N, T, GT, GEO_REG, PF>(blockIdx.x, b, E, u, G, Dm, wL, nullptr, pdot);
   else if constexpr (TILE == 7)
@@ -45,7 +45,7 @@ ax_local_kernel(Box b, int64_t E, const T *__restrict__ u, const GT *__restrict_
   else if constexpr (TILE == 2) ax_body_dma<N>(xcd_block(blockIdx.x, gridDim.x), b, E, u, G, Dm, wL);
   else if constexpr (TILE == 1)
     ax_body_tile<N, T, GT, PF>(xcd_block(blockIdx.x, gridDim.x), b, E, u, G, Dm, wL, pdot);
-  else ax_body<N, T, GT, PF>(xcd_block(blockIdx.x, gridDim.x), b, E, u, G, Dm, wL, nullptr, pdot);
+  else ax_body<N, T, GT, PF>(xcd_block(blockIdx.x, gridDim.x), b, E, u, G, Dm, wL, pdot);
 }
 
 // Operator of trilinear elements with factors computed in the kernel; OCC as above and
@@ -1433,7 +1433,7 @@ b_ax64_kernel(LaunchTable tab, const BatchSysDev *__restrict__ sys, double *__re
     ax_body_pencil<N, double, double, GEO_REG, PencilShape<N>::pfk, false, V == 5>(
         blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64, nullptr, pdot);
   else if constexpr (TILE == 1) ax_body_tile<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64, pdot);
-  else ax_body<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64, nullptr, pdot);
+  else ax_body<N, double, double, PF>(blk, lbox(L), L.E, S.p, L.G64, L.D64, L.w64, pdot);
 }
 
 // The pencil operator of every order of a level in one launch, the order selected per block. Systems
