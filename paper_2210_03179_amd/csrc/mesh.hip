@@ -326,7 +326,8 @@ template void launch_sum_lists<float, double>(const Level &, const float *, doub
 template <typename T>
 void launch_cheb_lists(const Level &L, const T *wL, const T *b, const T *r_in, T *r_out, T *d, T *x, const T *invdiag,
                        double a, double bc, double c, int flags, int mode, hipStream_t s, double cprev) {
-  // two unknowns per thread once one per thread fills the chip
+  // two unknowns per thread once one per thread fills the chip (2.4 M unknowns of order 9: FP64 cycle
+  // 333 -> 328 us; 3 M of orders 10 and 12 and 2.7 M of order 7 within 0.7 %, never slower)
   const bool two = L.n >= (int64_t)2048 * 1024;
   if (two)
     hipLaunchKernelGGL((cheb_lists_kernel<T, 2>), dim3(nblk((L.n + 1) / 2)), dim3(256), 0, s, L.n, L.copies, wL, b,
