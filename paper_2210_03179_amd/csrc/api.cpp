@@ -1379,17 +1379,19 @@ sem_status setup_box_impl(const sem_box_mesh *mesh, const sem_options *opt, hipS
       // fast-diagonalisation data of the Schwarz smoother (FP64 always: lambda_max estimate)
       SchwarzHost sh;
       build_schwarz(*mesh, h, sh);
-      const int64_t nb3 = (int64_t)sh.nb * sh.nb * sh.nb;
+      // subdomain results: all (N+3)^3 values, or the element's own (N+1)^3 (RAS)
+      const int64_t side = opt->schwarz == SEM_RAS ? h.n1 : sh.nb;
+      const size_t results = (size_t)L.E * side * side * side;
       L.sw_kind = opt->schwarz;
       TRY(upload(c, &L.swS64, sh.S.data(), sh.S.size(), s));
       TRY(upload(c, &L.swD64, sh.Dinv.data(), sh.Dinv.size(), s));
-      TRY(dalloc(c, &L.swY64, (size_t)L.E * nb3));
+      TRY(dalloc(c, &L.swY64, results));
       TRY(dalloc(c, &L.swT64, (size_t)L.n));
       if (mixed) {
         std::vector<float> S32(sh.S.begin(), sh.S.end()), D32(sh.Dinv.begin(), sh.Dinv.end());
         TRY(upload(c, &L.swS32, S32.data(), S32.size(), s));
         TRY(upload(c, &L.swD32, D32.data(), D32.size(), s));
-        TRY(dalloc(c, &L.swY32, (size_t)L.E * nb3));
+        TRY(dalloc(c, &L.swY32, results));
         TRY(dalloc(c, &L.swT32, (size_t)L.n));
       }
     }

@@ -1,0 +1,29 @@
+"""What contexts keep on the device. hipMalloc hands out memory in pieces of up to 2 MB, so the bounds
+leave 10 % of the arrays in question."""
+import torch
+import pytest
+
+import workload as wl
+from paper_2210_03179_amd.solver import SemSolver
+
+pytestmark = pytest.mark.gpu
+
+
+def used_by(make):
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    s = make()
+    used = free - torch.cuda.mem_get_info()[0]
+    s.close()
+    return used
+
+
+def test_ras_keeps_own_nodes_only():
+    """RAS holds (N+1)^3 results per element in both precisions where ASM holds (N+3)^3."""
+    print("memory of RAS and ASM", flush=True)
+    V = wl.deformed_box((20, 20, 20), 0.05)
+    kw = dict(N=7, precision="mixed", lambda_max=[2.0] * 2, orders=[7, 1])
+    used_by(lambda: SemSolver(V, schwarz="ras", **kw))  # device libraries and pools in place
+    asm = used_by(lambda: SemSolver(V, schwarz="asm", **kw))
+    ras = used_by(lambda: SemSolver(V, schwarz="ras", **kw))
+    assert asm - ras >= 0.9 * 8000 * (10 ** 3 - 8 ** 3) * 12
