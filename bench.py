@@ -229,6 +229,7 @@ def bench_batched(steps, nsys=64):
             "gdof_iter_per_s": round(sum(n * i for n, i in zip(ns, its)) / t_batch / 1e9, 4),
             "iterations_min_max": [min(its), max(its)], "fp64_iterations_min_max": [min(its64), max(its64)],
             "worst_true_relres": worst, "status": st, "operator_variants": tune,
+            "operator_shared": [int(v) for v in bs.host_array("ax_shared")],
             "launches_per_solve": int(bs.host_array("launches")[0]),
             "setup_s": {"fp64_systems": round(t_setup64, 1), "batched": round(t_setupb, 1)}}
 

@@ -313,6 +313,8 @@ sem_status sem_reset_counts(sem_ctx *ctx);
  * Batched contexts: "ax_tuning", one row per (level, order) of the single-precision cycle
  * operators and per order of the FP64 Krylov operator (level -1): level, order, the chosen
  * variant and the six variants' times in microseconds on the batched launch (-1: not timed);
+ * "ax_shared" (n = 2), per cycle level 1 where one launch serves all orders in place of
+ * the variants "ax_tuning" names, and
  * "launches" (n = 1), the number of kernel launches the last sem_solve_batched issued.
  * Returns SEM_EINVAL if `n` does not equal the array size, with the size
  * written to *needed when it is not NULL. */

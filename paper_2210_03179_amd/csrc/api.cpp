@@ -2352,9 +2352,16 @@ sem_status sem_host_array(const sem_ctx *c, const char *what, int32_t j, double 
   if (!c || !what) return SEM_EINVAL;
   if (c->batch) {
     // batched contexts: "ax_tuning", rows (level, order, chosen variant, six timings in us) for
-    // the single-precision cycle operators, level -1 for the FP64 Krylov operator; "launches",
+    // the single-precision cycle operators, level -1 for the FP64 Krylov operator; "ax_shared", per
+    // cycle level 1 where one launch serves all orders instead of the chosen variants; "launches",
     // the number of kernel launches the last batched solve issued
     std::vector<double> tmp;
+    if (std::string(what) == "ax_shared") {
+      if (needed) *needed = kBatchLevels - 1;
+      if (n != kBatchLevels - 1 || !out) return SEM_EINVAL;
+      for (int lev = 0; lev + 1 < kBatchLevels; ++lev) out[lev] = c->batch->shared32[lev] ? 1.0 : 0.0;
+      return SEM_OK;
+    }
     if (std::string(what) == "launches") {
       tmp.push_back((double)c->batch->last_launches);
       if (needed) *needed = 1;

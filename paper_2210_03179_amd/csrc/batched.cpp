@@ -211,7 +211,8 @@ void vcycle_b(const sem_ctx *c, const Tables &T, const BatchSysDev *d, hipStream
 // variants compute the same sums and differ in scheduling, so results agree to rounding. A level
 // with several orders is timed with one launch for all of them as well (apply_b).
 // SEMCHEB_AX_VARIANT=v fixes variant v everywhere; SEMCHEB_AUTOTUNE=0 keeps the defaults
-// (DMA-staged factors in FP32, register columns in FP64).
+// (DMA-staged factors in FP32, register columns in FP64). SEMCHEB_BATCH_SHARED=1 or 0 takes the one
+// launch for all orders on every level, or on none (tests cover both this way).
 sem_status autotune_batched(sem_ctx *c, hipStream_t s) {
   sem_batch &B = *c->batch;
   const int nsys = (int)B.sys.size();
@@ -220,6 +221,8 @@ sem_status autotune_batched(sem_ctx *c, hipStream_t s) {
   const Tables T = build_tables(B, all);
   const char *fv = std::getenv("SEMCHEB_AX_VARIANT");
   const char *at = std::getenv("SEMCHEB_AUTOTUNE");
+  const char *sh = std::getenv("SEMCHEB_BATCH_SHARED");
+  for (int j = 0; j + 1 < kBatchLevels; ++j) B.shared32[j] = sh && sh[0] == '1';
   if (fv || (at && at[0] == '0')) {
     const int v = fv ? std::atoi(fv) : -1;
     if (fv && (v < 0 || v > 5)) { c->err = "SEMCHEB_AX_VARIANT must be in [0, 6)"; return SEM_EINVAL; }
@@ -279,7 +282,7 @@ sem_status autotune_batched(sem_ctx *c, hipStream_t s) {
   }
   // several orders: their launches in turn against the one that serves all of them
   for (int j = 0; j + 1 < kBatchLevels && st == SEM_OK; ++j) {
-    if (T.ax[j].size() < 2) continue;
+    if (sh || T.ax[j].size() < 2) continue;
     auto apply = [&] { apply_b(c, T, B.dev, j, 0, s); };
     double best[2] = {1e30, 1e30};
     for (int round = 0; round < 3; ++round)
