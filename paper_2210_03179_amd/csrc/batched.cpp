@@ -298,6 +298,15 @@ sem_status autotune_batched(sem_ctx *c, hipStream_t s) {
   return st;
 }
 
+// gives a vector of a system's context back
+void release(sem_ctx *sub, double *&p) {
+  auto it = std::find(sub->allocations.begin(), sub->allocations.end(), (void *)p);
+  if (it == sub->allocations.end()) return;
+  (void)hipFree(p);
+  sub->allocations.erase(it);
+  p = nullptr;
+}
+
 sem_status setup_batched_impl(int nsys, const sem_box_mesh *meshes, const int32_t *orders, const sem_options *opt,
                               hipStream_t s, sem_ctx *c) {
   c->kind = kKindBatch;
@@ -368,6 +377,9 @@ sem_status setup_batched_impl(int nsys, const sem_box_mesh *meshes, const int32_
       }
     }
     D.r[0] = sub->kr; D.r[1] = sub->kr2; D.p = sub->kp;
+    // z and w of a single solve: the lambda_max estimates used them, batched solves do not
+    release(sub, sub->kz);
+    release(sub, sub->kw);
     D.cb = sub->coarse.b; D.cx = sub->coarse.x; D.Minv = sub->coarse.Minv; D.nc = sub->coarse.n;
     // partials of a system: an operator block covers at least one element, the vector kernels write
     // at most two values per 1024 unknowns or one per 512

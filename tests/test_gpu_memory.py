@@ -4,7 +4,7 @@ import torch
 import pytest
 
 import workload as wl
-from paper_2210_03179_amd.solver import SemSolver
+from paper_2210_03179_amd.solver import BatchedSolver, SemSolver
 
 pytestmark = pytest.mark.gpu
 
@@ -27,3 +27,12 @@ def test_ras_keeps_own_nodes_only():
     asm = used_by(lambda: SemSolver(V, schwarz="asm", **kw))
     ras = used_by(lambda: SemSolver(V, schwarz="ras", **kw))
     assert asm - ras >= 0.9 * 8000 * (10 ** 3 - 8 ** 3) * 12
+
+
+def test_batch_keeps_no_single_solver_vectors():
+    """Batched solves have no z and no A p: two FP64 vectors less per system than its single solver."""
+    print("memory of a batch", flush=True)
+    verts = [wl.deformed_box((10, 10, 10), 0.05) for _ in range(6)]
+    single = [used_by(lambda V=V: SemSolver(V, N=7, precision="mixed")) for V in verts + verts[:1]][1:]
+    batch = [used_by(lambda: BatchedSolver(verts, [7] * 6)) for _ in range(2)][1]  # the first loads its kernels
+    assert sum(single) - batch >= 0.9 * 6 * 2 * 8 * 69 ** 3 - 2 ** 22
