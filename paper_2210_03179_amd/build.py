@@ -55,7 +55,8 @@ def build(verbose: bool = False) -> str:
 
 # Host code of the library under AddressSanitizer and UndefinedBehaviorSanitizer: the
 # setup, validation and host-array code (api.cpp, host_setup.cpp, batched.cpp) is compiled
-# with the sanitizers on its host pass only; the device code is built as usual. The library
+# with the sanitizers on its host pass only; the device code is built as usual, or taken from the
+# library's own build where that is newer than every source. The library
 # expects the sanitizer runtime to be preloaded into the process (tests/test_host_sanitizers.py).
 SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
             "-Xarch_host", "-fno-omit-frame-pointer", "-Xarch_host", "-fno-sanitize-recover=all"]
@@ -64,7 +65,12 @@ SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=unde
 def build_host_sanitized(out_dir: str) -> str:
     os.makedirs(out_dir, exist_ok=True)
 
+    newest = max(os.path.getmtime(os.path.join(CSRC, f)) for f in os.listdir(CSRC))
+
     def comp(src):
+        built = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
+        if src.endswith(".hip") and os.path.exists(built) and os.path.getmtime(built) > newest:
+            return built
         obj = os.path.join(out_dir, os.path.splitext(src)[0] + ".o")
         extra = SANITIZE if not src.endswith(".hip") else []
         cmd = [HIPCC, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj] + COMMON + extra
