@@ -1056,8 +1056,9 @@ struct BlockShape {
 // multiply-adds, five barriers per element instead of three per plane, and every factor load
 // is independent of the contractions: PFK planes of factors are requested with the input
 // column, the rest once the first contractions have released their registers. Bound by HBM
-// for large meshes: 32^3 elements at N = 7, setup timing, FP64 159.0 (launch-order plane loop)
-// -> 153.9 us, BF16 factors 54.0 (matrix cores) -> 52.7 us, trilinear FP64 133.7 -> 93.6 us;
+// for large meshes: 32^3 elements at N = 7, setup timing (back to back), FP64 159.0 (launch-order
+// plane loop) -> 153.9 us, BF16 factors 54.0 (matrix cores) -> 52.7 us, trilinear FP64 133.7 -> 87.5
+// us; inside the solve the FP64 one takes 174.6 us, the plane loop took 175.7: no gain there;
 // N = 9, 5.8 M nodes: FP64 77.3 -> 72.7, BF16 40.2 -> 31.0 us. With few elements (8^3, N = 7)
 // one memory latency instead of one per plane: 11.3 -> 7.9 us (FP64), 9.0 -> 7.0 us (BF16).
 // NT = false reads the factors with ordinary loads: at small odd sizes a plane of factors ends
